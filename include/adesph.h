@@ -190,8 +190,10 @@ int ade_set_velocities(ade_ctx *ctx, const double *d_v);
 
 /* Cell-linked list: cell hash, counting sort by cell (stable, ordered by
  * particle id within a cell) and the cell-start table, then the particle
- * state is gathered into cell order.  Needed once after init; every step
- * rebuilds it.  For a uniform flow it also checks whether two particles of
+ * state is gathered into cell order.  Needed once after init.  A uniform flow
+ * moves every particle of a plume by the same displacement, so the order and
+ * the cells, taken in the plume's frame, hold for the whole run; a velocity
+ * field rebuilds them every step.  For a uniform flow it also checks whether two particles of
  * a plume share a position (and synchronises the stream for that): the sum
  * of Eq. (4) leaves out pairs at r = 0, and when no two particles coincide
  * the only candidate at r = 0 is a target's own record, whose term is zero,
@@ -206,14 +208,16 @@ int ade_build_cells(ade_ctx *ctx);
  * ADE_VELOCITY_FIELD contexts), else 0. */
 int ade_coincident(const ade_ctx *ctx, int32_t *out);
 
-/* nsteps explicit steps (pair sum of Eqs. 4-5, update of C and x, rebuild).
+/* nsteps explicit steps (pair sum of Eqs. 4-5, update of C and x; with a
+ * velocity field the rebuild of the cells).  The state is in the same buffers
+ * after every call, so a caller may capture the call into a graph of its own.
  * With ADE_CHECK_FINITE on any plume of the context, the concentrations are
  * checked after the last step (the stream is synchronised) and a NaN or an
  * infinity returns ADE_ENONFINITE (the steps have run). */
 int ade_step(ade_ctx *ctx, int64_t nsteps);
 
-/* The same steps replayed from a HIP graph holding one captured step (the
- * finite check as for ade_step, after the replays). */
+/* The same steps replayed from a HIP graph holding 16 captured steps, the rest
+ * launched one by one (the finite check as for ade_step, after them all). */
 int ade_step_graph(ade_ctx *ctx, int64_t nsteps);
 
 /* rhs of Eq. (4) at the current state, written in particle-id order to
@@ -295,8 +299,8 @@ int ade_kernel_timing(ade_ctx *ctx, int32_t mode, double *h_ms, int64_t *h_count
 /* Autotuner: times the pair kernel as a step launches it (update mode; reps
  * launches each plus one warm-up, each timed by HIP events stamped with the
  * kernel's own start and end on the context's stream; the kernel's outputs
- * go to the step's scratch buffers and the next build's cell counts, which
- * are cleared after every launch) over the launch shapes block {64,128,256} x (lanes,
+ * go to the step's scratch buffers, and a velocity field's to the next
+ * build's cell counts, which are cleared after every launch) over the launch shapes block {64,128,256} x (lanes,
  * targets) {(1,2), (1,1), (2,1), (4,1), (4,2)} x persistent {0, 8 workgroups
  * per CU} x xcd_group {8, 32, 128} that are valid and fit the LDS limit (a
  * velocity-field context: block x (lanes, targets) only), keeps the
@@ -326,7 +330,10 @@ int ade_info(const ade_ctx *ctx, int32_t plume, int64_t *n_total, int64_t *n_cel
  * flow kind, and each plume's particle range and cell grid (ADE_EINVAL when
  * any differs, or for a short buffer).  The state holds no other plume
  * parameter: a uniform-flow context steps with its own dispersivities and dt,
- * a velocity-field context with the velocities and tensors saved. */
+ * a velocity-field context with the velocities and tensors saved.  A
+ * uniform-flow state holds the positions and cells of the step they were
+ * built at, and that step; states without it, whose positions and cells are
+ * those of their own step, are read as well. */
 int ade_state_bytes(const ade_ctx *ctx, size_t *bytes);
 int ade_save_state(const ade_ctx *ctx, void *h_buf, size_t bytes);
 int ade_load_state(ade_ctx *ctx, const void *h_buf, size_t bytes);

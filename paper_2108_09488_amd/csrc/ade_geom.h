@@ -28,6 +28,14 @@ __device__ __forceinline__ real h2_of(const PlumeDev& P) {
     return sizeof(real) == 4 ? (real)P.H2f : (real)P.H2d;
 }
 
+// The displacement of plume P between the frame's origin and the current step
+// along axis c, in grid units (0 without a frame: a velocity field).
+__device__ __forceinline__ uint32_t frame_shift(const PlumeDev& P, const FrameStep* __restrict__ f, int c) {
+    if (!f) return 0u;
+    const double us = P.ushift[c];
+    return (uint32_t)((int64_t)rint((double)f->k * us) - (int64_t)rint((double)f->k0 * us));
+}
+
 constexpr int kMaxRowOffsets = 81;  // (2R+1)^2 for R <= 4
 // candidate records each lane fetches together, ahead of their use
 template <int LANES>

@@ -92,8 +92,25 @@ struct CellLists {
     uint32_t* ovf_count;  // [0] pairs added since the last scan, [1] pairs of the current build
 };
 
-// kModeFull: the corrector of the velocity-field predictor-corrector step
+// kModeStep: the update of C (a uniform flow: C + scale dt rhs; a velocity
+// field: also the moves and the next build's counts), kModeRhs: the
+// right-hand side; kModeHalf and kModeFull: the predictor and the corrector
+// of the velocity-field predictor-corrector step
 enum PairMode { kModeStep = 0, kModeHalf = 1, kModeRhs = 2, kModeFull = 3 };
+
+// A uniform flow moves every particle of a plume by the same displacement
+// rint((k+1) u) - rint(k u) (u = PlumeDev::ushift) at step k.  The sorted
+// state of such a context therefore keeps the positions of one step, the
+// frame's origin k0 (0 after a build), with the order and the cell table
+// built from them; the position at step k is the stored one plus frame_shift.
+// The context's step counter is the pair (k, k0).  Separations, hence
+// neighbour sets and pair sums, are the same in the frame.  A step is then one
+// launch with no sort behind it: per step 53.5 -> 27.3 us (512^2 plume, 46
+// neighbours), 149 -> 106 us (six-plume sweep), 417 -> 249 us (256-plume
+// ensemble), 22 -> 8.4 us (64^2 FP64), against a rebuild in every step.
+struct FrameStep {
+    int64_t k, k0;
+};
 
 struct PairLaunch {
     const PlumeDev* plumes;
@@ -112,18 +129,12 @@ struct PairLaunch {
     const uint32_t* spos[3];
     const uint32_t* sid;
     const void* Cpair;      // concentrations entering C_a - C_b
-    const void* Cbase;      // concentrations updated (step mode)
+    const void* Cbase;      // concentrations updated (update mode)
     const uint32_t* cell_start;
-    // step mode outputs
-    uint32_t* upos[3];
-    void* uC;
-    uint32_t* uid;
-    uint32_t* ukey;
-    CellLists lists;
-    const int64_t* step;
-    double scale;           // fraction of the plume's dt: step 1, half 0.5 (unused for rhs)
-    void* out;              // half: S-order output; rhs: id-order output
-    uint4* out_rec;         // half: candidate records with the half-step C (S order)
+    double scale;           // fraction of the plume's dt: step 1, predictor 0.5 (unused for rhs)
+    void* out;              // update: S-order output; rhs: id-order output
+    uint4* out_rec;         // update: candidate records with the new C (S order)
+    int64_t* step;          // update: the step counter, advanced by this launch (null: left)
     hipEvent_t ev0, ev1;    // if set: events stamped at the kernel's start and end
 };
 
@@ -190,13 +201,14 @@ enum AdjGenMode { kAdjGenEuler = 0, kAdjGenHalf = 1, kAdjGenFull = 2 };
 hipError_t launch_adjoint_gen(int dim, int real_bytes, int kernel, int mode, const AdjGenLaunch& a,
                               uint32_t block, hipStream_t s);
 hipError_t launch_pair_gen(int dim, int real_bytes, int kernel, int mode, const GenLaunch& g, hipStream_t s);
-hipError_t launch_pair(int dim, int real_bytes, int kernel, int mode, const PairLaunch& a,
-                       int block, hipStream_t s);
+hipError_t launch_pair(int dim, int real_bytes, int kernel, int mode, const PairLaunch& a, hipStream_t s);
+// C and candidate records of the sorted state from (C, rec)
+hipError_t launch_set_state(int dim, int real_bytes, StateArrays S, const void* C, uint32_t N, hipStream_t s);
 hipError_t launch_read_C(int real_bytes, StateArrays S, uint32_t N, void* out, hipStream_t s);
 hipError_t launch_coincident(int dim, const PlumeDev* plumes, const TileDev* tiles, uint32_t ntiles,
                              StateArrays S, const uint32_t* cell_start, uint32_t* flag, hipStream_t s);
 hipError_t launch_read_x(int dim, const PlumeDev* plumes, const TileDev* tiles, uint32_t ntiles,
-                         StateArrays S, uint32_t N, double* out, hipStream_t s);
+                         StateArrays S, const FrameStep* frame, uint32_t N, double* out, hipStream_t s);
 hipError_t launch_mass(int real_bytes, const PlumeDev* plumes, int nplumes, const TileDev* tiles,
                        uint32_t ntiles, StateArrays S, double* partial, double* out,
                        hipStream_t s);

@@ -26,7 +26,10 @@
 // The forward states are recomputed from checkpoints segment by segment
 // (the cell build and the pair sums are deterministic, so the recompute is
 // bit-identical to the forward run), and the gradient is accumulated in FP64
-// per workgroup in a fixed order.
+// per workgroup in a fixed order.  In a uniform flow the particles keep their
+// order and their relative positions, so a state is its C alone, lambda stays
+// in cell order, and when the states of all steps fit the workspace that the
+// checkpoints take nothing is recomputed.
 //
 // Sensors: Shepard interpolation C_s = sum_b W(r_sb) C_b / sum_b W(r_sb) with
 // the kernel of Eq. (7) (its normalisation cancels); its transpose seeds
@@ -62,13 +65,14 @@ __device__ __forceinline__ uint32_t to_fixed(double x, double L) {
 template <int DIM, typename real, int KERN>
 __global__ __launch_bounds__(256) void k_sensor_fwd(const PlumeDev* __restrict__ plumes,
                                                    const double* __restrict__ xs, int ns,
-                                                   StateArrays S, const uint32_t* __restrict__ cs,
+                                                   StateArrays S, const FrameStep* __restrict__ frame,
+                                                   const uint32_t* __restrict__ cs,
                                                    real* __restrict__ pred, real* __restrict__ den) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= ns) return;
     const PlumeDev P = plumes[0];
     uint32_t u[3] = {0u, 0u, 0u};
-    for (int c = 0; c < DIM; ++c) u[c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L);
+    for (int c = 0; c < DIM; ++c) u[c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L) - frame_shift(P, frame, c);
     const Target T = make_target<DIM>(P, u[0], u[1], u[2]);
     const real H2 = h2_of<real>(P), invHu = (real)P.invHu;
     const uint32_t* px = S.pos[0];
@@ -117,12 +121,14 @@ __global__ __launch_bounds__(256) void k_sensor_resid(int ns, const real* __rest
     if (threadIdx.x == 0) *J = acc;
 }
 
-// lambda^N[id_b] = sum_s r_s W(r_sb), sensors staged through LDS in chunks
+// lambda^N of particle b = sum_s r_s W(r_sb), sensors staged through LDS in
+// chunks; in id order for a velocity field, in cell order in a frame
 template <int DIM, typename real, int KERN>
 __global__ __launch_bounds__(256) void k_sensor_seed(const PlumeDev* __restrict__ plumes,
                                                     const double* __restrict__ xs, int ns,
                                                     const real* __restrict__ rw, StateArrays S,
-                                                    uint32_t N, real* __restrict__ lam) {
+                                                    const FrameStep* __restrict__ frame, uint32_t N,
+                                                    real* __restrict__ lam) {
     __shared__ uint32_t su[256][3];
     __shared__ real sr[256];
     const PlumeDev P = plumes[0];
@@ -137,7 +143,8 @@ __global__ __launch_bounds__(256) void k_sensor_seed(const PlumeDev* __restrict_
         __syncthreads();
         const int s = s0 + threadIdx.x;
         if (s < ns) {
-            for (int c = 0; c < DIM; ++c) su[threadIdx.x][c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L);
+            for (int c = 0; c < DIM; ++c)
+                su[threadIdx.x][c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L) - frame_shift(P, frame, c);
             sr[threadIdx.x] = rw[s];
         }
         __syncthreads();
@@ -155,7 +162,7 @@ __global__ __launch_bounds__(256) void k_sensor_seed(const PlumeDev* __restrict_
             }
         }
     }
-    if (active) lam[S.id[i]] = acc;
+    if (active) lam[frame ? i : S.id[i]] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -181,28 +188,32 @@ struct ARec {
 __device__ __forceinline__ uint32_t fbits(float v) { return __builtin_bit_cast(uint32_t, v); }
 __device__ __forceinline__ float bitsf(uint32_t v) { return __builtin_bit_cast(float, v); }
 
-// lambda from id order into cell order (and the records (x, y, X, lambda))
-template <int DIM, typename real>
-__global__ __launch_bounds__(256) void k_adj_gather(StateArrays S, const real* __restrict__ lam_id,
-                                                   const real* __restrict__ X, uint32_t N,
-                                                   real* __restrict__ lam_s, uint4* __restrict__ arec) {
+// velocity field: lambda from id order into the cell order of a snapshot
+template <typename real>
+__global__ __launch_bounds__(256) void k_adj_gather(StateArrays S, const real* __restrict__ lam_id, uint32_t N,
+                                                   real* __restrict__ lam_s) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N) return;
-    const real l = lam_id[S.id[i]];
-    lam_s[i] = l;
-    if constexpr (ARec<DIM, real>::kPacked) arec[i] = make_uint4(S.pos[0][i], S.pos[1][i], fbits(X[i]), fbits(l));
+    if (i < N) lam_s[i] = lam_id[S.id[i]];
+}
+
+// uniform flow, 2D FP32: the records (x, y, X, u) of the first pass
+__global__ __launch_bounds__(256) void k_adj_pack(StateArrays S, const float* __restrict__ X,
+                                                 const float* __restrict__ u, uint32_t N, uint4* __restrict__ arec) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < N) arec[i] = make_uint4(S.pos[0][i], S.pos[1][i], fbits(X[i]), fbits(u[i]));
 }
 
 struct AdjConst {
     double speed;    // |v|
 };
 
-// kAdjEuler: out = lambda^n (id order) = lam + dt L lam, gradient dt lam . L_k X.
-// kAdjHalf:  out = mu (cell order) = lam + dt/2 L lam, xh_out = C^h (cell
-//            order) = X + dt/2 L X, arec_out = their records, gradient
-//            dt (mu - lam) . L_k X.
-// kAdjFull:  out = lambda^n (id order) = lam + dt L u (u = mu), gradient
-//            dt lam . L_k X (X = C^h).
+// kAdjEuler: out = lambda^n = lam + dt L lam, gradient dt lam . L_k X.
+// kAdjHalf:  out = mu = lam + dt/2 L lam, xh_out = C^h = X + dt/2 L X,
+//            arec_out = their records, gradient dt (mu - lam) . L_k X.
+// kAdjFull:  out = lambda^n = lam + dt L u (u = mu), gradient dt lam . L_k X
+//            (X = C^h).
+// Everything in cell order.  Given Xnext = C^(n-1), the passes that end a step
+// also write the next step's records (x, y, Xnext, lambda^n).
 // A workgroup takes blockDim.x consecutive targets of a tile; its gradient
 // partials go to gpart[3 * blockIdx.x ..].
 enum AdjMode { kAdjEuler = 0, kAdjHalf = 1, kAdjFull = 2 };
@@ -216,6 +227,7 @@ __global__ __launch_bounds__(256) void k_adjoint(const PlumeDev* __restrict__ pl
                                                 const real* __restrict__ X,
                                                 const uint4* __restrict__ arec,
                                                 real* __restrict__ lam_out, real* __restrict__ xh_out,
+                                                const real* __restrict__ Xnext,
                                                 uint4* __restrict__ arec_out, AdjConst ac,
                                                 double* __restrict__ gpart) {
     extern __shared__ uint2 lds_list[];
@@ -301,7 +313,10 @@ __global__ __launch_bounds__(256) void k_adjoint(const PlumeDev* __restrict__ pl
             if constexpr (kPacked) arec_out[i] = make_uint4(T.ux, T.uy, fbits(xh), fbits(mu));
             mult = 0.5 * sd * (double)al;  // mu - lambda
         } else {
-            lam_out[S.id[i]] = fmar((real)sd, al, li);
+            const real ln = fmar((real)sd, al, li);
+            lam_out[i] = ln;
+            if constexpr (kPacked)
+                if (Xnext) arec_out[i] = make_uint4(T.ux, T.uy, fbits(Xnext[i]), fbits(ln));
             mult = (double)li;
         }
     }
@@ -387,7 +402,8 @@ namespace {
         else { CALL(3, double, 2); }                                    \
     } while (0)
 
-// One state snapshot: the sorted particle state and its cell table.
+// One state snapshot of a velocity field: the sorted particle state and its
+// cell table.
 struct Snap {
     uint32_t* pos[3];
     void* C;
@@ -440,6 +456,9 @@ struct SnapSeq {
 
 struct AdjLayout {
     size_t bytes = 0;
+    // velocity field: snapshots; a uniform flow keeps its states in their place
+    char* pool = nullptr;
+    size_t pool_bytes = 0;
     SnapSeq ck;    // checkpoints (every K steps, plus the final state)
     SnapSeq seg;   // states of one segment
     SnapSeq segh;  // velocity field with the predictor-corrector: their half-step states
@@ -448,7 +467,7 @@ struct AdjLayout {
     void* lam_s;
     void* mu_s;  // predictor-corrector: mu and C^h of the step (cell order)
     void* ch_s;
-    uint4* arec;   // 2D FP32: candidate records of the pass (x, y, X, u)
+    uint4* arec;   // 2D FP32, uniform flow: candidate records of the pass (x, y, X, u)
     uint4* arec2;  // predictor-corrector: those of the second pass
     void* pred;
     void* den;
@@ -505,7 +524,9 @@ void adj_layout(const ade_ctx* c, int64_t nsteps, int32_t K, int32_t ns, char* b
         off += count * snap_bytes;
     };
     seq(L.ck, (size_t)nck);
+    L.pool = base;
     seq(L.seg, (size_t)K);
+    L.pool_bytes = off;
     seq(L.segh, gpc ? (size_t)K : 0);
     const size_t N = (size_t)pl.N, rb = (size_t)pl.real_bytes;
     L.lam[0] = take(N * rb);
@@ -613,7 +634,7 @@ int launch_sensor_fwd(ade_ctx* c, const double* d_xs, int32_t ns, const StateArr
     const Plan& pl = c->plan;
     dim3 g((ns + 255) / 256), b(256);
 #define CALL(D, R, K)                                                                        \
-    hipLaunchKernelGGL((k_sensor_fwd<D, R, K>), g, b, 0, c->stream, c->plumes, d_xs, ns, S, cs, \
+    hipLaunchKernelGGL((k_sensor_fwd<D, R, K>), g, b, 0, c->stream, c->plumes, d_xs, ns, S, frame_of(c), cs, \
                        (R*)pred, (R*)den)
     ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
 #undef CALL
@@ -650,31 +671,14 @@ int ade_adjoint_workspace_bytes(const ade_ctx* c, int64_t nsteps, int32_t ckpt_e
 
 namespace {
 
-// The adjoint run of ade_adjoint over a workspace of ws_bytes at d_ws
-// (256-byte aligned; arguments checked by the caller).
-int adjoint_run(ade_ctx* c, int64_t nsteps, int32_t K, const double* d_xs, int32_t ns, const void* d_obs,
-                void* d_ws, size_t ws_bytes, double* h_J, double* h_grad) {
-    int rc = ADE_OK;
-    AdjLayout L;
-    adj_layout(c, nsteps, K, ns, nullptr, L);
-    if (ws_bytes < L.bytes) return fail(ADE_EWORKSPACE, "adjoint workspace too small: need %zu bytes", L.bytes);
-    adj_layout(c, nsteps, K, ns, static_cast<char*>(d_ws), L);
-
+// misfit of the state S and the adjoint seed of its last step in lam
+int misfit_and_seed(ade_ctx* c, const AdjLayout& L, const StateArrays& S, const double* d_xs, int32_t ns,
+                    const void* d_obs, void* lam) {
     const Plan& pl = c->plan;
     const uint32_t N = (uint32_t)pl.N;
     hipStream_t st = c->stream;
-    const Snap cur = live(c);
-    const int64_t nck = (nsteps + K - 1) / K;
-
-    // forward run with checkpoints
-    for (int64_t n = 0; n < nsteps; ++n) {
-        if (n % K == 0 && (rc = copy_state(c, L.ck[(size_t)(n / K)], cur))) return rc;
-        if ((rc = enqueue_step(c))) return rc;
-    }
-    if ((rc = copy_state(c, L.ck[(size_t)nck], cur))) return rc;
-
-    // misfit and the adjoint seed at step N
-    if ((rc = launch_sensor_fwd(c, d_xs, ns, c->S, c->cell_start, L.pred, L.den))) return rc;
+    int rc;
+    if ((rc = launch_sensor_fwd(c, d_xs, ns, S, c->cell_start, L.pred, L.den))) return rc;
     if (pl.real_bytes == 4)
         hipLaunchKernelGGL((k_sensor_resid<float>), dim3(1), dim3(256), 0, st, ns, (const float*)L.pred,
                            (const float*)L.den, (const float*)d_obs, (float*)L.rw, L.J);
@@ -682,115 +686,20 @@ int adjoint_run(ade_ctx* c, int64_t nsteps, int32_t K, const double* d_xs, int32
         hipLaunchKernelGGL((k_sensor_resid<double>), dim3(1), dim3(256), 0, st, ns, (const double*)L.pred,
                            (const double*)L.den, (const double*)d_obs, (double*)L.rw, L.J);
     HIPCHK(hipGetLastError());
-    {
-        dim3 g((N + 255) / 256), b(256);
+    dim3 g((N + 255) / 256), b(256);
 #define CALL(D, R, KK)                                                                             \
     hipLaunchKernelGGL((k_sensor_seed<D, R, KK>), g, b, 0, st, c->plumes, d_xs, ns, (const R*)L.rw, \
-                       c->S, N, (R*)L.lam[0])
-        ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
+                       S, frame_of(c), N, (R*)lam)
+    ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
 #undef CALL
-        HIPCHK(hipGetLastError());
-    }
+    HIPCHK(hipGetLastError());
     HIPCHK(hipMemsetAsync(L.gpart, 0, (size_t)pl.ntiles * kAdjMaxSubs * 3 * 8, st));
-    const uint32_t ab = adj_block(pl), asubs = kTile / ab;
-    const size_t ashm = (size_t)ab * (size_t)pl.list_cap * 8u;
-    if (ashm > kPairLdsMax) return fail(ADE_EINVAL, "candidate lists of the adjoint do not fit in LDS");
+    return ADE_OK;
+}
 
-    AdjConst ac{};
-    {
-        const PlumeDev& P = pl.plumes[0];
-        double sp = 0;
-        for (int k = 0; k < pl.dim; ++k) sp += P.vel[k] * P.vel[k];
-        sp = std::sqrt(sp);
-        ac.speed = sp;
-    }
-
-    // reverse sweep, segment by segment
-    int li = 0;
-    for (int64_t sgi = nck - 1; sgi >= 0; --sgi) {
-        const int64_t n0 = sgi * K, n1 = std::min<int64_t>(n0 + K, nsteps);
-        if ((rc = copy_state(c, cur, L.ck[(size_t)sgi]))) return rc;
-        const bool gpc = pl.general && pl.integrator == ADE_PC;
-        for (int64_t n = n0; n < n1; ++n) {
-            if ((rc = copy_state(c, L.seg[(size_t)(n - n0)], cur))) return rc;
-            if (gpc) {  // the step in its stages, keeping the half-step state
-                if ((rc = run_gen(c, kModeHalf, nullptr)) || (rc = enqueue_build(c, 0))) return rc;
-                if ((rc = copy_state(c, L.segh[(size_t)(n - n0)], cur))) return rc;
-                if ((rc = run_gen(c, kModeFull, nullptr)) || (rc = enqueue_build(c, 1))) return rc;
-            } else if ((rc = enqueue_step(c))) {
-                return rc;
-            }
-        }
-        for (int64_t n = n1 - 1; n >= n0; --n) {
-            const Snap sn = L.seg[(size_t)(n - n0)];
-            const StateArrays Sa = snap_arrays(c, sn);
-            dim3 g((N + 255) / 256), b(256);
-            const dim3 ag(pl.ntiles * asubs), abk(ab);
-#define GATHER(D, R, KK)                                                                                   \
-    hipLaunchKernelGGL((k_adj_gather<D, R>), g, b, 0, st, Sa, (const R*)L.lam[li], (const R*)sn.C, N,       \
-                       (R*)L.lam_s, L.arec)
-            ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, GATHER);
-#undef GATHER
-#define LAUNCH(D, R, KK, MODE, U, X, REC, OUT, XH, RECOUT)                                                   \
-    hipLaunchKernelGGL((k_adjoint<D, R, KK, MODE>), ag, abk, (uint32_t)ashm, st, c->plumes, c->tiles, Sa,     \
-                       sn.cs, (const R*)(U), (const R*)L.lam_s, (const R*)(X), (const uint4*)(REC), (R*)(OUT), \
-                       (R*)(XH), (uint4*)(RECOUT), ac, L.gpart)
-            if (pl.general) {  // velocity field
-                AdjGenLaunch ga;
-                ga.plumes = c->plumes;
-                ga.tiles = c->tiles;
-                ga.ntiles = pl.ntiles;
-                ga.list_cap = pl.list_cap;
-                ga.S = Sa;
-                ga.cell_start = sn.cs;
-                ga.lam_s = L.lam_s;
-                ga.lam_id = nullptr;
-                ga.lam_out = L.lam[1 - li];
-                ga.gpart = L.gpart;
-                if (pl.integrator == ADE_PC) {
-                    // y = L2 lambda at the half-step state (its own cells and
-                    // order), then lambda^n = lambda + dt y + dt^2/2 L1 y here
-                    const Snap sh = L.segh[(size_t)(n - n0)];
-                    const StateArrays Sh = snap_arrays(c, sh);
-#define GATHER_H(D, R, KK)                                                                                 \
-    hipLaunchKernelGGL((k_adj_gather<D, R>), g, b, 0, st, Sh, (const R*)L.lam[li], (const R*)sh.C, N,       \
-                       (R*)L.lam_s, L.arec)
-                    ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, GATHER_H);
-#undef GATHER_H
-                    AdjGenLaunch gh = ga;
-                    gh.S = Sh;
-                    gh.cell_start = sh.cs;
-                    gh.lam_out = L.y;
-                    HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenHalf, gh, kGenAdjBlock, st));
-#define GATHER_Y(D, R, KK)                                                                                 \
-    hipLaunchKernelGGL((k_adj_gather<D, R>), g, b, 0, st, Sa, (const R*)L.y, (const R*)sn.C, N,             \
-                       (R*)L.lam_s, L.arec)
-                    ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, GATHER_Y);
-#undef GATHER_Y
-                    ga.lam_id = L.lam[li];
-                    HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenFull, ga, kGenAdjBlock, st));
-                } else {
-                    HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenEuler, ga, kGenAdjBlock, st));
-                }
-            } else if (pl.integrator == ADE_PC) {
-#define CALL(D, R, KK)                                                                                    \
-    LAUNCH(D, R, KK, kAdjHalf, L.lam_s, sn.C, L.arec, L.mu_s, L.ch_s, L.arec2);                              \
-    LAUNCH(D, R, KK, kAdjFull, L.mu_s, L.ch_s, L.arec2, L.lam[1 - li], nullptr, nullptr)
-                ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
-#undef CALL
-            } else {
-#define CALL(D, R, KK) LAUNCH(D, R, KK, kAdjEuler, L.lam_s, sn.C, L.arec, L.lam[1 - li], nullptr, nullptr)
-                ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
-#undef CALL
-            }
-#undef LAUNCH
-            HIPCHK(hipGetLastError());
-            li = 1 - li;
-        }
-    }
-    // leave the context at step nsteps
-    if ((rc = copy_state(c, cur, L.ck[(size_t)nck]))) return rc;
-    const uint32_t nparts = pl.ntiles * (pl.general ? kAdjMaxSubs : asubs);  // workgroups of the passes
+// the gradient from its nparts workgroup partials, and J, to the host
+int reduce_to_host(ade_ctx* c, const AdjLayout& L, uint32_t nparts, double* h_J, double* h_grad) {
+    hipStream_t st = c->stream;
     hipLaunchKernelGGL(k_grad_reduce, dim3(1), dim3(256), 0, st, L.gpart, nparts, L.grad);
     HIPCHK(hipGetLastError());
     double hostv[4];
@@ -800,6 +709,208 @@ int adjoint_run(ade_ctx* c, int64_t nsteps, int32_t K, const double* d_xs, int32
     for (int k = 0; k < 3; ++k) h_grad[k] = hostv[k];
     *h_J = hostv[3];
     return ADE_OK;
+}
+
+// The adjoint of a uniform flow.  The snapshots' part of the workspace holds
+// the states (C only): all of them when they fit, else the checkpoints and one
+// segment.
+int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, const double* d_xs, int32_t ns,
+                    const void* d_obs, double* h_J, double* h_grad) {
+    const Plan& pl = c->plan;
+    const uint32_t N = (uint32_t)pl.N;
+    const size_t sbytes = (size_t)N * (size_t)pl.real_bytes, slot = (sbytes + 255) & ~size_t(255);
+    hipStream_t st = c->stream;
+    const bool pc = pl.integrator == ADE_PC, packed = pl.dim == 2 && pl.real_bytes == 4;
+    const uint32_t ab = adj_block(pl), asubs = kTile / ab;
+    const size_t ashm = (size_t)ab * (size_t)pl.list_cap * 8u;
+    if (ashm > kPairLdsMax) return fail(ADE_EINVAL, "candidate lists of the adjoint do not fit in LDS");
+
+    char* pool = L.pool;
+    size_t room = L.pool_bytes;
+    uint4* arecs[2] = {L.arec, L.arec2};  // the passes' records, read and written in turn
+    if (packed && !pc) {
+        arecs[1] = reinterpret_cast<uint4*>(pool);
+        const size_t rbytes = ((size_t)N * 16 + 255) & ~size_t(255);
+        pool += rbytes;
+        room -= rbytes;
+    }
+    const int64_t nck = (nsteps + K - 1) / K;
+    const bool all = room / slot >= (size_t)nsteps + 1;
+    if (!all && room / slot < (size_t)(nck + 1 + K)) return fail(ADE_EWORKSPACE, "adjoint workspace too small");
+    // where state n lives: checkpoints 0 .. nck (the last one the final
+    // state), then the segment's states by n mod K
+    auto state = [&](int64_t n) -> void* {
+        size_t k;
+        if (all) k = (size_t)n;
+        else if (n == nsteps) k = (size_t)nck;
+        else if (n % K == 0) k = (size_t)(n / K);
+        else k = (size_t)(nck + 1 + n % K);
+        return pool + k * slot;
+    };
+    int rc;
+    // states n0 + 1 .. n1 from state n0, whose records S.rec holds
+    auto advance = [&](int64_t n0, int64_t n1, bool count) -> int {
+        uint4* rec[2] = {c->S.rec, pc ? c->S.rec : c->aux_rec};
+        for (int64_t n = n0; n < n1; ++n)
+            if ((rc = enqueue_uniform(c, state(n), rec[(n - n0) & 1], state(n + 1), rec[(n - n0 + 1) & 1], count)))
+                return rc;
+        return ADE_OK;
+    };
+
+    HIPCHK(hipMemcpyAsync(state(0), c->S.C, sbytes, hipMemcpyDeviceToDevice, st));
+    if ((rc = advance(0, nsteps, true))) return rc;
+    StateArrays fin = c->S;
+    fin.C = state(nsteps);
+    if ((rc = misfit_and_seed(c, L, fin, d_xs, ns, d_obs, L.lam[0]))) return rc;
+
+    AdjConst ac{};
+    {
+        const PlumeDev& P = pl.plumes[0];
+        double sp = 0;
+        for (int k = 0; k < pl.dim; ++k) sp += P.vel[k] * P.vel[k];
+        ac.speed = std::sqrt(sp);
+    }
+    const dim3 g((N + 255) / 256), b(256), ag(pl.ntiles * asubs), abk(ab);
+    int li = 0, ri = 0;
+    for (int64_t n = nsteps - 1; n >= 0; --n) {
+        const bool top = n == nsteps - 1;
+        // entering an earlier segment: its states are recomputed (those of the
+        // last one are still there)
+        const bool enter = !all && !top && (n + 1) % K == 0;
+        if (enter && n % K != 0) {
+            const int64_t n0 = n / K * K;
+            HIPCHK(launch_set_state(pl.dim, pl.real_bytes, c->S, state(n0), N, st));
+            if ((rc = advance(n0, n, false))) return rc;
+        }
+        if (packed && (top || enter)) {
+            hipLaunchKernelGGL(k_adj_pack, g, b, 0, st, c->S, (const float*)state(n), (const float*)L.lam[li], N,
+                               arecs[ri]);
+            HIPCHK(hipGetLastError());
+        }
+        const void* next = (n > 0 && (all || n % K != 0)) ? state(n - 1) : nullptr;
+#define LAUNCH(D, R, KK, MODE, U, X, REC, OUT, XH, NEXT, RECOUT)                                             \
+    hipLaunchKernelGGL((k_adjoint<D, R, KK, MODE>), ag, abk, (uint32_t)ashm, st, c->plumes, c->tiles, c->S,   \
+                       c->cell_start, (const R*)(U), (const R*)L.lam[li], (const R*)(X), (const uint4*)(REC), \
+                       (R*)(OUT), (R*)(XH), (const R*)(NEXT), (uint4*)(RECOUT), ac, L.gpart)
+        if (pc) {
+#define CALL(D, R, KK)                                                                                    \
+    LAUNCH(D, R, KK, kAdjHalf, L.lam[li], state(n), arecs[0], L.mu_s, L.ch_s, nullptr, arecs[1]);            \
+    LAUNCH(D, R, KK, kAdjFull, L.mu_s, L.ch_s, arecs[1], L.lam[1 - li], nullptr, next, arecs[0])
+            ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
+#undef CALL
+        } else {
+#define CALL(D, R, KK) \
+    LAUNCH(D, R, KK, kAdjEuler, L.lam[li], state(n), arecs[ri], L.lam[1 - li], nullptr, next, arecs[1 - ri])
+            ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
+#undef CALL
+            ri = 1 - ri;
+        }
+#undef LAUNCH
+        HIPCHK(hipGetLastError());
+        li = 1 - li;
+    }
+    // leave the context at step nsteps (the forward run counted its steps)
+    HIPCHK(launch_set_state(pl.dim, pl.real_bytes, c->S, state(nsteps), N, st));
+    return reduce_to_host(c, L, pl.ntiles * asubs, h_J, h_grad);
+}
+
+// The adjoint of a velocity field over snapshots of the whole state.
+int adjoint_field(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, const double* d_xs, int32_t ns,
+                  const void* d_obs, double* h_J, double* h_grad) {
+    int rc = ADE_OK;
+    const Plan& pl = c->plan;
+    const uint32_t N = (uint32_t)pl.N;
+    hipStream_t st = c->stream;
+    const Snap cur = live(c);
+    const int64_t nck = (nsteps + K - 1) / K;
+    if ((size_t)kGenAdjBlock / 4 * (size_t)pl.list_cap * 8u > kPairLdsMax)
+        return fail(ADE_EINVAL, "candidate lists of the adjoint do not fit in LDS");
+
+    // forward run with checkpoints
+    for (int64_t n = 0; n < nsteps; ++n) {
+        if (n % K == 0 && (rc = copy_state(c, L.ck[(size_t)(n / K)], cur))) return rc;
+        if ((rc = enqueue_steps(c, 1))) return rc;
+    }
+    if ((rc = copy_state(c, L.ck[(size_t)nck], cur))) return rc;
+    if ((rc = misfit_and_seed(c, L, c->S, d_xs, ns, d_obs, L.lam[0]))) return rc;
+
+    // lambda of id order in a snapshot's cell order
+    auto gather = [&](const StateArrays& S, const void* lam) -> int {
+        dim3 g((N + 255) / 256), b(256);
+        if (pl.real_bytes == 4)
+            hipLaunchKernelGGL((k_adj_gather<float>), g, b, 0, st, S, (const float*)lam, N, (float*)L.lam_s);
+        else
+            hipLaunchKernelGGL((k_adj_gather<double>), g, b, 0, st, S, (const double*)lam, N, (double*)L.lam_s);
+        HIPCHK(hipGetLastError());
+        return ADE_OK;
+    };
+
+    // reverse sweep, segment by segment
+    int li = 0;
+    const bool pc = pl.integrator == ADE_PC;
+    for (int64_t sgi = nck - 1; sgi >= 0; --sgi) {
+        const int64_t n0 = sgi * K, n1 = std::min<int64_t>(n0 + K, nsteps);
+        if ((rc = copy_state(c, cur, L.ck[(size_t)sgi]))) return rc;
+        for (int64_t n = n0; n < n1; ++n) {
+            if ((rc = copy_state(c, L.seg[(size_t)(n - n0)], cur))) return rc;
+            if (pc) {  // the step in its stages, keeping the half-step state
+                if ((rc = run_gen(c, kModeHalf, nullptr)) || (rc = enqueue_build(c, 0))) return rc;
+                if ((rc = copy_state(c, L.segh[(size_t)(n - n0)], cur))) return rc;
+                if ((rc = run_gen(c, kModeFull, nullptr)) || (rc = enqueue_build(c, 1))) return rc;
+            } else if ((rc = enqueue_steps(c, 1))) {
+                return rc;
+            }
+        }
+        for (int64_t n = n1 - 1; n >= n0; --n) {
+            const Snap sn = L.seg[(size_t)(n - n0)];
+            const StateArrays Sa = snap_arrays(c, sn);
+            AdjGenLaunch ga;
+            ga.plumes = c->plumes;
+            ga.tiles = c->tiles;
+            ga.ntiles = pl.ntiles;
+            ga.list_cap = pl.list_cap;
+            ga.S = Sa;
+            ga.cell_start = sn.cs;
+            ga.lam_s = L.lam_s;
+            ga.lam_id = nullptr;
+            ga.lam_out = L.lam[1 - li];
+            ga.gpart = L.gpart;
+            if (pc) {
+                // y = L2 lambda at the half-step state (its own cells and
+                // order), then lambda^n = lambda + dt y + dt^2/2 L1 y here
+                const Snap sh = L.segh[(size_t)(n - n0)];
+                AdjGenLaunch gh = ga;
+                gh.S = snap_arrays(c, sh);
+                gh.cell_start = sh.cs;
+                gh.lam_out = L.y;
+                if ((rc = gather(gh.S, L.lam[li]))) return rc;
+                HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenHalf, gh, kGenAdjBlock, st));
+                if ((rc = gather(Sa, L.y))) return rc;
+                ga.lam_id = L.lam[li];
+                HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenFull, ga, kGenAdjBlock, st));
+            } else {
+                if ((rc = gather(Sa, L.lam[li]))) return rc;
+                HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenEuler, ga, kGenAdjBlock, st));
+            }
+            HIPCHK(hipGetLastError());
+            li = 1 - li;
+        }
+    }
+    // leave the context at step nsteps
+    if ((rc = copy_state(c, cur, L.ck[(size_t)nck]))) return rc;
+    return reduce_to_host(c, L, pl.ntiles * kAdjMaxSubs, h_J, h_grad);
+}
+
+// The adjoint run of ade_adjoint over a workspace of ws_bytes at d_ws
+// (256-byte aligned; arguments checked by the caller).
+int adjoint_run(ade_ctx* c, int64_t nsteps, int32_t K, const double* d_xs, int32_t ns, const void* d_obs,
+                void* d_ws, size_t ws_bytes, double* h_J, double* h_grad) {
+    AdjLayout L;
+    adj_layout(c, nsteps, K, ns, nullptr, L);
+    if (ws_bytes < L.bytes) return fail(ADE_EWORKSPACE, "adjoint workspace too small: need %zu bytes", L.bytes);
+    adj_layout(c, nsteps, K, ns, static_cast<char*>(d_ws), L);
+    if (c->plan.general) return adjoint_field(c, L, nsteps, K, d_xs, ns, d_obs, h_J, h_grad);
+    return adjoint_uniform(c, L, nsteps, K, d_xs, ns, d_obs, h_J, h_grad);
 }
 
 int check_adjoint_args(ade_ctx* c, int64_t nsteps, int32_t K, const double* d_xs, int32_t ns, const void* d_obs,

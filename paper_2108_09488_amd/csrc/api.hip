@@ -406,7 +406,7 @@ void layout(Bump& b, ade_ctx* c, const Plan& pl) {
     c->aux_rec = (pl.dim == 3 && pl.real_bytes == 8) ? nullptr : b.take<uint4>(N);
     c->mass_partial = b.take<double>(pl.ntiles);
     c->range_partial = b.take<double>(2 * (size_t)pl.ntiles);
-    c->step = b.take<int64_t>(1);
+    c->step = b.take<int64_t>(2);
     c->nonfinite = b.take<uint32_t>(1);
 }
 
@@ -514,7 +514,7 @@ int run_pair(ade_ctx* c, int mode, const PairLaunch& a) {
     b.ev0 = b.ev1 = nullptr;
     int rc = take_events(c, b.ev0, b.ev1);
     if (rc) return rc;
-    HIPCHK(launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->tuning.block, c->stream));
+    HIPCHK(launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->stream));
     return ADE_OK;
 }
 
@@ -528,7 +528,8 @@ int run_gen(ade_ctx* c, int mode, void* out) {
     return ADE_OK;
 }
 
-PairLaunch pair_args(ade_ctx* c, int mode, const void* Cpair, const void* Cbase, double scale, void* out) {
+PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void* Cbase, double scale, void* out,
+                     uint4* out_rec) {
     PairLaunch a;
     std::memset(&a, 0, sizeof a);
     a.plumes = c->plumes;
@@ -541,25 +542,15 @@ PairLaunch pair_args(ade_ctx* c, int mode, const void* Cpair, const void* Cbase,
     a.persistent = c->tuning.persistent;
     a.xcd_group = c->tuning.xcd_group > 0 ? (uint32_t)c->tuning.xcd_group : 32u;
     a.zc = c->coincident ? 1 : 0;
-    // candidate records carrying the concentrations the pair sum reads
-    a.rec = (Cpair == c->aux) ? c->aux_rec : c->S.rec;
-    a.out_rec = c->aux_rec;
-    for (int d = 0; d < 3; ++d) {
-        a.spos[d] = c->S.pos[d];
-        a.upos[d] = c->U.pos[d];
-    }
+    a.rec = rec;
+    for (int d = 0; d < 3; ++d) a.spos[d] = c->S.pos[d];
     a.sid = c->S.id;
     a.Cpair = Cpair;
     a.Cbase = Cbase;
     a.cell_start = c->cell_start;
-    a.uC = c->U.C;
-    a.uid = c->U.id;
-    a.ukey = c->U.key;
-    a.lists = c->lists;
-    a.step = c->step;
     a.scale = scale;
     a.out = out;
-    (void)mode;
+    a.out_rec = out_rec;
     return a;
 }
 
@@ -591,32 +582,58 @@ GenLaunch gen_args(ade_ctx* c, void* out) {
     return g;
 }
 
-int enqueue_step(ade_ctx* c) {
+int enqueue_uniform(ade_ctx* c, const void* C, const uint4* rec, void* Cn, uint4* recn, bool count) {
+    int rc;
+    PairLaunch f;
+    if (c->plan.integrator == ADE_PC) {
+        // the corrector reads C^(1/2) and its records only, so it may write
+        // over C^n (each particle's own) and its records
+        const PairLaunch h = pair_args(c, C, rec, C, 0.5, c->aux, c->aux_rec);
+        if ((rc = run_pair(c, kModeStep, h))) return rc;
+        f = pair_args(c, c->aux, c->aux_rec, C, 1.0, Cn, recn);
+    } else {
+        f = pair_args(c, C, rec, C, 1.0, Cn, recn);
+    }
+    f.step = count ? c->step : nullptr;
+    return run_pair(c, kModeStep, f);
+}
+
+int enqueue_steps(ade_ctx* c, int64_t n) {
     const Plan& pl = c->plan;
     int rc;
-    if (pl.general && pl.integrator == ADE_PC) {
-        // velocity field, predictor-corrector: the corrector's positions
-        // x^(1/2) have their own relative geometry, so they get a cell build
-        if ((rc = run_gen(c, kModeHalf, nullptr))) return rc;
-        if ((rc = enqueue_build(c, 0))) return rc;
-        if ((rc = run_gen(c, kModeFull, nullptr))) return rc;
-    } else if (pl.general) {  // velocity field: explicit Euler
-        if ((rc = run_gen(c, kModeStep, nullptr))) return rc;
-    } else if (pl.integrator == ADE_PC) {
-        PairLaunch h = pair_args(c, kModeHalf, c->S.C, c->S.C, 0.5, c->aux);
-        if ((rc = run_pair(c, kModeHalf, h))) return rc;
-        PairLaunch f = pair_args(c, kModeStep, c->aux, c->S.C, 1.0, nullptr);
-        if ((rc = run_pair(c, kModeStep, f))) return rc;
-    } else {
-        PairLaunch f = pair_args(c, kModeStep, c->S.C, c->S.C, 1.0, nullptr);
-        if ((rc = run_pair(c, kModeStep, f))) return rc;
+    for (int64_t s = 0; s < n; ++s) {
+        if (pl.general && pl.integrator == ADE_PC) {
+            // velocity field, predictor-corrector: the corrector's positions
+            // x^(1/2) have their own relative geometry, so they get a cell build
+            if ((rc = run_gen(c, kModeHalf, nullptr))) return rc;
+            if ((rc = enqueue_build(c, 0))) return rc;
+            if ((rc = run_gen(c, kModeFull, nullptr))) return rc;
+            if ((rc = enqueue_build(c, 1))) return rc;
+        } else if (pl.general) {  // velocity field: explicit Euler
+            if ((rc = run_gen(c, kModeStep, nullptr))) return rc;
+            if ((rc = enqueue_build(c, 1))) return rc;
+        } else if (pl.integrator == ADE_PC) {
+            if ((rc = enqueue_uniform(c, c->S.C, c->S.rec, c->S.C, c->S.rec, true))) return rc;
+        } else if (s % 2 == 0) {  // explicit Euler: to the second buffer and back
+            if ((rc = enqueue_uniform(c, c->S.C, c->S.rec, c->aux, c->aux_rec, true))) return rc;
+        } else {
+            if ((rc = enqueue_uniform(c, c->aux, c->aux_rec, c->S.C, c->S.rec, true))) return rc;
+        }
     }
-    return enqueue_build(c, 1);
+    // an odd number of Euler steps ended in the second buffer: the state goes
+    // back, so that it is in one place between calls (a caller's own graph of
+    // a call stays valid whatever other calls ran)
+    if (!pl.general && pl.integrator == ADE_EULER && (n & 1))
+        HIPCHK(launch_set_state(pl.dim, pl.real_bytes, c->S, c->aux, (uint32_t)pl.N, c->stream));
+    return ADE_OK;
 }
 
 }  // namespace ade
 
 namespace {
+
+// steps in the captured graph of ade_step_graph
+constexpr int64_t kGraphSteps = 16;
 
 void drop_events(ade_ctx* c) {
     for (hipEvent_t e : c->events) hipEventDestroy(e);
@@ -734,7 +751,7 @@ int ade_create(const ade_params* params, const int64_t* counts, int32_t nplumes,
         hipMemcpyAsync(c->pair_tiles, pl.pair_tiles.data(), sizeof(TileDev) * pl.ntiles, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipMemcpyAsync(c->cell_start + pl.ncell, &c->h_total, sizeof(uint32_t), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipMemsetAsync(c->count, 0, sizeof(uint32_t) * cell_pad(pl.ncell), c->stream) != hipSuccess ||
-        hipMemsetAsync(c->step, 0, sizeof(int64_t), c->stream) != hipSuccess ||
+        hipMemsetAsync(c->step, 0, 2 * sizeof(int64_t), c->stream) != hipSuccess ||
         hipMemsetAsync(c->lists.ovf_count, 0, 2 * sizeof(uint32_t), c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
         return cleanup(fail(ADE_EHIP, "uploading the plume tables failed"));
@@ -747,7 +764,7 @@ int ade_init_particles(ade_ctx* c, const double* d_x, const void* d_C) {
     const Plan& pl = c->plan;
     HIPCHK(hipMemsetAsync(c->count, 0, sizeof(uint32_t) * cell_pad(pl.ncell), c->stream));
     HIPCHK(hipMemsetAsync(c->lists.ovf_count, 0, 2 * sizeof(uint32_t), c->stream));
-    HIPCHK(hipMemsetAsync(c->step, 0, sizeof(int64_t), c->stream));
+    HIPCHK(hipMemsetAsync(c->step, 0, 2 * sizeof(int64_t), c->stream));
     HIPCHK(launch_init(pl.dim, pl.real_bytes, c->plumes, c->tiles, pl.ntiles, d_x, d_C, (uint32_t)pl.N,
                        c->U, c->lists, c->stream));
     c->initialized = true;
@@ -796,7 +813,7 @@ int ade_build_cells(ade_ctx* c) {
     if (!c->initialized) return fail(ADE_ESTATE, "ade_build_cells before ade_init_particles");
     if (c->plan.general && !c->vel_set && !c->built)
         return fail(ADE_ESTATE, "ade_build_cells before ade_set_velocities (ADE_VELOCITY_FIELD)");
-    if (c->built) return ADE_OK;  // every step already leaves the cells built
+    if (c->built) return ADE_OK;  // every step leaves the cells valid
     int rc = enqueue_build(c, 0);
     if (rc) return rc;
     c->built = true;
@@ -834,10 +851,8 @@ int ade_step(ade_ctx* c, int64_t nsteps) {
     if (!c) return fail(ADE_EINVAL, "null ctx");
     if (nsteps < 0) return fail(ADE_EINVAL, "nsteps must be >= 0");
     if (!c->built) return fail(ADE_ESTATE, "ade_step before ade_build_cells");
-    for (int64_t s = 0; s < nsteps; ++s) {
-        int rc = enqueue_step(c);
-        if (rc) return rc;
-    }
+    int rc = enqueue_steps(c, nsteps);
+    if (rc) return rc;
     return nsteps > 0 ? check_finite(c) : ADE_OK;
 }
 
@@ -846,10 +861,13 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
     if (nsteps < 0) return fail(ADE_EINVAL, "nsteps must be >= 0");
     if (!c->built) return fail(ADE_ESTATE, "ade_step_graph before ade_build_cells");
     if (!c->stream) return fail(ADE_EINVAL, "graph capture needs a non-default stream");
-    if (!c->graph_exec) {
+    // the graph holds kGraphSteps steps (an even number: the state ends where
+    // it began); fewer steps, and the rest, are launched one by one
+    int64_t left = nsteps;
+    if (left >= kGraphSteps && !c->graph_exec) {
         HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         c->capturing = true;
-        int rc = enqueue_step(c);
+        int rc = enqueue_steps(c, kGraphSteps);
         c->capturing = false;
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(c->stream, &g);
@@ -865,7 +883,9 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
             return fail(ADE_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
         }
     }
-    for (int64_t s = 0; s < nsteps; ++s) HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
+    for (; left >= kGraphSteps; left -= kGraphSteps) HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
+    int rc = enqueue_steps(c, left);
+    if (rc) return rc;
     return nsteps > 0 ? check_finite(c) : ADE_OK;
 }
 
@@ -874,8 +894,7 @@ int ade_rhs(ade_ctx* c, void* d_rhs) {
     if (!c->built) return fail(ADE_ESTATE, "ade_rhs before ade_build_cells");
     const Plan& pl = c->plan;
     if (pl.general) return run_gen(c, kModeRhs, d_rhs);
-    PairLaunch a = pair_args(c, kModeRhs, c->S.C, c->S.C, 1.0, d_rhs);
-    return run_pair(c, kModeRhs, a);
+    return run_pair(c, kModeRhs, pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, d_rhs, nullptr));
 }
 
 int ade_read_C(const ade_ctx* c, void* d_C_out) {
@@ -888,7 +907,7 @@ int ade_read_C(const ade_ctx* c, void* d_C_out) {
 int ade_read_x(const ade_ctx* c, double* d_x_out) {
     if (!c || !d_x_out) return fail(ADE_EINVAL, "null argument");
     if (!c->built) return fail(ADE_ESTATE, "ade_read_x before ade_build_cells");
-    HIPCHK(launch_read_x(c->plan.dim, c->plumes, c->tiles, c->plan.ntiles, c->S, (uint32_t)c->plan.N,
+    HIPCHK(launch_read_x(c->plan.dim, c->plumes, c->tiles, c->plan.ntiles, c->S, frame_of(c), (uint32_t)c->plan.N,
                          d_x_out, c->stream));
     return ADE_OK;
 }
@@ -962,8 +981,8 @@ static int clear_counts(ade_ctx* c) {
 }
 
 // Times the candidate launch shapes of a tuner: `launch(k)` enqueues
-// candidate k's step-mode kernel with the events around it (and clears the
-// cell counts it leaves).  The clocks of the GPU rise only under sustained
+// candidate k's step-mode kernel with the events around it (a velocity
+// field's leaves cell counts, which are cleared).  The clocks of the GPU rise only under sustained
 // load and fall again within seconds of idling (a context timed back to back
 // ran 10% faster from its second timing on; with 2 s idle between timings it
 // never did), so the GPU is first kept busy for ~50 ms with the first
@@ -973,7 +992,7 @@ static int time_candidates(ade_ctx* c, int ncand, int32_t reps, hipEvent_t e0, h
                            const std::function<hipError_t(int)>& launch, int* best) {
     auto timed = [&](int k, float* ms) -> int {
         if (launch(k) != hipSuccess) return fail(ADE_EHIP, "autotune launch");
-        int rc = clear_counts(c);
+        int rc = c->plan.general ? clear_counts(c) : ADE_OK;
         if (rc) return rc;
         if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(ms, e0, e1) != hipSuccess)
             return fail(ADE_EHIP, "event synchronise");
@@ -984,7 +1003,7 @@ static int time_candidates(ade_ctx* c, int ncand, int32_t reps, hipEvent_t e0, h
     const int warm = std::min(4000, (int)std::ceil(50.0 / std::max(one, 0.01f)));
     for (int k = 0; !rc && k < warm; ++k) {
         if (launch(0) != hipSuccess) rc = fail(ADE_EHIP, "autotune launch");
-        else rc = clear_counts(c);
+        else if (c->plan.general) rc = clear_counts(c);
     }
     std::vector<float> tot((size_t)ncand, 0.f);
     for (int r = 0; !rc && r <= reps; ++r)
@@ -1063,21 +1082,17 @@ int ade_autotune(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* best) {
     HIPCHK(hipEventCreate(&e0));
     HIPCHK(hipEventCreate(&e1));
     int kbest = 0;
-    // the step-mode kernel, as a step runs it; its outputs go to the hashed
-    // buffer U and the cell counts of the next build, which are cleared again
-    // after every launch
+    // the update-mode kernel, as a step runs it, to the second C buffer
     int rc = time_candidates(c, (int)cands.size(), reps, e0, e1,
                              [&](int k) {
                                  c->tuning = cands[(size_t)k];
-                                 PairLaunch a = pair_args(c, kModeStep, c->S.C, c->S.C, 1.0, nullptr);
+                                 PairLaunch a =
+                                     pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, c->aux, c->aux_rec);
                                  a.ev0 = e0;
                                  a.ev1 = e1;
-                                 return launch_pair(pl.dim, pl.real_bytes, pl.kernel, kModeStep, a, a.block,
-                                                    c->stream);
+                                 return launch_pair(pl.dim, pl.real_bytes, pl.kernel, kModeStep, a, c->stream);
                              },
                              &kbest);
-    const int rc_clear = clear_counts(c);  // also after a failed launch
-    if (!rc) rc = rc_clear;
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     c->tuning = rc ? start : cands[(size_t)kbest];
@@ -1153,7 +1168,11 @@ struct StateHeader {
     uint64_t N, ncell, bytes;
     uint64_t layout;  // layout_hash of the saving context
 };
-constexpr uint64_t kStateMagic = 0x3154415453454441ull;  // "ADESTAT1"
+constexpr uint64_t kStateMagic = 0x3154415453454441ull;   // "ADESTAT1"
+// a uniform flow's state ends in (k, k0): positions and cells are those of
+// step k0.  A state of the first form, whose positions and cells are those
+// of its own step k, is read as well (k0 = k).
+constexpr uint64_t kStateMagic2 = 0x3254415453454441ull;  // "ADESTAT2"
 
 // FNV-1a over what places the saved arrays: each plume's particle range and
 // cell grid.  Two contexts of equal N and cell count but another split of
@@ -1199,7 +1218,7 @@ std::vector<Section> state_sections(const ade_ctx* c) {
         if (S.rD[d]) v.push_back({S.rD[d], N * rb});
     if (S.grec) v.push_back({S.grec, N * 32});
     v.push_back({c->cell_start, ((size_t)pl.ncell + 1) * 4});
-    v.push_back({c->step, 8});
+    v.push_back({c->step, pl.general ? size_t(8) : sizeof(FrameStep)});
     return v;
 }
 
@@ -1225,7 +1244,7 @@ int ade_save_state(const ade_ctx* c, void* h_buf, size_t bytes) {
     const size_t need = state_size(c);
     if (bytes < need) return fail(ADE_EINVAL, "state buffer too small: need %zu bytes", need);
     const Plan& pl = c->plan;
-    StateHeader h{kStateMagic, (uint32_t)pl.dim, (uint32_t)pl.real_bytes, pl.general ? 1u : 0u,
+    StateHeader h{pl.general ? kStateMagic : kStateMagic2, (uint32_t)pl.dim, (uint32_t)pl.real_bytes, pl.general ? 1u : 0u,
                   (uint32_t)pl.integrator, (uint64_t)pl.N, (uint64_t)pl.ncell, (uint64_t)need,
                   layout_hash(pl)};
     char* p = static_cast<char*>(h_buf);
@@ -1245,8 +1264,11 @@ int ade_load_state(ade_ctx* c, const void* h_buf, size_t bytes) {
     StateHeader h;
     if (bytes < sizeof h) return fail(ADE_EINVAL, "state buffer too small");
     std::memcpy(&h, h_buf, sizeof h);
-    const size_t need = state_size(c);
-    if (h.magic != kStateMagic || h.dim != (uint32_t)pl.dim || h.real_bytes != (uint32_t)pl.real_bytes ||
+    // a uniform flow's state of the first form lacks k0
+    const bool first_form = !pl.general && h.magic == kStateMagic;
+    const size_t need = state_size(c) - (first_form ? 8 : 0);
+    if ((h.magic != (pl.general ? kStateMagic : kStateMagic2) && !first_form) || h.dim != (uint32_t)pl.dim ||
+        h.real_bytes != (uint32_t)pl.real_bytes ||
         h.general != (pl.general ? 1u : 0u) || h.integrator != (uint32_t)pl.integrator ||
         h.N != (uint64_t)pl.N || h.ncell != (uint64_t)pl.ncell || h.bytes != need ||
         h.layout != layout_hash(pl))
@@ -1254,8 +1276,10 @@ int ade_load_state(ade_ctx* c, const void* h_buf, size_t bytes) {
     if (bytes < need) return fail(ADE_EINVAL, "state buffer too small: need %zu bytes", need);
     const char* p = static_cast<const char*>(h_buf) + sizeof h;
     for (const Section& s : state_sections(c)) {
-        HIPCHK(hipMemcpyAsync(s.dev, p, s.bytes, hipMemcpyHostToDevice, c->stream));
-        p += s.bytes;
+        const size_t nb = (first_form && s.dev == c->step) ? 8 : s.bytes;
+        HIPCHK(hipMemcpyAsync(s.dev, p, nb, hipMemcpyHostToDevice, c->stream));
+        if (nb != s.bytes) HIPCHK(hipMemcpyAsync(c->step + 1, p, 8, hipMemcpyHostToDevice, c->stream));
+        p += nb;
     }
     // the next step's counting pass starts from empty cells
     HIPCHK(hipMemsetAsync(c->count, 0, sizeof(uint32_t) * cell_pad(pl.ncell), c->stream));

@@ -62,7 +62,7 @@ struct ade_ctx {
     uint4* aux_rec = nullptr;
     double* mass_partial = nullptr;
     double* range_partial = nullptr;  // per tile: min and max of C
-    int64_t* step = nullptr;
+    int64_t* step = nullptr;  // the step counter (uniform flow: a FrameStep, k then k0)
     uint32_t* nonfinite = nullptr;  // finite check: set when a concentration is not finite
     uint32_t h_total = 0;  // host copy of N for the cell-start sentinel
     bool initialized = false, built = false;
@@ -85,12 +85,21 @@ namespace ade {
 
 // enqueue a pair kernel (timed when timing is on)
 int run_pair(ade_ctx* c, int mode, const PairLaunch& a);
-// launch arguments of a pair kernel over the sorted state of c
-PairLaunch pair_args(ade_ctx* c, int mode, const void* Cpair, const void* Cbase, double scale, void* out);
+// launch arguments of a pair kernel over the sorted particles of c: rec the
+// candidate records carrying Cpair
+PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void* Cbase, double scale, void* out,
+                     uint4* out_rec);
+// one step of a uniform flow from the concentrations (C, rec) to (Cn, recn),
+// which differ from them; advances the step counter if asked
+int enqueue_uniform(ade_ctx* c, const void* C, const uint4* rec, void* Cn, uint4* recn, bool count);
+// the frame of a uniform flow (null for a velocity field)
+inline const FrameStep* frame_of(const ade_ctx* c) {
+    return c->plan.general ? nullptr : reinterpret_cast<const FrameStep*>(c->step);
+}
 // counting sort of the hashed U buffer into S and the cell-start table
 int enqueue_build(ade_ctx* c, int inc_step);
-// one explicit step (pair sum, update, rebuild)
-int enqueue_step(ade_ctx* c);
+// n explicit steps (velocity field: pair sum, update and rebuild each)
+int enqueue_steps(ade_ctx* c, int64_t n);
 // launch arguments of the velocity-field pair kernel over the sorted state of c
 GenLaunch gen_args(ade_ctx* c, void* out);
 // enqueue the velocity-field pair kernel (timed when timing is on)

@@ -4,7 +4,7 @@
 // orders the particles of each cell by id, so that the sorted order is a pure
 // function of the positions (deterministic pair sums).
 // Also: read-back of C and x in id order and the FP64 mass reduction.
-#include "ade_device.h"
+#include "ade_geom.h"
 
 namespace ade {
 
@@ -288,14 +288,27 @@ __global__ __launch_bounds__(256) void k_read_C(StateArrays S, uint32_t N, real*
 template <int DIM>
 __global__ __launch_bounds__(kTile) void k_read_x(const PlumeDev* __restrict__ plumes,
                                                  const TileDev* __restrict__ tiles, StateArrays S,
-                                                 uint32_t N, double* __restrict__ out) {
+                                                 const FrameStep* __restrict__ frame, uint32_t N,
+                                                 double* __restrict__ out) {
     const TileDev t = tiles[blockIdx.x];
-    const double scale = plumes[t.plume].L * (1.0 / 4294967296.0);
+    const PlumeDev& P = plumes[t.plume];
+    const double scale = P.L * (1.0 / 4294967296.0);
     const uint32_t i = t.start + threadIdx.x;
     if (i >= t.end) return;
     const uint32_t id = S.id[i];
 #pragma unroll
-    for (int c = 0; c < DIM; ++c) out[(size_t)c * N + id] = (double)S.pos[c][i] * scale;
+    for (int c = 0; c < DIM; ++c) out[(size_t)c * N + id] = (double)(S.pos[c][i] + frame_shift(P, frame, c)) * scale;
+}
+
+// C (and its candidate records) of the sorted state replaced
+template <int DIM, typename real>
+__global__ __launch_bounds__(256) void k_set_state(StateArrays S, const real* __restrict__ C, uint32_t N) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N) return;
+    const real c = C[i];
+    static_cast<real*>(S.C)[i] = c;
+    if (Rec<DIM, real>::kStageable)
+        S.rec[i] = Rec<DIM, real>::pack(S.pos[0][i], S.pos[1][i], (DIM == 3) ? S.pos[2][i] : 0u, c);
 }
 
 template <typename real>
@@ -361,9 +374,18 @@ hipError_t launch_read_C(int real_bytes, StateArrays S, uint32_t N, void* out, h
 }
 
 hipError_t launch_read_x(int dim, const PlumeDev* plumes, const TileDev* tiles, uint32_t ntiles,
-                         StateArrays S, uint32_t N, double* out, hipStream_t s) {
-    if (dim == 2) hipLaunchKernelGGL((k_read_x<2>), dim3(ntiles), dim3(kTile), 0, s, plumes, tiles, S, N, out);
-    else hipLaunchKernelGGL((k_read_x<3>), dim3(ntiles), dim3(kTile), 0, s, plumes, tiles, S, N, out);
+                         StateArrays S, const FrameStep* frame, uint32_t N, double* out, hipStream_t s) {
+    if (dim == 2) hipLaunchKernelGGL((k_read_x<2>), dim3(ntiles), dim3(kTile), 0, s, plumes, tiles, S, frame, N, out);
+    else hipLaunchKernelGGL((k_read_x<3>), dim3(ntiles), dim3(kTile), 0, s, plumes, tiles, S, frame, N, out);
+    return hipGetLastError();
+}
+
+hipError_t launch_set_state(int dim, int real_bytes, StateArrays S, const void* C, uint32_t N, hipStream_t s) {
+    dim3 g((N + 255) / 256), b(256);
+    if (dim == 2 && real_bytes == 4) hipLaunchKernelGGL((k_set_state<2, float>), g, b, 0, s, S, (const float*)C, N);
+    else if (dim == 2) hipLaunchKernelGGL((k_set_state<2, double>), g, b, 0, s, S, (const double*)C, N);
+    else if (real_bytes == 4) hipLaunchKernelGGL((k_set_state<3, float>), g, b, 0, s, S, (const float*)C, N);
+    else hipLaunchKernelGGL((k_set_state<3, double>), g, b, 0, s, S, (const double*)C, N);
     return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
 // kernels_pair.hip -- the SPH pair sum of Eqs. (4)-(5) (Klapp et al.,
-// arXiv:2108.09488, Section 2.2) on gfx950, fused with the explicit update of
-// C and x and with the hashing of the moved particle for the next cell build.
+// arXiv:2108.09488, Section 2.2) on gfx950, fused with the explicit update of C.
 //
 // For a uniform flow the harmonic mean of Eq. (5) of two equal tensors is 2 D,
 // so the pair term is
@@ -154,56 +153,32 @@ __device__ __forceinline__ void walk_list(const Term& term, const Target& T,
 }
 
 // The end of a target's pair sum acc: rhs mode writes the right-hand side
-// (vphi * acc) in id order; half mode the half-step concentration (and its
-// candidate record); step mode updates C and x and returns the moved
-// particle's cell key (its id in id), which the caller enters into the next
-// build's cell lists (enlist).
+// (vphi * acc) in id order; update mode the new concentration Cbase +
+// scale dt rhs with its candidate record, in cell order.  A uniform flow
+// moves every particle of a plume by the same displacement, so neither the
+// order of the particles nor the cells of the build change (positions are
+// kept in the plume's frame, ade_internal.h).
 template <int DIM, typename real, int KERN, int MODE>
-__device__ __forceinline__ uint32_t finish_core(const PairLaunch& a, const PlumeDev& P, const Target& T, uint32_t i,
-                                                real acc, uint32_t& id) {
+__device__ __forceinline__ void finish_target(const PairLaunch& a, const PlumeDev& P, const Target& T, uint32_t i,
+                                              real acc) {
     constexpr bool kRec = Rec<DIM, real>::kStageable;
     // the kernel factor's constant and the bracket's sign S (the pair term
     // sums S times the bracket)
     const double kS = kPolyScale<KERN> * P.dterm[4];
-    id = 0u;
     if (MODE == kModeRhs) {
         static_cast<real*>(a.out)[a.sid[i]] = (real)(kS * P.vphi) * acc;
-        return 0u;
+        return;
     }
     const real sc = (real)(a.scale * P.dt * P.vphi * kS);
-    const real Cb = static_cast<const real*>(a.Cbase)[i];
-    if (MODE == kModeHalf) {
-        const real Ch = fmar(sc, acc, Cb);
-        static_cast<real*>(a.out)[i] = Ch;
-        if (kRec) a.out_rec[i] = Rec<DIM, real>::pack(T.ux, T.uy, T.uz, Ch);
-        return 0u;
-    }
-    // step: update C and x, key of the moved particle for the next build
-    const int64_t k = *a.step;
-    uint32_t u[3] = {T.ux, T.uy, T.uz};
-#pragma unroll
-    for (int c = 0; c < DIM; ++c) {
-        const double us = P.ushift[c];
-        const int64_t s1 = (int64_t)rint((double)(k + 1) * us);
-        const int64_t s0 = (int64_t)rint((double)k * us);
-        u[c] += (uint32_t)(s1 - s0);
-        a.upos[c][i] = u[c];
-    }
-    static_cast<real*>(a.uC)[i] = fmar(sc, acc, Cb);
-    id = a.sid[i];
-    a.uid[i] = id;
-    const uint32_t key = cell_key<DIM>(P, u[0], u[1], u[2]);
-    a.ukey[i] = key;
-    return key;
+    const real Cn = fmar(sc, acc, static_cast<const real*>(a.Cbase)[i]);
+    static_cast<real*>(a.out)[i] = Cn;
+    if (kRec) a.out_rec[i] = Rec<DIM, real>::pack(T.ux, T.uy, T.uz, Cn);
 }
 
-// finish_core, and in step mode the moved particle entered into its cell.
-template <int DIM, typename real, int KERN, int MODE>
-__device__ __forceinline__ void finish_target(const PairLaunch& a, const PlumeDev& P, const Target& T, uint32_t i,
-                                              real acc) {
-    uint32_t id;
-    const uint32_t key = finish_core<DIM, real, KERN, MODE>(a, P, T, i, acc, id);
-    if (MODE == kModeStep) enlist(a.lists, key, id);
+// The step counter, advanced by one thread of the launch that ends a step
+// (no kernel of the launch reads it).
+__device__ __forceinline__ void advance_step(const PairLaunch& a) {
+    if (a.step && blockIdx.x == 0 && threadIdx.x == 0) *a.step += 1;
 }
 
 // One work item = `block / LANES` consecutive target particles of one tile.
@@ -394,18 +369,8 @@ __device__ __forceinline__ void pair_item2(const PairLaunch& a, const PlumeDev* 
     else list[0] = make_uint2(kListEndStart, kListEndEnd);
     const PairTerm<DIM, real, KERN, ZC> term = make_term<DIM, real, KERN, ZC>(P);
     walk_pair<DIM>(term, TA, TB, CA, CB, iA, list, stride, total, fetch, accA, accB);
-    // the pair's moved particles: two of one cell are counted with one atomic
-    uint32_t idA = 0u, idB = 0u, kA = 0u, kB = 0u;
-    if (actA) kA = finish_core<DIM, real, KERN, MODE>(a, P, TA, iA, accA, idA);
-    if (merged) kB = finish_core<DIM, real, KERN, MODE>(a, P, TB, iB, accB, idB);
-    if (MODE == kModeStep) {
-        if (merged && kA == kB) {
-            enlist2(a.lists, kA, idA, idB);
-        } else {
-            if (actA) enlist(a.lists, kA, idA);
-            if (merged) enlist(a.lists, kB, idB);
-        }
-    }
+    if (actA) finish_target<DIM, real, KERN, MODE>(a, P, TA, iA, accA);
+    if (merged) finish_target<DIM, real, KERN, MODE>(a, P, TB, iB, accB);
 
     // b of a pair that could not be merged walks its own list (a second walk
     // that only wavefronts holding such a pair enter)
@@ -523,6 +488,7 @@ template <int DIM, typename real, int KERN, int MODE, bool ZC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(6))) void k_pair42(PairLaunch a, const PlumeDev* __restrict__ plumes,
                                                 const TileDev* __restrict__ tiles, uint32_t nwork) {
     extern __shared__ uint2 lds_list[];
+    advance_step(a);
     if (a.persistent == 0) {
         pair_item42<DIM, real, KERN, MODE, ZC>(a, plumes, tiles, xcd_remap(blockIdx.x, gridDim.x, a.xcd_group),
                                                lds_list);
@@ -545,6 +511,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(real
 void k_pair(PairLaunch a, const PlumeDev* __restrict__ plumes,
                                               const TileDev* __restrict__ tiles, uint32_t nwork) {
     extern __shared__ uint2 lds_list[];
+    advance_step(a);
     if (a.persistent == 0) {
         pair_item<DIM, real, KERN, MODE, LANES, ZC>(a, plumes, tiles, xcd_remap(blockIdx.x, gridDim.x, a.xcd_group),
                                                     lds_list);
@@ -570,6 +537,7 @@ template <int DIM, typename real, int KERN, int MODE, bool ZC>
 __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(sizeof(real) == 4 && DIM == 2 ? 6 : 1)))
 void k_pair2(PairLaunch a, const PlumeDev* __restrict__ plumes, const TileDev* __restrict__ tiles, uint32_t nwork) {
     extern __shared__ uint2 lds_list[];
+    advance_step(a);
     if (a.persistent == 0) {
         pair_item2<DIM, real, KERN, MODE, ZC>(a, plumes, tiles, xcd_remap(blockIdx.x, gridDim.x, a.xcd_group), lds_list);
         return;
@@ -635,9 +603,8 @@ static void launch_pair_l(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t grid = (c.persistent > 0) ? max(8u, min(nwork, (uint32_t)c.persistent)) : nwork;
     dim3 g(grid), b(a.block);
     const size_t shm = pair_lds_bytes(a.block, LANES, a.list_cap);
-    auto kern = (mode == kModeStep)   ? k_pair<DIM, real, KERN, kModeStep, LANES, ZC>
-                : (mode == kModeHalf) ? k_pair<DIM, real, KERN, kModeHalf, LANES, ZC>
-                                      : k_pair<DIM, real, KERN, kModeRhs, LANES, ZC>;
+    auto kern = (mode == kModeRhs) ? k_pair<DIM, real, KERN, kModeRhs, LANES, ZC>
+                                   : k_pair<DIM, real, KERN, kModeStep, LANES, ZC>;
     if (c.ev0)  // timed launch: the events carry the kernel's own start and end stamps
         hipExtLaunchKernelGGL(kern, g, b, (uint32_t)shm, s, c.ev0, c.ev1, 0u, c, c.plumes, c.tiles, nwork);
     else
@@ -653,9 +620,8 @@ static void launch_pair_2(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t grid = (c.persistent > 0) ? max(8u, min(nwork, (uint32_t)c.persistent)) : nwork;
     dim3 g(grid), b(a.block);
     const size_t shm = pair_lds_bytes(a.block, 1, a.list_cap);
-    auto kern = (mode == kModeStep)   ? k_pair2<DIM, real, KERN, kModeStep, ZC>
-                : (mode == kModeHalf) ? k_pair2<DIM, real, KERN, kModeHalf, ZC>
-                                      : k_pair2<DIM, real, KERN, kModeRhs, ZC>;
+    auto kern = (mode == kModeRhs) ? k_pair2<DIM, real, KERN, kModeRhs, ZC>
+                                   : k_pair2<DIM, real, KERN, kModeStep, ZC>;
     if (c.ev0)
         hipExtLaunchKernelGGL(kern, g, b, (uint32_t)shm, s, c.ev0, c.ev1, 0u, c, c.plumes, c.tiles, nwork);
     else
@@ -671,9 +637,8 @@ static void launch_pair_42(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t grid = (c.persistent > 0) ? max(8u, min(nwork, (uint32_t)c.persistent)) : nwork;
     dim3 g(grid), b(a.block);
     const size_t shm = pair_lds_bytes(a.block, 4, a.list_cap);
-    auto kern = (mode == kModeStep)   ? k_pair42<DIM, real, KERN, kModeStep, ZC>
-                : (mode == kModeHalf) ? k_pair42<DIM, real, KERN, kModeHalf, ZC>
-                                      : k_pair42<DIM, real, KERN, kModeRhs, ZC>;
+    auto kern = (mode == kModeRhs) ? k_pair42<DIM, real, KERN, kModeRhs, ZC>
+                                   : k_pair42<DIM, real, KERN, kModeStep, ZC>;
     if (c.ev0)
         hipExtLaunchKernelGGL(kern, g, b, (uint32_t)shm, s, c.ev0, c.ev1, 0u, c, c.plumes, c.tiles, nwork);
     else
@@ -706,9 +671,7 @@ static void launch_pair_t(int mode, const PairLaunch& a, hipStream_t s) {
     launch_pair_z<DIM, real, KERN, true>(mode, a, s);
 }
 
-hipError_t launch_pair(int dim, int real_bytes, int kernel, int mode, const PairLaunch& a,
-                       int block, hipStream_t s) {
-    (void)block;
+hipError_t launch_pair(int dim, int real_bytes, int kernel, int mode, const PairLaunch& a, hipStream_t s) {
     if (a.block <= 0 || a.block > kTile || kTile % a.block != 0) return hipErrorInvalidValue;
     if (a.lanes != 1 && a.lanes != 2 && a.lanes != 4) return hipErrorInvalidValue;
     if (a.targets != 1 && (a.targets != 2 || !((a.lanes == 1 && 2 * a.block <= kTile) || a.lanes == 4)))
