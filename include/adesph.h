@@ -118,7 +118,8 @@ typedef struct {
  * quad two consecutive targets: they list the candidates of both together
  * (the same bytes per quad as a lane's two-target list) and evaluate every
  * candidate for both.  The summation order, and so the last bits of the
- * result, depend on lanes and targets and on nothing else here.  A new
+ * result, depend on lanes and targets (and on whether the plume has neighbour
+ * lists) and on nothing else here.  A new
  * context starts with the fewest lanes per particle that keep about 4
  * wavefronts per SIMD: block 64 with two targets per lane from 2^19
  * particles on, else 256 threads with 1 (from 2^18), 2 (from 2^17) or 4
@@ -140,7 +141,10 @@ typedef struct {
 } ade_tuning;
 
 /* Bytes of device workspace needed for nplumes plumes with counts[p]
- * particles each (host-only, pure). */
+ * particles each (host-only, pure).  For a uniform flow it has room for
+ * neighbour lists: about 2 bytes (2D) or 4 bytes (3D) per neighbour and
+ * particle with a margin, for plumes of at most 2000 expected neighbours per
+ * particle; none when a context's lists would pass 16 GiB. */
 int ade_workspace_bytes(const ade_params *params, const int64_t *counts, int32_t nplumes,
                         size_t *bytes);
 
@@ -152,8 +156,9 @@ int ade_workspace_bytes(const ade_params *params, const int64_t *counts, int32_t
  * contexts.  A plume of a multi-plume context evolves bit for bit as it does
  * alone when both runs have the same cell grid (cell_rows, and cell_xsub
  * where the context's cell tables would pass the 160 MiB budget, since the
- * default x cells then widen for the whole context) and the same lanes and
- * targets: the grid fixes the candidate order of every sum. */
+ * default x cells then widen for the whole context), the same lanes and
+ * targets, and neighbour lists in both or in neither (a context whose lists
+ * would pass 16 GiB keeps none): these fix the order of every sum. */
 int ade_create(const ade_params *params, const int64_t *counts, int32_t nplumes, void *d_ws,
                size_t ws_bytes, void *stream, ade_ctx **out);
 
@@ -192,8 +197,10 @@ int ade_set_velocities(ade_ctx *ctx, const double *d_v);
  * particle id within a cell) and the cell-start table, then the particle
  * state is gathered into cell order.  Needed once after init.  A uniform flow
  * moves every particle of a plume by the same displacement, so the order and
- * the cells, taken in the plume's frame, hold for the whole run; a velocity
- * field rebuilds them every step.  For a uniform flow it also checks whether two particles of
+ * the cells, taken in the plume's frame, hold for the whole run, and so do
+ * the neighbour lists built with them, which the steps walk (a plume whose
+ * lists do not fit their room walks the cells); a velocity field rebuilds its
+ * cells every step.  For a uniform flow it also checks whether two particles of
  * a plume share a position (and synchronises the stream for that): the sum
  * of Eq. (4) leaves out pairs at r = 0, and when no two particles coincide
  * the only candidate at r = 0 is a target's own record, whose term is zero,

@@ -112,6 +112,26 @@ struct FrameStep {
     int64_t k, k0;
 };
 
+// Neighbour lists (kernels_list.hip): where a plume's lists stand for the
+// launch shape they were built for.
+struct ListPlume {
+    uint32_t row0;   // first row (64 words) of the plume's lists
+    uint32_t rows;   // rows per wavefront (0: the plume keeps no lists)
+    uint32_t wave0;  // the plume's first wavefront
+    uint32_t pad;
+};
+// What is uniform in a wavefront's lists.
+struct ListWave {
+    static constexpr uint32_t kTwoPasses = 0x80000000u;
+    uint32_t base;  // 2D: the record that its entries count from
+    uint32_t nb;    // batches, and whether a second pass follows (kTwoPasses)
+    uint32_t nb2;   // batches of the second pass
+    uint32_t full;  // batches in which every lane has entries (16 bits a pass)
+};
+// entries a lane evaluates per batch, and rows read past a wavefront's last
+constexpr int kListBatch = 4;
+constexpr uint32_t kListSlack = 4 * kListBatch;
+
 struct PairLaunch {
     const PlumeDev* plumes;
     const TileDev* tiles;
@@ -135,6 +155,10 @@ struct PairLaunch {
     void* out;              // update: S-order output; rhs: id-order output
     uint4* out_rec;         // update: candidate records with the new C (S order)
     int64_t* step;          // update: the step counter, advanced by this launch (null: left)
+    // neighbour lists (list null: walk the row windows)
+    const uint32_t* list;
+    const ListPlume* lplumes;
+    const ListWave* waves;
     hipEvent_t ev0, ev1;    // if set: events stamped at the kernel's start and end
 };
 
@@ -150,6 +174,24 @@ inline size_t pair_lds_bytes(int block, int lanes, int list_cap) {
     return (size_t)(block / lanes) * (size_t)list_cap * 8u;
 }
 constexpr size_t kPairLdsMax = 65536;
+
+// Build of the neighbour lists of a launch shape.
+struct ListBuild {
+    const PlumeDev* plumes;
+    const TileDev* tiles;
+    uint32_t ntiles;
+    int lanes, targets;     // the launch shape
+    int list_cap;           // candidate-list entries per group in LDS
+    const ListPlume* lplumes;
+    const uint4* rec;       // candidate records, or null: positions from spos
+    const uint32_t* spos[3];
+    const uint32_t* cell_start;
+    uint32_t* list;
+    ListWave* waves;
+    uint32_t* over;         // per plume: set when its lists do not fit
+};
+hipError_t launch_list(int dim, int real_bytes, const ListBuild& a, hipStream_t s);
+hipError_t launch_pair_list(int dim, int real_bytes, int kernel, int mode, const PairLaunch& a, hipStream_t s);
 
 // kernel launchers (kernels_*.hip); all return hipError_t of the launch
 hipError_t launch_init(int dim, int real_bytes, const PlumeDev* plumes, const TileDev* tiles,

@@ -483,4 +483,37 @@ __device__ __forceinline__ RowRanges union_row(const PlumeDev& P, const uint32_t
     return window_ranges(P, cs, row_base(P, yy, zz), lo, hi);
 }
 
+// The union listed by one lane alone.
+template <int DIM>
+__device__ __forceinline__ uint32_t build_union(const PlumeDev& P, const uint32_t* __restrict__ cs, const Target& A,
+                                                const Target& B, int dy, int dz, uint2* list, uint32_t stride) {
+    const int R = P.R;
+    const int ny = 2 * R + 1 + (dy != 0 ? 1 : 0);
+    const int nz = (DIM == 3) ? 2 * R + 1 + (dz != 0 ? 1 : 0) : 1;
+    const int nrows = ny * nz;
+    const int oy0 = min(0, dy) - R, oy1 = oy0 + ny - 1;
+    int oy = oy0, oz = (DIM == 3) ? min(0, dz) - R : 0;  // the row of j, stepped on (oy fastest)
+    const float dxc = (float)(int32_t)(B.ux - A.ux) * P.cellx;
+    ListWriter w(list, stride);
+    // two rows at a time: their cell-start loads are in flight together
+    for (int j = 0; j < nrows; j += 2) {
+        RowRanges r[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            r[q] = RowRanges{0u, 0u, 0u, 0u};
+            if (j + q < nrows) r[q] = union_row<DIM>(P, cs, A, B, dxc, dy, dz, oy, oz);
+            if (++oy > oy1) {
+                oy = oy0;
+                ++oz;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (r[q].e1 > r[q].s1) w.put(r[q].s1, r[q].e1);
+            if (r[q].e0 > r[q].s0) w.put(r[q].s0, r[q].e0);
+        }
+    }
+    return w.flush();
+}
+
 }  // namespace ade

@@ -747,7 +747,8 @@ int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, c
         else k = (size_t)(nck + 1 + n % K);
         return pool + k * slot;
     };
-    int rc;
+    int rc = settle_lists(c);
+    if (rc) return rc;
     // states n0 + 1 .. n1 from state n0, whose records S.rec holds
     auto advance = [&](int64_t n0, int64_t n1, bool count) -> int {
         uint4* rec[2] = {c->S.rec, pc ? c->S.rec : c->aux_rec};

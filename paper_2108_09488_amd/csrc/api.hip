@@ -62,6 +62,87 @@ bool tuning_fits(const Plan& pl, const ade_tuning& t) {
     return pair_lds_bytes(t.block, t.lanes, tuning_list_cap(pl, t)) <= kPairLdsMax;
 }
 
+// default launch shape: the fewest lanes per particle that still give
+// the chip about 4 wavefronts per SIMD (4096 wavefronts of 64 lanes, i.e.
+// 2^18 lanes): two targets per lane from 2^19 particles on (the fastest
+// shape on the 2D sweep), one lane per target from 2^18, two lanes from
+// 2^17, else four; then the next shapes whose candidate lists fit in LDS.
+// Plumes of thousands of neighbours per particle, and 3D plumes, take
+// four lanes per target, or in FP32 four lanes per two neighbouring
+// targets: the targets of a wavefront then walk nearly the same candidate
+// ranges and share their cache lines, and a pair of targets shares every
+// record it fetches (the autotuner's choice on the 10^6-particle,
+// 31k-neighbour problem: 19.3 ms per pair launch against 22.8 ms for one
+// target a quad; on the 128^3 plume 0.88-0.90 ms against 0.90-0.92).
+bool default_tuning(const Plan& pl, ade_tuning& out) {
+    const int64_t N = pl.N;
+    const bool quads = pl.nbar_max > 2000.0 || pl.dim == 3;
+    const int qtargets = pl.real_bytes == 4 ? 2 : 1;
+    const ade_tuning first = quads ? ade_tuning{pl.dim == 3 ? 64 : 128, 4, 128, 0, qtargets}
+                             : N >= (1 << 19) ? ade_tuning{64, 1, 0, 0, 2}
+                             : N >= (1 << 18) ? ade_tuning{256, 1, 0, 0, 1}
+                             : N >= (1 << 17) ? ade_tuning{256, 2, 0, 0, 1}
+                                              : ade_tuning{256, 4, 0, 0, 1};
+    const ade_tuning defaults[6] = {first, {256, 2, 0, 0, 1}, {256, 4, 0, 0, 1}, {128, 4, 0, 0, 1},
+                                    {64, 4, 0, 0, 1}, {64, 1, 0, 0, 2}};
+    bool ok = false;
+    for (const ade_tuning& t : defaults)
+        if (!ok && tuning_fits(pl, t)) {
+            out = t;
+            ok = true;
+        }
+    if (!ok) return false;
+    // a velocity field: four lanes per target in the largest workgroup
+    // whose lists fit, or in 2D FP32 for plumes of thousands of
+    // neighbours four lanes per two targets, block 128 (10^6 particles,
+    // 31k neighbours: 44 against 64 ms per update launch; on the 512^2
+    // plumes of 46 and 111 neighbours the same as, or 3% slower than,
+    // one target a quad).  Its autotuner may choose otherwise.
+    if (pl.general) {
+        for (int bb : {64, 128, 256})
+            if (gen_tuning_fits(pl, ade_tuning{bb, 4, 0, 0, 1})) out = ade_tuning{bb, 4, 0, 0, 1};
+        const ade_tuning q{128, 4, 0, 0, 2};
+        if (pl.nbar_max > 2000.0 && gen_tuning_fits(pl, q)) out = q;
+    }
+    return true;
+}
+
+// Neighbour lists.  A plume keeps them when it has at most 2000 expected
+// neighbours per particle (beyond, its rows of H/4 hold 1.15 candidates per
+// neighbour, and a list entry per candidate costs more than it saves) and, in
+// 2D, when a wavefront's entries count records from its base with 16 bits (the
+// rows its targets reach hold fewer than 65536 particles).  A list has room for
+// the expected entries (two targets share up to 1.31 times one's) and a margin;
+// a plume whose particles need more walks the row windows.
+constexpr size_t kListBudget = size_t(16) << 30;  // bytes; contexts whose lists would take more keep none
+
+ListPlan list_plan(const Plan& pl, int lanes, int targets) {
+    ListPlan L;
+    if (pl.general) return L;
+    L.place.assign((size_t)pl.P, ListPlume{0u, 0u, 0u, 0u});
+    for (int p = 0; p < pl.P; ++p) {
+        const PlumeDev& d = pl.plumes[(size_t)p];
+        ListPlume& q = L.place[(size_t)p];
+        const size_t waves = (size_t)d.tcount * (size_t)(kTile / 64 * lanes / targets);
+        q.wave0 = (uint32_t)L.waves;
+        L.waves += waves;
+        const double nbar = pl.nbar[(size_t)p];
+        if (nbar > 2000.0) continue;
+        if (pl.dim == 2 && d.n > 65536u && (2.0 * d.R + 4.0) * 1.25 * d.n / d.nr + 512.0 > 65536.0) continue;
+        const double e = targets == 2 ? 1.3 * nbar + 2.0 : nbar;
+        const double cap = std::ceil((1.15 * e + 3.0 * std::sqrt(e) + 6.0) / lanes);
+        const uint32_t slots = (uint32_t)((cap + kListBatch - 1) / kListBatch) * kListBatch;
+        q.row0 = (uint32_t)L.rows;
+        q.rows = (targets == 2 ? 1 : 0) + slots / (pl.dim == 2 ? 2 : 1);
+        L.rows += waves * q.rows;
+    }
+    if (L.rows == 0) return L;
+    auto part = [](size_t n) { return (n * 4 + 255) & ~size_t(255); };
+    L.bytes = part((L.rows + kListSlack) * 64) + part(L.waves * 4);
+    if (L.bytes > kListBudget) L.bytes = 0;
+    return L;
+}
+
 double trace_D(int dim, double aL, double aT, double Dm, const double* v, double D[9]) {
     double s2 = 0;
     for (int i = 0; i < dim; ++i) s2 += v[i] * v[i];
@@ -132,6 +213,7 @@ int plan_grid(const ade_params* params, const int64_t* counts, int32_t nplumes, 
     if (pl.integrator != ADE_EULER && pl.integrator != ADE_PC)
         return fail(ADE_EINVAL, "integrator must be ADE_EULER or ADE_PC");
     pl.plumes.clear();
+    pl.nbar.clear();
     pl.tiles.clear();
     pl.list_cap = pl.list_cap_pair = 0;
     pl.nbar_max = 0.0;
@@ -310,6 +392,7 @@ int plan_grid(const ade_params* params, const int64_t* counts, int32_t nplumes, 
         pl.list_cap = std::max(pl.list_cap, list_cap_for(pl.dim, span));
         pl.list_cap_pair = std::max(pl.list_cap_pair, list_cap_pair_for(pl.dim, span));
         pl.plumes.push_back(d);
+        pl.nbar.push_back(nbar);
     }
     pl.N = (int64_t)N;
     pl.ncell = cbase;
@@ -378,36 +461,63 @@ void layout(Bump& b, ade_ctx* c, const Plan& pl) {
     c->plumes = b.take<PlumeDev>(pl.P);
     c->tiles = b.take<TileDev>(pl.ntiles);
     c->pair_tiles = b.take<TileDev>(pl.ntiles);
-    StateArrays* bufs[2] = {&c->S, &c->U};
-    for (int k = 0; k < 2; ++k) {
-        StateArrays& s = *bufs[k];
+    // sorted state and hashed buffer; what only a build uses (the hashed
+    // buffer, the counts and the buckets) comes last of the two, since a
+    // uniform flow's neighbour lists take its place between builds
+    auto state = [&](StateArrays& s, bool sorted) {
         for (int d = 0; d < 3; ++d) s.pos[d] = (d < pl.dim) ? b.take<uint32_t>(N) : nullptr;
-        s.rec = (k == 0 && !(pl.dim == 3 && pl.real_bytes == 8)) ? b.take<uint4>(N) : nullptr;
+        s.rec = (sorted && !(pl.dim == 3 && pl.real_bytes == 8)) ? b.take<uint4>(N) : nullptr;
         s.C = b.take_bytes(N * rb);
         s.id = b.take<uint32_t>(N);
-        s.key = (k == 1) ? b.take<uint32_t>(N) : nullptr;
+        s.key = !sorted ? b.take<uint32_t>(N) : nullptr;
         for (int d = 0; d < 3; ++d) s.vel[d] = (pl.general && d < pl.dim) ? b.take_bytes(N * rb) : nullptr;
         for (int d = 0; d < 6; ++d) s.rD[d] = (pl.general && d < (pl.dim == 2 ? 3 : 6)) ? b.take_bytes(N * rb) : nullptr;
-        s.grec = (k == 0 && pl.general && pl.dim == 2 && pl.real_bytes == 4) ? b.take<uint4>(2 * N) : nullptr;
+        s.grec = (sorted && pl.general && pl.dim == 2 && pl.real_bytes == 4) ? b.take<uint4>(2 * N) : nullptr;
         s.Cb = (pl.general && pl.integrator == ADE_PC) ? b.take_bytes(N * rb) : nullptr;
-    }
-    if (pl.dim == 2) {  // never read in 2D, but keep the pointers valid
-        c->S.pos[2] = c->S.pos[0];
-        c->U.pos[2] = c->U.pos[0];
-    }
-    c->count = b.take<uint32_t>(cell_pad(pl.ncell));
-    c->lists.count = c->count;
-    c->lists.bucket = b.take<uint32_t>(cell_pad(pl.ncell) * kBucket);
-    c->lists.ovf = b.take<uint2>(N);
-    c->lists.ovf_count = b.take<uint32_t>(2);
+    };
+    state(c->S, true);
     c->cell_start = b.take<uint32_t>(cell_pad(pl.ncell));
     c->scan_partial = b.take_bytes((size_t)pl.nscan * 8);
     c->aux = b.take_bytes(N * rb);
     c->aux_rec = (pl.dim == 3 && pl.real_bytes == 8) ? nullptr : b.take<uint4>(N);
     c->mass_partial = b.take<double>(pl.ntiles);
     c->range_partial = b.take<double>(2 * (size_t)pl.ntiles);
-    c->step = b.take<int64_t>(2);
-    c->nonfinite = b.take<uint32_t>(1);
+    c->lplumes = b.take<ListPlume>(pl.P);
+    c->win_tiles = b.take<TileDev>(pl.P > 1 ? pl.ntiles : 0);
+    // what a new state starts from zero, in one piece with the counts: the
+    // step counter, the overflow counters, the flags
+    const size_t words = 4 + 2 + 1 + (size_t)pl.P;
+    uint32_t* zero = b.take<uint32_t>(words);
+    c->step = reinterpret_cast<int64_t*>(zero);
+    c->lists.ovf_count = zero ? zero + 4 : nullptr;
+    c->flags = zero ? zero + 6 : nullptr;
+    const size_t build = (b.off + 255) & ~size_t(255);
+    c->count = b.take<uint32_t>(cell_pad(pl.ncell));
+    c->lists.count = c->count;
+    c->zero_bytes = ((words * 4 + 255) & ~size_t(255)) + sizeof(uint32_t) * cell_pad(pl.ncell);
+    state(c->U, false);
+    c->lists.bucket = b.take<uint32_t>(cell_pad(pl.ncell) * kBucket);
+    c->lists.ovf = b.take<uint2>(N);
+    if (pl.dim == 2) {  // never read in 2D, but keep the pointers valid
+        c->S.pos[2] = c->S.pos[0];
+        c->U.pos[2] = c->U.pos[0];
+    }
+    // the lists of any launch shape: all or none of them fit the budget
+    c->list_bytes = 0;
+    for (int shape = 0; shape < 5; ++shape) {
+        const size_t need = list_plan(pl, shape == 0 || shape == 3 ? 1 : shape == 1 ? 2 : 4, shape < 3 ? 1 : 2).bytes;
+        if (need == 0) {
+            c->list_bytes = 0;
+            break;
+        }
+        c->list_bytes = std::max(c->list_bytes, need);
+    }
+    if (c->list_bytes > 0) {
+        const size_t end = b.off;
+        b.off = build;
+        c->list_mem = b.take<char>(c->list_bytes);
+        b.off = std::max(b.off, end);
+    }
 }
 
 // smallest and largest C of a tile, then of each plume (FP64; NaNs are
@@ -487,6 +597,13 @@ int flush_events(ade_ctx* c) {
 
 namespace ade {
 
+static void drop_graph(ade_ctx* c) {
+    if (c->graph_exec) hipGraphExecDestroy(c->graph_exec);
+    if (c->graph) hipGraphDestroy(c->graph);
+    c->graph_exec = nullptr;
+    c->graph = nullptr;
+}
+
 // a pair of timing events from the context's pool into e0, e1; they are left
 // as they are when timing is off (or a graph is being captured)
 static int take_events(ade_ctx* c, hipEvent_t& e0, hipEvent_t& e1) {
@@ -506,6 +623,20 @@ static int take_events(ade_ctx* c, hipEvent_t& e0, hipEvent_t& e1) {
     return ADE_OK;
 }
 
+// the arrays of the lists of plan L
+struct ListArrays {
+    uint32_t* list;
+    ListWave* waves;
+};
+static ListArrays list_arrays(const ade_ctx* c, const ListPlan& L) {
+    Bump b(c->list_mem);
+    ListArrays q;
+    q.list = b.take<uint32_t>((L.rows + kListSlack) * 64);
+    q.waves = b.take<ListWave>(L.waves);
+    return q;
+}
+static int shape_of(const ade_tuning& t) { return 4 * t.lanes + targets_of(t); }
+
 // launch a pair kernel; when timing is on, events stamped with the kernel's
 // own start and end times are attached to the launch
 int run_pair(ade_ctx* c, int mode, const PairLaunch& a) {
@@ -515,6 +646,112 @@ int run_pair(ade_ctx* c, int mode, const PairLaunch& a) {
     int rc = take_events(c, b.ev0, b.ev1);
     if (rc) return rc;
     HIPCHK(launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->stream));
+    if (a.list && c->win_ntiles > 0) {  // the plumes without lists
+        b.list = nullptr;
+        b.step = nullptr;
+        b.tiles = c->win_tiles;
+        b.ntiles = c->win_ntiles;
+        b.ev0 = b.ev1 = nullptr;
+        if ((rc = take_events(c, b.ev0, b.ev1))) return rc;
+        HIPCHK(launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->stream));
+    }
+    return ADE_OK;
+}
+
+// Builds the lists of the current launch shape; their flags (flags[1 + plume],
+// zero before) tell lists_built which plumes' do not fit.
+static int enqueue_lists(ade_ctx* c) {
+    const Plan& pl = c->plan;
+    const int shape = shape_of(c->tuning);
+    c->list_on = false;
+    c->win_ntiles = 0;
+    c->list_shape = shape;
+    if (c->list_bytes == 0) return ADE_OK;
+    if (c->place_shape != shape) {
+        c->lists_of = list_plan(pl, c->tuning.lanes, targets_of(c->tuning));  // lives until the copy ran
+        HIPCHK(hipMemcpyAsync(c->lplumes, c->lists_of.place.data(), sizeof(ListPlume) * (size_t)pl.P,
+                              hipMemcpyHostToDevice, c->stream));
+        c->place_shape = shape;
+    }
+    const ListArrays q = list_arrays(c, c->lists_of);
+    ListBuild a;
+    std::memset(&a, 0, sizeof a);
+    a.plumes = c->plumes;
+    a.tiles = c->tiles;
+    a.ntiles = pl.ntiles;
+    a.lanes = c->tuning.lanes;
+    a.targets = targets_of(c->tuning);
+    a.list_cap = tuning_list_cap(pl, c->tuning);
+    a.lplumes = c->lplumes;
+    a.rec = c->S.rec;
+    for (int d = 0; d < 3; ++d) a.spos[d] = c->S.pos[d];
+    a.cell_start = c->cell_start;
+    a.list = q.list;
+    a.waves = q.waves;
+    a.over = c->flags + 1;
+    HIPCHK(launch_list(pl.dim, pl.real_bytes, a, c->stream));
+    return ADE_OK;
+}
+
+// the flags, by a synchronisation of the stream
+static int read_flags(ade_ctx* c, std::vector<uint32_t>& h) {
+    h.resize(1 + (size_t)c->plan.P);
+    HIPCHK(hipMemcpyAsync(h.data(), c->flags, sizeof(uint32_t) * h.size(), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipStreamSynchronize(c->stream));
+    return ADE_OK;
+}
+
+// From the flags behind enqueue_lists: which plumes have lists.
+static int lists_built(ade_ctx* c, const std::vector<uint32_t>& flags) {
+    if (c->list_bytes == 0) return ADE_OK;
+    const Plan& pl = c->plan;
+    std::vector<ListPlume>& place = c->lists_of.place;
+    bool full = false, with = false;
+    std::vector<TileDev> rest;
+    for (int p = 0; p < pl.P; ++p) {
+        if (flags[1 + (size_t)p]) {  // a list did not fit: the plume walks the row windows
+            place[(size_t)p].rows = 0;
+            full = true;
+        }
+        with = with || place[(size_t)p].rows != 0;
+    }
+    if (full) {
+        HIPCHK(hipMemcpyAsync(c->lplumes, place.data(), sizeof(ListPlume) * place.size(), hipMemcpyHostToDevice,
+                              c->stream));
+        c->place_shape = 0;  // other particles may fit
+    }
+    for (const TileDev& t : pl.pair_tiles)
+        if (with && place[t.plume].rows == 0) rest.push_back(t);
+    if (!rest.empty())
+        HIPCHK(hipMemcpyAsync(c->win_tiles, rest.data(), sizeof(TileDev) * rest.size(), hipMemcpyHostToDevice,
+                              c->stream));
+    if (full || !rest.empty()) HIPCHK(hipStreamSynchronize(c->stream));
+    c->list_on = with;
+    c->win_ntiles = (uint32_t)rest.size();
+    return ADE_OK;
+}
+
+// The lists belong to the particles and the launch shape of their build.  A
+// caller's own graph of the call may be replayed after either changed, so a
+// call under capture walks the row windows instead.
+int settle_lists(ade_ctx* c) {
+    c->list_use = false;
+    if (c->plan.general || c->list_bytes == 0) return ADE_OK;
+    if (c->stream) {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
+            (void)hipGetLastError();
+            return ADE_OK;
+        }
+    }
+    if (c->list_shape != shape_of(c->tuning)) {
+        std::vector<uint32_t> h;
+        HIPCHK(hipMemsetAsync(c->flags + 1, 0, sizeof(uint32_t) * (size_t)c->plan.P, c->stream));
+        int rc = enqueue_lists(c);
+        if (rc || (rc = read_flags(c, h)) || (rc = lists_built(c, h))) return rc;
+        drop_graph(c);  // captured over other lists
+    }
+    c->list_use = c->list_on;
     return ADE_OK;
 }
 
@@ -532,6 +769,12 @@ PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void
                      uint4* out_rec) {
     PairLaunch a;
     std::memset(&a, 0, sizeof a);
+    if (c->list_use) {
+        const ListArrays q = list_arrays(c, c->lists_of);
+        a.list = q.list;
+        a.lplumes = c->lplumes;
+        a.waves = q.waves;
+    }
     a.plumes = c->plumes;
     a.tiles = c->pair_tiles;
     a.ntiles = c->plan.ntiles;
@@ -641,13 +884,6 @@ void drop_events(ade_ctx* c) {
     c->ev_used = 0;
 }
 
-void drop_graph(ade_ctx* c) {
-    if (c->graph_exec) hipGraphExecDestroy(c->graph_exec);
-    if (c->graph) hipGraphDestroy(c->graph);
-    c->graph_exec = nullptr;
-    c->graph = nullptr;
-}
-
 }  // namespace
 
 extern "C" {
@@ -687,51 +923,9 @@ int ade_create(const ade_params* params, const int64_t* counts, int32_t nplumes,
         delete c;
         return fail(ADE_EINVAL, "a 2D FP32 velocity-field context holds at most 2^27 - 256 particles");
     }
-    // default launch shape: the fewest lanes per particle that still give
-    // the chip about 4 wavefronts per SIMD (4096 wavefronts of 64 lanes, i.e.
-    // 2^18 lanes): two targets per lane from 2^19 particles on (the fastest
-    // shape on the 2D sweep), one lane per target from 2^18, two lanes from
-    // 2^17, else four; then the next shapes whose candidate lists fit in LDS.
-    // Plumes of thousands of neighbours per particle, and 3D plumes, take
-    // four lanes per target, or in FP32 four lanes per two neighbouring
-    // targets: the targets of a wavefront then walk nearly the same candidate
-    // ranges and share their cache lines, and a pair of targets shares every
-    // record it fetches (the autotuner's choice on the 10^6-particle,
-    // 31k-neighbour problem: 19.3 ms per pair launch against 22.8 ms for one
-    // target a quad; on the 128^3 plume 0.88-0.90 ms against 0.90-0.92).
-    {
-        const int64_t N = c->plan.N;
-        const bool quads = c->plan.nbar_max > 2000.0 || c->plan.dim == 3;
-        const int qtargets = c->plan.real_bytes == 4 ? 2 : 1;
-        const ade_tuning first = quads ? ade_tuning{c->plan.dim == 3 ? 64 : 128, 4, 128, 0, qtargets}
-                                 : N >= (1 << 19) ? ade_tuning{64, 1, 0, 0, 2}
-                                 : N >= (1 << 18) ? ade_tuning{256, 1, 0, 0, 1}
-                                 : N >= (1 << 17) ? ade_tuning{256, 2, 0, 0, 1}
-                                                  : ade_tuning{256, 4, 0, 0, 1};
-        const ade_tuning defaults[6] = {first, {256, 2, 0, 0, 1}, {256, 4, 0, 0, 1}, {128, 4, 0, 0, 1},
-                                        {64, 4, 0, 0, 1}, {64, 1, 0, 0, 2}};
-        bool ok = false;
-        for (const ade_tuning& t : defaults)
-            if (!ok && tuning_fits(c->plan, t)) {
-                c->tuning = t;
-                ok = true;
-            }
-        if (!ok) {
-            delete c;
-            return fail(ADE_EINVAL, "too many neighbour rows: the candidate lists do not fit in LDS");
-        }
-        // a velocity field: four lanes per target in the largest workgroup
-        // whose lists fit, or in 2D FP32 for plumes of thousands of
-        // neighbours four lanes per two targets, block 128 (10^6 particles,
-        // 31k neighbours: 44 against 64 ms per update launch; on the 512^2
-        // plumes of 46 and 111 neighbours the same as, or 3% slower than,
-        // one target a quad).  Its autotuner may choose otherwise.
-        if (c->plan.general) {
-            for (int bb : {64, 128, 256})
-                if (gen_tuning_fits(c->plan, ade_tuning{bb, 4, 0, 0, 1})) c->tuning = ade_tuning{bb, 4, 0, 0, 1};
-            const ade_tuning q{128, 4, 0, 0, 2};
-            if (c->plan.nbar_max > 2000.0 && gen_tuning_fits(c->plan, q)) c->tuning = q;
-        }
+    if (!default_tuning(c->plan, c->tuning)) {
+        delete c;
+        return fail(ADE_EINVAL, "too many neighbour rows: the candidate lists do not fit in LDS");
     }
     Bump b(d_ws);
     layout(b, c, c->plan);
@@ -750,9 +944,7 @@ int ade_create(const ade_params* params, const int64_t* counts, int32_t nplumes,
         hipMemcpyAsync(c->tiles, pl.tiles.data(), sizeof(TileDev) * pl.ntiles, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipMemcpyAsync(c->pair_tiles, pl.pair_tiles.data(), sizeof(TileDev) * pl.ntiles, hipMemcpyHostToDevice, c->stream) != hipSuccess ||
         hipMemcpyAsync(c->cell_start + pl.ncell, &c->h_total, sizeof(uint32_t), hipMemcpyHostToDevice, c->stream) != hipSuccess ||
-        hipMemsetAsync(c->count, 0, sizeof(uint32_t) * cell_pad(pl.ncell), c->stream) != hipSuccess ||
-        hipMemsetAsync(c->step, 0, 2 * sizeof(int64_t), c->stream) != hipSuccess ||
-        hipMemsetAsync(c->lists.ovf_count, 0, 2 * sizeof(uint32_t), c->stream) != hipSuccess ||
+        hipMemsetAsync(c->step, 0, c->zero_bytes, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess)
         return cleanup(fail(ADE_EHIP, "uploading the plume tables failed"));
     *out = c;
@@ -762,14 +954,13 @@ int ade_create(const ade_params* params, const int64_t* counts, int32_t nplumes,
 int ade_init_particles(ade_ctx* c, const double* d_x, const void* d_C) {
     if (!c || !d_x || !d_C) return fail(ADE_EINVAL, "null argument");
     const Plan& pl = c->plan;
-    HIPCHK(hipMemsetAsync(c->count, 0, sizeof(uint32_t) * cell_pad(pl.ncell), c->stream));
-    HIPCHK(hipMemsetAsync(c->lists.ovf_count, 0, 2 * sizeof(uint32_t), c->stream));
-    HIPCHK(hipMemsetAsync(c->step, 0, 2 * sizeof(int64_t), c->stream));
+    HIPCHK(hipMemsetAsync(c->step, 0, c->zero_bytes, c->stream));
     HIPCHK(launch_init(pl.dim, pl.real_bytes, c->plumes, c->tiles, pl.ntiles, d_x, d_C, (uint32_t)pl.N,
                        c->U, c->lists, c->stream));
     c->initialized = true;
     c->built = false;
     c->vel_set = false;
+    c->list_shape = 0;
     if (!c->coincident) drop_graph(c);
     c->coincident = true;  // until the cell build checks the new positions
     return ADE_OK;
@@ -787,23 +978,26 @@ int ade_set_velocities(ade_ctx* c, const double* d_v) {
     return ADE_OK;
 }
 
-// Whether two particles of a plume share a position, from the built cells
-// (synchronises the stream).  With a uniform flow every particle of a plume
-// moves by the same displacement, so the answer holds for the whole run; a
-// velocity-field context keeps its own kernels and is not checked.
-static int check_coincident(ade_ctx* c) {
+// What a build leaves to find out, the flags being zero (synchronises the
+// stream): whether two
+// particles of a plume share a position, and the neighbour lists.  With a
+// uniform flow every particle of a plume moves by the same displacement, so
+// both hold for the whole run; a velocity-field context keeps its own kernels
+// and is not checked.
+static int after_build(ade_ctx* c) {
     const Plan& pl = c->plan;
     bool found = true;
     if (!pl.general) {
-        uint32_t h = 0;
-        HIPCHK(hipMemsetAsync(c->nonfinite, 0, sizeof(uint32_t), c->stream));
-        HIPCHK(launch_coincident(pl.dim, c->plumes, c->tiles, pl.ntiles, c->S, c->cell_start, c->nonfinite,
+        std::vector<uint32_t> h;
+        HIPCHK(launch_coincident(pl.dim, c->plumes, c->tiles, pl.ntiles, c->S, c->cell_start, c->flags,
                                  c->stream));
-        HIPCHK(hipMemcpyAsync(&h, c->nonfinite, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
-        HIPCHK(hipStreamSynchronize(c->stream));
-        found = h != 0;
+        int rc = enqueue_lists(c);
+        if (rc || (rc = read_flags(c, h)) || (rc = lists_built(c, h))) return rc;
+        found = h[0] != 0;
+        // a captured step holds the other kernels
+        if (c->graph_lists != c->list_on || c->win_ntiles > 0) drop_graph(c);
     }
-    if (found != c->coincident) drop_graph(c);  // a captured step holds the other kernels
+    if (found != c->coincident) drop_graph(c);  // here too
     c->coincident = found;
     return ADE_OK;
 }
@@ -817,7 +1011,7 @@ int ade_build_cells(ade_ctx* c) {
     int rc = enqueue_build(c, 0);
     if (rc) return rc;
     c->built = true;
-    return check_coincident(c);
+    return after_build(c);
 }
 
 int ade_coincident(const ade_ctx* c, int32_t* out) {
@@ -832,16 +1026,16 @@ static int check_finite(ade_ctx* c) {
     const Plan& pl = c->plan;
     if (!pl.check_finite) return ADE_OK;
     uint32_t h = 0;
-    HIPCHK(hipMemsetAsync(c->nonfinite, 0, sizeof(uint32_t), c->stream));
+    HIPCHK(hipMemsetAsync(c->flags, 0, sizeof(uint32_t), c->stream));
     const uint32_t N = (uint32_t)pl.N;
     if (pl.real_bytes == 4)
         hipLaunchKernelGGL((k_check_finite<float>), dim3((N + 255) / 256), dim3(256), 0, c->stream,
-                           (const float*)c->S.C, N, c->nonfinite);
+                           (const float*)c->S.C, N, c->flags);
     else
         hipLaunchKernelGGL((k_check_finite<double>), dim3((N + 255) / 256), dim3(256), 0, c->stream,
-                           (const double*)c->S.C, N, c->nonfinite);
+                           (const double*)c->S.C, N, c->flags);
     HIPCHK(hipGetLastError());
-    HIPCHK(hipMemcpyAsync(&h, c->nonfinite, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(hipMemcpyAsync(&h, c->flags, sizeof(uint32_t), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     if (h) return fail(ADE_ENONFINITE, "a concentration is not finite after the step (ADE_CHECK_FINITE)");
     return ADE_OK;
@@ -851,8 +1045,8 @@ int ade_step(ade_ctx* c, int64_t nsteps) {
     if (!c) return fail(ADE_EINVAL, "null ctx");
     if (nsteps < 0) return fail(ADE_EINVAL, "nsteps must be >= 0");
     if (!c->built) return fail(ADE_ESTATE, "ade_step before ade_build_cells");
-    int rc = enqueue_steps(c, nsteps);
-    if (rc) return rc;
+    int rc = settle_lists(c);
+    if (rc || (rc = enqueue_steps(c, nsteps))) return rc;
     return nsteps > 0 ? check_finite(c) : ADE_OK;
 }
 
@@ -864,10 +1058,13 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
     // the graph holds kGraphSteps steps (an even number: the state ends where
     // it began); fewer steps, and the rest, are launched one by one
     int64_t left = nsteps;
+    int rc = settle_lists(c);
+    if (rc) return rc;
     if (left >= kGraphSteps && !c->graph_exec) {
         HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         c->capturing = true;
-        int rc = enqueue_steps(c, kGraphSteps);
+        c->graph_lists = c->list_use;
+        rc = enqueue_steps(c, kGraphSteps);
         c->capturing = false;
         hipGraph_t g = nullptr;
         hipError_t e = hipStreamEndCapture(c->stream, &g);
@@ -884,8 +1081,7 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
         }
     }
     for (; left >= kGraphSteps; left -= kGraphSteps) HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
-    int rc = enqueue_steps(c, left);
-    if (rc) return rc;
+    if ((rc = enqueue_steps(c, left))) return rc;
     return nsteps > 0 ? check_finite(c) : ADE_OK;
 }
 
@@ -894,6 +1090,8 @@ int ade_rhs(ade_ctx* c, void* d_rhs) {
     if (!c->built) return fail(ADE_ESTATE, "ade_rhs before ade_build_cells");
     const Plan& pl = c->plan;
     if (pl.general) return run_gen(c, kModeRhs, d_rhs);
+    int rc = settle_lists(c);
+    if (rc) return rc;
     return run_pair(c, kModeRhs, pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, d_rhs, nullptr));
 }
 
@@ -1086,6 +1284,7 @@ int ade_autotune(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* best) {
     int rc = time_candidates(c, (int)cands.size(), reps, e0, e1,
                              [&](int k) {
                                  c->tuning = cands[(size_t)k];
+                                 if (settle_lists(c) != ADE_OK) return hipErrorUnknown;
                                  PairLaunch a =
                                      pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, c->aux, c->aux_rec);
                                  a.ev0 = e0;
@@ -1281,14 +1480,14 @@ int ade_load_state(ade_ctx* c, const void* h_buf, size_t bytes) {
         if (nb != s.bytes) HIPCHK(hipMemcpyAsync(c->step + 1, p, 8, hipMemcpyHostToDevice, c->stream));
         p += nb;
     }
-    // the next step's counting pass starts from empty cells
+    // a velocity field's next counting pass starts from empty cells; the flags
     HIPCHK(hipMemsetAsync(c->count, 0, sizeof(uint32_t) * cell_pad(pl.ncell), c->stream));
-    HIPCHK(hipMemsetAsync(c->lists.ovf_count, 0, 2 * sizeof(uint32_t), c->stream));
+    HIPCHK(hipMemsetAsync(c->lists.ovf_count, 0, sizeof(uint32_t) * (2 + 1 + (size_t)pl.P), c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
     c->initialized = true;
     c->built = true;
     c->vel_set = true;
-    return check_coincident(c);
+    return after_build(c);
 }
 
 int ade_destroy(ade_ctx* c) {

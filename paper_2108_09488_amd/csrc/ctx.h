@@ -34,10 +34,18 @@ struct Plan {
     bool general = false;   // velocity field: per-particle velocities (ADE_VELOCITY_FIELD)
     bool check_finite = false;  // ADE_CHECK_FINITE on any plume
     std::vector<PlumeDev> plumes;
+    std::vector<double> nbar;   // expected neighbours per particle of each plume
     std::vector<TileDev> tiles;
     std::vector<TileDev> pair_tiles;  // the tiles in the pair kernel's order (costliest plumes first)
 };
 
+// The neighbour lists of a plan for a launch shape: each plume's place, and the
+// sizes of the arrays they take (bytes 0: no plume keeps any).
+struct ListPlan {
+    size_t rows = 0, waves = 0, bytes = 0;
+    std::vector<ListPlume> place;
+};
+ListPlan list_plan(const Plan& pl, int lanes, int targets);
 // whether a launch shape fits the plan (LDS of the candidate lists)
 bool tuning_fits(const Plan& pl, const ade_tuning& t);
 
@@ -63,7 +71,21 @@ struct ade_ctx {
     double* mass_partial = nullptr;
     double* range_partial = nullptr;  // per tile: min and max of C
     int64_t* step = nullptr;  // the step counter (uniform flow: a FrameStep, k then k0)
-    uint32_t* nonfinite = nullptr;  // finite check: set when a concentration is not finite
+    // checks: [0] a non-finite concentration or coincident particles, [1 + plume] its lists do not fit
+    uint32_t* flags = nullptr;
+    size_t zero_bytes = 0;  // from step on: what a new state starts from zero
+    // neighbour lists (uniform flow), in the buffers that only a build uses
+    char* list_mem = nullptr;
+    size_t list_bytes = 0;  // 0: the context keeps none
+    ade::ListPlume* lplumes = nullptr;
+    ade::TileDev* win_tiles = nullptr;  // tiles of the plumes without lists, when some plumes have them
+    ade::ListPlan lists_of;  // the lists that are there
+    int list_shape = 0;      // launch shape (lists_shape) they, or their absence, were settled for; 0: not since the build
+    int place_shape = 0;     // launch shape lplumes holds the places of (0: none)
+    uint32_t win_ntiles = 0;
+    bool list_on = false;    // some plume has lists
+    bool list_use = false;   // the kernels of the current call read them
+    bool graph_lists = false;  // the captured steps read lists
     uint32_t h_total = 0;  // host copy of N for the cell-start sentinel
     bool initialized = false, built = false;
     // two particles of a plume share a position (the pair kernels then test
@@ -83,6 +105,9 @@ struct ade_ctx {
 
 namespace ade {
 
+// settles whether the kernels of the call read neighbour lists, and builds
+// them for the current launch shape if they are not there
+int settle_lists(ade_ctx* c);
 // enqueue a pair kernel (timed when timing is on)
 int run_pair(ade_ctx* c, int mode, const PairLaunch& a);
 // launch arguments of a pair kernel over the sorted particles of c: rec the

@@ -37,103 +37,9 @@
 // current one is evaluated.
 #include <hip/hip_ext.h>
 
-#include "ade_walk.h"
+#include "ade_pair.h"
 
 namespace ade {
-
-// One candidate: the pair term, evaluated without a branch (the lanes of a
-// wavefront almost never all fail the predicate together); the kernel factor
-// vanishes outside the support, and a candidate at r = 0 adds nothing.
-// the constant the kernel factor of the pair term leaves out: its value at q = 0
-template <int KERN>
-constexpr double kPolyScale = (KERN == 4) ? 6.0 : 1.0;
-
-// the bracket is A0 + S (E . x / r)^2 with S = +-1 (PlumeDev::dterm; in 2D
-// S = +1 always).  The term forms S times it, (E . x / r)^2 + S A0, and
-// finish_target multiplies the sum by S.
-// ZC (zero separations): two distinct particles may share a position, so a
-// candidate at r = 0 is cut by a select.  Without ZC the only candidate at
-// r = 0 is the target's own record (a padding slot re-reads it): r^2 starts
-// from a tiny offset (2^-40 in FP32), far below half a unit in the last place
-// of any r^2 >= 1 (grid units), so it changes such an r^2 only where the
-// exact sum sits on a rounding tie (then by one unit in the last place); it
-// keeps the self term finite, and the self term is w (C_a - C_a) = 0 exactly.
-template <typename real>
-constexpr real kTinyR2 = sizeof(real) == 4 ? (real)9.094947017729282e-13 : (real)7.888609052210118e-31;  // 2^-40, 2^-100
-template <int DIM, typename real, int KERN, bool ZC>
-struct PairTerm {
-    real invHu, a0s, ex, ey, ez;
-    __device__ __forceinline__ void operator()(const Target& T, real Ca, uint32_t bx, uint32_t by,
-                                               uint32_t bz, real Cb, real& acc) const {
-        (*this)(T, Ca, bx, by, bz, Cb, true, acc);
-    }
-    // the same, added only if keep (a padding slot of a walk shared by two
-    // targets)
-    __device__ __forceinline__ void operator()(const Target& T, real Ca, uint32_t bx, uint32_t by,
-                                               uint32_t bz, real Cb, bool keep, real& acc) const {
-        const real dx = (real)(int32_t)(T.ux - bx);
-        const real dy = (real)(int32_t)(T.uy - by);
-        const real dz = (DIM == 3) ? (real)(int32_t)(T.uz - bz) : (real)0;
-        sep(dx, dy, dz, Ca, Cb, keep, acc);
-    }
-    // the same from the separation (dx, dy, dz) = x_a - x_b in grid units
-    __device__ __forceinline__ void sep(real dx, real dy, real dz, real Ca, real Cb, bool keep, real& acc) const {
-        real r2 = ZC ? dx * dx : fmar(dx, dx, kTinyR2<real>);
-        r2 = fmar(dy, dy, r2);
-        if (DIM == 3) r2 = fmar(dz, dz, r2);
-        // with ZC, r2 = 0 (the target itself, a padding slot, a coincident
-        // particle) is cut by the select below; the support r <= H by the
-        // clamp of 1 - q at 0, which zeroes the kernel factor outside it (W is
-        // 0 at q = 1, so where the rounding of r puts 1 - q on the other side
-        // of 0 the term is below 1e-28 of a typical one either way)
-        const bool inside = ZC ? (keep && r2 > (real)0) : keep;
-        const real rinv = rsqrt_r(r2);
-        const real r = r2 * rinv;
-        const real omq = clamp_unit(fmar(-r, invHu, (real)1));
-        real f;
-        if (KERN == 4) {  // (1 - q)^5 (1 + 5q) / 6
-            const real o2 = omq * omq;
-            f = (o2 * o2) * fmar((real)(-5.0 / 6.0), o2, omq);
-        } else {
-            f = omq * omq * omq;
-        }
-        real p = ex * dx;
-        p = fmar(ey, dy, p);
-        if (DIM == 3) p = fmar(ez, dz, p);
-        const real pr = p * rinv;
-        const real A = fmar(pr, pr, a0s);  // S times the bracket
-        const real w = inside ? A * f : (real)0;
-        acc = fmar(w, Ca - Cb, acc);
-    }
-};
-
-// the constants come from the plume table as they are (FP32 copies for FP32),
-// so they stay in scalar registers
-template <int DIM, typename real, int KERN, bool ZC>
-__device__ __forceinline__ PairTerm<DIM, real, KERN, ZC> make_term(const PlumeDev& P) {
-    PairTerm<DIM, real, KERN, ZC> t;
-    real c[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) c[k] = (sizeof(real) == 4) ? (real)P.fterm[k] : (real)P.dterm[k];
-    t.invHu = c[1];
-    t.a0s = c[3] * c[4];
-    t.ex = c[5];
-    t.ey = c[6];
-    t.ez = c[7];
-    return t;
-}
-
-
-template <typename real>
-struct Cand {
-    uint32_t x, y, z;
-    real C;
-};
-
-template <int DIM, typename real>
-__device__ __forceinline__ Cand<real> unpack(const uint4& r) {
-    return Cand<real>{r.x, r.y, (DIM == 3) ? r.z : 0u, Rec<DIM, real>::conc(r)};
-}
 
 // Walk a target's list: every lane evaluates its share of the concatenated
 // ranges in batches of B records.  The wavefront runs as many batches as its
@@ -150,35 +56,6 @@ __device__ __forceinline__ void walk_list(const Term& term, const Target& T,
     walk_list_fn<LANES, Batch<LANES>::value>(self, list, stride, total, lj, fetch, [&](const Cand<real>& c, bool) {
         term(T, Ca, c.x, c.y, c.z, c.C, acc);
     });
-}
-
-// The end of a target's pair sum acc: rhs mode writes the right-hand side
-// (vphi * acc) in id order; update mode the new concentration Cbase +
-// scale dt rhs with its candidate record, in cell order.  A uniform flow
-// moves every particle of a plume by the same displacement, so neither the
-// order of the particles nor the cells of the build change (positions are
-// kept in the plume's frame, ade_internal.h).
-template <int DIM, typename real, int KERN, int MODE>
-__device__ __forceinline__ void finish_target(const PairLaunch& a, const PlumeDev& P, const Target& T, uint32_t i,
-                                              real acc) {
-    constexpr bool kRec = Rec<DIM, real>::kStageable;
-    // the kernel factor's constant and the bracket's sign S (the pair term
-    // sums S times the bracket)
-    const double kS = kPolyScale<KERN> * P.dterm[4];
-    if (MODE == kModeRhs) {
-        static_cast<real*>(a.out)[a.sid[i]] = (real)(kS * P.vphi) * acc;
-        return;
-    }
-    const real sc = (real)(a.scale * P.dt * P.vphi * kS);
-    const real Cn = fmar(sc, acc, static_cast<const real*>(a.Cbase)[i]);
-    static_cast<real*>(a.out)[i] = Cn;
-    if (kRec) a.out_rec[i] = Rec<DIM, real>::pack(T.ux, T.uy, T.uz, Cn);
-}
-
-// The step counter, advanced by one thread of the launch that ends a step
-// (no kernel of the launch reads it).
-__device__ __forceinline__ void advance_step(const PairLaunch& a) {
-    if (a.step && blockIdx.x == 0 && threadIdx.x == 0) *a.step += 1;
 }
 
 // One work item = `block / LANES` consecutive target particles of one tile.
@@ -240,7 +117,7 @@ __device__ __forceinline__ void pair_item(const PairLaunch& a, const PlumeDev* _
     if (LANES >= 2) acc += __shfl_xor(acc, 1, kWave);
     if (LANES >= 4) acc += __shfl_xor(acc, 2, kWave);
     if (!active || lj != 0) return;
-    finish_target<DIM, real, KERN, MODE>(a, P, T, i, acc);
+    finish_target<DIM, real, KERN, MODE>(a, P, Cand<real>{T.ux, T.uy, T.uz, Ca}, i, acc);
 }
 
 // ---------------------------------------------------------------------------
@@ -262,38 +139,6 @@ __device__ __forceinline__ void pair_item(const PairLaunch& a, const PlumeDev* _
 // rows).  A pair whose rows are further apart (sparse plumes) walks a's own
 // list, then b's.
 // ---------------------------------------------------------------------------
-template <int DIM>
-__device__ __forceinline__ uint32_t build_union(const PlumeDev& P, const uint32_t* __restrict__ cs, const Target& A,
-                                                const Target& B, int dy, int dz, uint2* list, uint32_t stride) {
-    const int R = P.R;
-    const int ny = 2 * R + 1 + (dy != 0 ? 1 : 0);
-    const int nz = (DIM == 3) ? 2 * R + 1 + (dz != 0 ? 1 : 0) : 1;
-    const int nrows = ny * nz;
-    const int oy0 = min(0, dy) - R, oy1 = oy0 + ny - 1;
-    int oy = oy0, oz = (DIM == 3) ? min(0, dz) - R : 0;  // the row of j, stepped on (oy fastest)
-    const float dxc = (float)(int32_t)(B.ux - A.ux) * P.cellx;
-    ListWriter w(list, stride);
-    // two rows at a time: their cell-start loads are in flight together
-    for (int j = 0; j < nrows; j += 2) {
-        RowRanges r[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            r[q] = RowRanges{0u, 0u, 0u, 0u};
-            if (j + q < nrows) r[q] = union_row<DIM>(P, cs, A, B, dxc, dy, dz, oy, oz);
-            if (++oy > oy1) {
-                oy = oy0;
-                ++oz;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            if (r[q].e1 > r[q].s1) w.put(r[q].s1, r[q].e1);
-            if (r[q].e0 > r[q].s0) w.put(r[q].s0, r[q].e0);
-        }
-    }
-    return w.flush();
-}
-
 // The walk of one lane's list (walk_stream) for two targets: every record
 // fetched is evaluated against TA and TB.  Padding slots re-read a's own
 // record, which a's predicate rejects (r2 = 0); b's evaluation keeps only the
@@ -369,8 +214,8 @@ __device__ __forceinline__ void pair_item2(const PairLaunch& a, const PlumeDev* 
     else list[0] = make_uint2(kListEndStart, kListEndEnd);
     const PairTerm<DIM, real, KERN, ZC> term = make_term<DIM, real, KERN, ZC>(P);
     walk_pair<DIM>(term, TA, TB, CA, CB, iA, list, stride, total, fetch, accA, accB);
-    if (actA) finish_target<DIM, real, KERN, MODE>(a, P, TA, iA, accA);
-    if (merged) finish_target<DIM, real, KERN, MODE>(a, P, TB, iB, accB);
+    if (actA) finish_target<DIM, real, KERN, MODE>(a, P, Cand<real>{TA.ux, TA.uy, TA.uz, CA}, iA, accA);
+    if (merged) finish_target<DIM, real, KERN, MODE>(a, P, Cand<real>{TB.ux, TB.uy, TB.uz, CB}, iB, accB);
 
     // b of a pair that could not be merged walks its own list (a second walk
     // that only wavefronts holding such a pair enter)
@@ -383,7 +228,7 @@ __device__ __forceinline__ void pair_item2(const PairLaunch& a, const PlumeDev* 
     else list[0] = make_uint2(kListEndStart, kListEndEnd);
     real acc2 = (real)0;
     walk_list<1>(term, T2, C2, iB, list, stride, total2, 0u, fetch, acc2);
-    if (alone) finish_target<DIM, real, KERN, MODE>(a, P, T2, iB, acc2);
+    if (alone) finish_target<DIM, real, KERN, MODE>(a, P, Cand<real>{T2.ux, T2.uy, T2.uz, C2}, iB, acc2);
 }
 
 // ---------------------------------------------------------------------------
@@ -477,8 +322,8 @@ __device__ __forceinline__ void pair_item42(const PairLaunch& a, const PlumeDev*
     accA += __shfl_xor(accA, 2, kWave);
     accB += __shfl_xor(accB, 1, kWave);
     accB += __shfl_xor(accB, 2, kWave);
-    if (lj == 0 && actA) finish_target<DIM, real, KERN, MODE>(a, P, target(iA), iA, accA);
-    if (lj == 1 && actB) finish_target<DIM, real, KERN, MODE>(a, P, target(iB), iB, accB);
+    if (lj == 0 && actA) finish_target<DIM, real, KERN, MODE>(a, P, unpack<DIM, real>(rec[iA]), iA, accA);
+    if (lj == 1 && actB) finish_target<DIM, real, KERN, MODE>(a, P, unpack<DIM, real>(rec[iB]), iB, accB);
 }
 
 // Six wavefronts per SIMD: at most 80 VGPRs (101 without the bound, four
@@ -676,6 +521,7 @@ hipError_t launch_pair(int dim, int real_bytes, int kernel, int mode, const Pair
     if (a.lanes != 1 && a.lanes != 2 && a.lanes != 4) return hipErrorInvalidValue;
     if (a.targets != 1 && (a.targets != 2 || !((a.lanes == 1 && 2 * a.block <= kTile) || a.lanes == 4)))
         return hipErrorInvalidValue;
+    if (a.list) return launch_pair_list(dim, real_bytes, kernel, mode, a, s);
     if (a.list_cap < 3 || pair_lds_bytes(a.block, a.lanes, a.list_cap) > kPairLdsMax) return hipErrorInvalidValue;
     if (dim == 2) {
         if (real_bytes == 4) {
