@@ -39,7 +39,7 @@
 #include <mutex>
 #include <type_traits>
 
-#include "ade_walk.h"
+#include "ade_list.h"
 #include "ctx.h"
 
 namespace ade {
@@ -168,9 +168,9 @@ __global__ __launch_bounds__(256) void k_sensor_seed(const PlumeDev* __restrict_
 // ---------------------------------------------------------------------------
 // adjoint step
 // ---------------------------------------------------------------------------
-// The adjoint passes walk the candidate lists of the forward kernels (cell
-// rows in LDS, one lane per target, batches of records in flight).  A
-// candidate carries its position and the pass's two values: X (the state in
+// The adjoint passes walk the neighbour lists of the forward kernels, or, for a
+// plume without lists, its row windows (one lane per target).  A candidate
+// carries its position and the pass's two values: X (the state in
 // the gradient terms) and u (the vector the operator is applied to).  In 2D
 // FP32 they travel as one 16-byte record (x, y, X, u) written just before
 // the pass; otherwise they are read from the arrays.
@@ -203,10 +203,6 @@ __global__ __launch_bounds__(256) void k_adj_pack(StateArrays S, const float* __
     if (i < N) arec[i] = make_uint4(S.pos[0][i], S.pos[1][i], fbits(X[i]), fbits(u[i]));
 }
 
-struct AdjConst {
-    double speed;    // |v|
-};
-
 // kAdjEuler: out = lambda^n = lam + dt L lam, gradient dt lam . L_k X.
 // kAdjHalf:  out = mu = lam + dt/2 L lam, xh_out = C^h = X + dt/2 L X,
 //            arec_out = their records, gradient dt (mu - lam) . L_k X.
@@ -218,60 +214,43 @@ struct AdjConst {
 // partials go to gpart[3 * blockIdx.x ..].
 enum AdjMode { kAdjEuler = 0, kAdjHalf = 1, kAdjFull = 2 };
 
+struct AdjLaunch {
+    const PlumeDev* plumes;
+    const TileDev* tiles;
+    uint32_t ntiles;
+    StateArrays S;
+    const uint32_t* cs;
+    const void* u;       // the vector the operator is applied to
+    const void* lam;
+    const void* X;       // the state in the gradient terms
+    const uint4* arec;   // 2D FP32: records (x, y, X, u)
+    void* lam_out;
+    void* xh_out;
+    const void* Xnext;
+    uint4* arec_out;
+    double speed;        // |v|
+    double* gpart;
+    // neighbour lists of the launch shape (list null: row windows)
+    const uint32_t* list;
+    const ListPlume* lplumes;
+    const ListWave* waves;
+};
+
+// The pass's term of one pair: sums of a target.
 template <int DIM, typename real, int KERN, int AMODE>
-__global__ __launch_bounds__(256) void k_adjoint(const PlumeDev* __restrict__ plumes,
-                                                const TileDev* __restrict__ tiles, StateArrays S,
-                                                const uint32_t* __restrict__ cs,
-                                                const real* __restrict__ u_s,
-                                                const real* __restrict__ lam_s,
-                                                const real* __restrict__ X,
-                                                const uint4* __restrict__ arec,
-                                                real* __restrict__ lam_out, real* __restrict__ xh_out,
-                                                const real* __restrict__ Xnext,
-                                                uint4* __restrict__ arec_out, AdjConst ac,
-                                                double* __restrict__ gpart) {
-    extern __shared__ uint2 lds_list[];
-    __shared__ double lds[kTile / kWave];
-    constexpr bool kPacked = ARec<DIM, real>::kPacked;
-    const uint32_t tpb = blockDim.x, subs = kTile / tpb;
-    const TileDev t = tiles[blockIdx.x / subs];
-    const uint32_t i0 = t.start + (blockIdx.x % subs) * tpb;
-    if (i0 >= t.end) return;  // whole workgroup: ragged last tile
-    const uint32_t i1 = min(t.end, i0 + tpb);
-    const PlumeDev P = plumes[t.plume];
-    const bool active = i0 + threadIdx.x < i1;
-    const uint32_t i = active ? i0 + threadIdx.x : i0;
-    const uint32_t* __restrict__ px = S.pos[0];
-    const uint32_t* __restrict__ py = S.pos[1];
-    const uint32_t* __restrict__ pz = S.pos[2];
-    const Target T = make_target<DIM>(P, px[i], py[i], (DIM == 3) ? pz[i] : 0u);
-    const real Xi = X[i], ui = u_s[i], li = lam_s[i];
-    const real H2 = h2_of<real>(P), invHu = (real)P.invHu;
-    const real a0 = (real)P.a0, a1 = (real)P.a1;
-    const real gam = (real)(DIM + 2), spd = (real)ac.speed;
-    const real vx = (real)P.ehat[0], vy = (real)P.ehat[1], vz = (real)P.ehat[2];
-
-    uint2* list = lds_list + threadIdx.x;
-    uint32_t total = 0;
-    if (active) total = build_list<DIM, 1>(P, cs, T, list, tpb);
-    else list[0] = make_uint2(kListEndStart, kListEndEnd);
-
-    real al = 0, cl = 0, g1 = 0, g2 = 0, g3 = 0;
-    auto fetch = [&](uint32_t k) {
-        if constexpr (kPacked) {
-            const uint4 r = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(arec) + k);
-            return ACand<real>{r.x, r.y, 0u, (real)bitsf(r.z), (real)bitsf(r.w)};
-        } else {
-            k /= kRecBytes;
-            return ACand<real>{px[k], py[k], (DIM == 3) ? pz[k] : 0u, X[k], u_s[k]};
-        }
+struct AdjTerm {
+    real H2, invHu, a0, a1, gam, spd, vx, vy, vz;
+    struct Sums {
+        real al = 0, cl = 0, g1 = 0, g2 = 0, g3 = 0;
     };
-    // branch-free: outside the support (and at r2 = 0, where 1/r is infinite)
-    // f and p are replaced by 0, so every term is exactly 0
-    auto eval = [&](const ACand<real>& c, bool keep) {
-        const real dx = (real)(int32_t)(T.ux - c.x);
-        const real dy = (real)(int32_t)(T.uy - c.y);
-        const real dz = (DIM == 3) ? (real)(int32_t)(T.uz - c.z) : (real)0;
+    __device__ __forceinline__ AdjTerm(const PlumeDev& P, double speed)
+        : H2(h2_of<real>(P)), invHu((real)P.invHu), a0((real)P.a0), a1((real)P.a1), gam((real)(DIM + 2)),
+          spd((real)speed), vx((real)P.ehat[0]), vy((real)P.ehat[1]), vz((real)P.ehat[2]) {}
+    // the target t and a candidate c at the separation (dx, dy, dz) = x_t - x_c.
+    // Branch-free: outside the support (and at r2 = 0, where 1/r is infinite) f
+    // and p are replaced by 0, so every term is exactly 0
+    __device__ __forceinline__ void operator()(real dx, real dy, real dz, const ACand<real>& t, const ACand<real>& c,
+                                               bool keep, Sums& s) const {
         real r2 = dx * dx;
         r2 = fmar(dy, dy, r2);
         if (DIM == 3) r2 = fmar(dz, dz, r2);
@@ -293,43 +272,147 @@ __global__ __launch_bounds__(256) void k_adjoint(const PlumeDev* __restrict__ pl
         f = in ? f : (real)0;
         p = in ? p : (real)0;
         const real A = fmar(a1, p, a0);
-        const real dCf = (Xi - c.X) * f;
-        al = fmar(A * f, ui - c.u, al);
-        if (AMODE == kAdjHalf) cl = fmar(A, dCf, cl);
-        g1 = fmar(spd * fmar(gam, p, (real)-1), dCf, g1);
-        g2 = fmar(spd * fmar(-gam, p, gam - (real)(DIM - 1)), dCf, g2);
-        g3 = fmar(gam - (real)DIM, dCf, g3);
-    };
-    walk_stream<4>(list, tpb, total, i, fetch, eval);
-
-    double mult = 0.0;  // the gradient's multiplier of this particle
-    if (active) {
-        const double sd = P.dt * P.vphi;
-        if (AMODE == kAdjHalf) {
-            const real h = (real)(0.5 * sd);
-            const real mu = fmar(h, al, li), xh = fmar(h, cl, Xi);
-            lam_out[i] = mu;
-            xh_out[i] = xh;
-            if constexpr (kPacked) arec_out[i] = make_uint4(T.ux, T.uy, fbits(xh), fbits(mu));
-            mult = 0.5 * sd * (double)al;  // mu - lambda
-        } else {
-            const real ln = fmar((real)sd, al, li);
-            lam_out[i] = ln;
-            if constexpr (kPacked)
-                if (Xnext) arec_out[i] = make_uint4(T.ux, T.uy, fbits(Xnext[i]), fbits(ln));
-            mult = (double)li;
-        }
+        const real dCf = (t.X - c.X) * f;
+        s.al = fmar(A * f, t.u - c.u, s.al);
+        if (AMODE == kAdjHalf) s.cl = fmar(A, dCf, s.cl);
+        s.g1 = fmar(spd * fmar(gam, p, (real)-1), dCf, s.g1);
+        s.g2 = fmar(spd * fmar(-gam, p, gam - (real)(DIM - 1)), dCf, s.g2);
+        s.g3 = fmar(gam - (real)DIM, dCf, s.g3);
     }
-    // per-workgroup gradient partials, accumulated over the steps in FP64
-    const double s = P.dt * P.vphi;
-    const double c1 = block_sum(active ? s * mult * (double)g1 : 0.0, lds);
-    const double c2 = block_sum(active ? s * mult * (double)g2 : 0.0, lds);
-    const double c3 = block_sum(active ? s * mult * (double)g3 : 0.0, lds);
+};
+
+template <int DIM, typename real>
+__device__ __forceinline__ ACand<real> adj_part(const AdjLaunch& a, uint32_t k) {
+    if constexpr (ARec<DIM, real>::kPacked) {
+        const uint4 r = a.arec[k];
+        return ACand<real>{r.x, r.y, 0u, (real)bitsf(r.z), (real)bitsf(r.w)};
+    } else {
+        return ACand<real>{a.S.pos[0][k], a.S.pos[1][k], (DIM == 3) ? a.S.pos[2][k] : 0u,
+                           static_cast<const real*>(a.X)[k], static_cast<const real*>(a.u)[k]};
+    }
+}
+
+// The end of target i of a pass; returns its multiplier of the gradient sums.
+template <int DIM, typename real, int AMODE, typename Sums>
+__device__ __forceinline__ double adj_finish(const AdjLaunch& a, const PlumeDev& P, const ACand<real>& t, uint32_t i,
+                                             const Sums& s) {
+    constexpr bool kPacked = ARec<DIM, real>::kPacked;
+    const double sd = P.dt * P.vphi;
+    const real li = static_cast<const real*>(a.lam)[i];
+    if (AMODE == kAdjHalf) {
+        const real h = (real)(0.5 * sd);
+        const real mu = fmar(h, s.al, li), xh = fmar(h, s.cl, t.X);
+        static_cast<real*>(a.lam_out)[i] = mu;
+        static_cast<real*>(a.xh_out)[i] = xh;
+        if constexpr (kPacked) a.arec_out[i] = make_uint4(t.x, t.y, fbits(xh), fbits(mu));
+        return 0.5 * sd * (double)s.al;  // mu - lambda
+    }
+    const real ln = fmar((real)sd, s.al, li);
+    static_cast<real*>(a.lam_out)[i] = ln;
+    if constexpr (kPacked)
+        if (a.Xnext) a.arec_out[i] = make_uint4(t.x, t.y, fbits(static_cast<const real*>(a.Xnext)[i]), fbits(ln));
+    return (double)li;
+}
+
+// per-workgroup gradient partials, accumulated over the steps in FP64
+__device__ __forceinline__ void adj_partials(double c1, double c2, double c3, double* lds, double* gpart) {
+    c1 = block_sum(c1, lds);
+    c2 = block_sum(c2, lds);
+    c3 = block_sum(c3, lds);
     if (threadIdx.x == 0) {
         gpart[3 * blockIdx.x + 0] += c1;
         gpart[3 * blockIdx.x + 1] += c2;
         gpart[3 * blockIdx.x + 2] += c3;
     }
+}
+
+// over the row windows, one lane per target
+template <int DIM, typename real, int KERN, int AMODE>
+__global__ __launch_bounds__(256) void k_adjoint(AdjLaunch a, const PlumeDev* __restrict__ plumes,
+                                                const TileDev* __restrict__ tiles) {
+    extern __shared__ uint2 lds_list[];
+    __shared__ double lds[kTile / kWave];
+    const uint32_t tpb = blockDim.x, subs = kTile / tpb;
+    const TileDev t = tiles[blockIdx.x / subs];
+    const uint32_t i0 = t.start + (blockIdx.x % subs) * tpb;
+    if (i0 >= t.end) return;  // whole workgroup: ragged last tile
+    const uint32_t i1 = min(t.end, i0 + tpb);
+    const PlumeDev P = plumes[t.plume];
+    const bool active = i0 + threadIdx.x < i1;
+    const uint32_t i = active ? i0 + threadIdx.x : i0;
+    const ACand<real> self = adj_part<DIM, real>(a, i);
+    const Target T = make_target<DIM>(P, self.x, self.y, self.z);
+    uint2* list = lds_list + threadIdx.x;
+    uint32_t total = 0;
+    if (active) total = build_list<DIM, 1>(P, a.cs, T, list, tpb);
+    else list[0] = make_uint2(kListEndStart, kListEndEnd);
+    const AdjTerm<DIM, real, KERN, AMODE> term(P, a.speed);
+    typename AdjTerm<DIM, real, KERN, AMODE>::Sums s;
+    walk_stream<4>(
+        list, tpb, total, i, [&](uint32_t k) { return adj_part<DIM, real>(a, k / kRecBytes); },
+        [&](const ACand<real>& c, bool keep) {
+            term((real)(int32_t)(T.ux - c.x), (real)(int32_t)(T.uy - c.y),
+                 (DIM == 3) ? (real)(int32_t)(T.uz - c.z) : (real)0, self, c, keep, s);
+        });
+    double m = 0.0;
+    if (active) m = P.dt * P.vphi * adj_finish<DIM, real, AMODE>(a, P, self, i, s);
+    adj_partials(m * (double)s.g1, m * (double)s.g2, m * (double)s.g3, lds, a.gpart);
+}
+
+// over the neighbour lists of the launch shape: blockDim.x / G * T targets of a
+// tile a workgroup.  256^2 plume (26 neighbours, four lanes a target): 14.9 us a
+// pass over the windows with one lane a target, 7.2 us here.
+template <int DIM, typename real, int KERN, int AMODE, int G, int T>
+__global__ __launch_bounds__(256) void k_adjoint_list(AdjLaunch a, const PlumeDev* __restrict__ plumes,
+                                                     const TileDev* __restrict__ tiles) {
+    __shared__ double lds[kTile / kWave];
+    constexpr uint32_t kWaves = kTile / (kWave / G * T);
+    const uint32_t wv = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+    const TileDev t = tiles[wv / kWaves];
+    const uint32_t i0 = t.start + (wv % kWaves) * (kTile / kWaves);
+    const PlumeDev P = plumes[t.plume];
+    double c1 = 0.0, c2 = 0.0, c3 = 0.0;
+    if (i0 < t.end) {  // the wavefront has targets (ragged last tile)
+        const ListTargets<G, T> q(i0, t.end);
+        const AdjTerm<DIM, real, KERN, AMODE> term(P, a.speed);
+        typename AdjTerm<DIM, real, KERN, AMODE>::Sums sA, sB;
+        walk_lists<DIM, G, T>(
+            a.list, a.waves, a.lplumes[t.plume], P, i0, q,
+            [&](uint32_t k) { return adj_part<DIM, real>(a, k / kRecBytes); },
+            [&](uint32_t k0, uint32_t k1, bool second, auto&& walk) {
+                const ACand<real> T0 = adj_part<DIM, real>(a, k0), T1 = adj_part<DIM, real>(a, k1);
+                typename AdjTerm<DIM, real, KERN, AMODE>::Sums s0, s1;
+                walk([&](const ACand<real>& c, bool keep) {
+                    // a slot past the end of the list holds target k0: no term for it
+                    term((real)(int32_t)(T0.x - c.x), (real)(int32_t)(T0.y - c.y),
+                         (DIM == 3) ? (real)(int32_t)(T0.z - c.z) : (real)0, T0, c, true, s0);
+                    if (T == 2)
+                        term((real)(int32_t)(T1.x - c.x), (real)(int32_t)(T1.y - c.y),
+                             (DIM == 3) ? (real)(int32_t)(T1.z - c.z) : (real)0, T1, c, keep, s1);
+                });
+                if (second) {
+                    sB = s0;
+                } else {
+                    sA = s0;
+                    sB = s1;
+                }
+            });
+        auto end = [&](auto& s, bool mine, uint32_t i) {
+            s.al = group_sum<G>(s.al);
+            if (AMODE == kAdjHalf) s.cl = group_sum<G>(s.cl);
+            s.g1 = group_sum<G>(s.g1);
+            s.g2 = group_sum<G>(s.g2);
+            s.g3 = group_sum<G>(s.g3);
+            if (!mine) return;
+            const double m = P.dt * P.vphi * adj_finish<DIM, real, AMODE>(a, P, adj_part<DIM, real>(a, i), i, s);
+            c1 += m * (double)s.g1;
+            c2 += m * (double)s.g2;
+            c3 += m * (double)s.g3;
+        };
+        end(sA, q.lj == 0 && q.actA, q.iA);
+        if (T == 2) end(sB, q.lj == (G == 1 ? 0u : 1u) && q.actB, q.iB);
+    }
+    adj_partials(c1, c2, c3, lds, a.gpart);
 }
 
 __global__ __launch_bounds__(256) void k_grad_reduce(const double* __restrict__ gpart, uint32_t nb,
@@ -764,14 +847,60 @@ int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, c
     fin.C = state(nsteps);
     if ((rc = misfit_and_seed(c, L, fin, d_xs, ns, d_obs, L.lam[0]))) return rc;
 
-    AdjConst ac{};
+    AdjLaunch base{};
+    base.plumes = c->plumes;
+    base.tiles = c->tiles;
+    base.ntiles = pl.ntiles;
+    base.S = c->S;
+    base.cs = c->cell_start;
+    base.gpart = L.gpart;
     {
         const PlumeDev& P = pl.plumes[0];
         double sp = 0;
         for (int k = 0; k < pl.dim; ++k) sp += P.vel[k] * P.vel[k];
-        ac.speed = std::sqrt(sp);
+        base.speed = std::sqrt(sp);
     }
-    const dim3 g((N + 255) / 256), b(256), ag(pl.ntiles * asubs), abk(ab);
+    // the lists of the forward run, if the plume has them: workgroups of 256
+    // threads, or of 64 where those would not fill the chip; at most
+    // kAdjMaxSubs of them a tile
+    const PairLaunch fwd = pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, nullptr, nullptr);
+    base.list = fwd.list;
+    base.lplumes = fwd.lplumes;
+    base.waves = fwd.waves;
+    const uint32_t lwaves = (uint32_t)(kTile / 64) * (uint32_t)fwd.lanes / (uint32_t)fwd.targets;  // per tile
+    const uint32_t lsubs = std::min(lwaves, kAdjMaxSubs), lblock = 64 * (lwaves / lsubs);
+    const uint32_t parts = pl.ntiles * (fwd.list ? lsubs : asubs);
+    auto run = [&](int mode, const void* u, const void* lam, const void* X, const uint4* rec, void* out, void* xh,
+                   const void* next, uint4* rec_out) -> int {
+        AdjLaunch a = base;
+        a.u = u;
+        a.lam = lam;
+        a.X = X;
+        a.arec = rec;
+        a.lam_out = out;
+        a.xh_out = xh;
+        a.Xnext = next;
+        a.arec_out = rec_out;
+#define SHAPE(D, R, KK, M)                                                                                       \
+    do {                                                                                                         \
+        auto kern = k_adjoint_list<D, R, KK, M, 1, 1>;                                                           \
+        if (fwd.targets == 2) kern = fwd.lanes == 4 ? k_adjoint_list<D, R, KK, M, 4, 2> : k_adjoint_list<D, R, KK, M, 1, 2>; \
+        else if (fwd.lanes == 4) kern = k_adjoint_list<D, R, KK, M, 4, 1>;                                       \
+        else if (fwd.lanes == 2) kern = k_adjoint_list<D, R, KK, M, 2, 1>;                                       \
+        if (a.list) hipLaunchKernelGGL(kern, dim3(parts), dim3(lblock), 0, st, a, a.plumes, a.tiles);            \
+        else hipLaunchKernelGGL((k_adjoint<D, R, KK, M>), dim3(parts), dim3(ab), (uint32_t)ashm, st, a, a.plumes, a.tiles); \
+    } while (0)
+#define CALL(D, R, KK)                                  \
+    if (mode == kAdjEuler) SHAPE(D, R, KK, kAdjEuler);  \
+    else if (mode == kAdjHalf) SHAPE(D, R, KK, kAdjHalf); \
+    else SHAPE(D, R, KK, kAdjFull)
+        ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
+#undef CALL
+#undef SHAPE
+        HIPCHK(hipGetLastError());
+        return ADE_OK;
+    };
+    const dim3 g((N + 255) / 256), b(256);
     int li = 0, ri = 0;
     for (int64_t n = nsteps - 1; n >= 0; --n) {
         const bool top = n == nsteps - 1;
@@ -789,30 +918,21 @@ int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, c
             HIPCHK(hipGetLastError());
         }
         const void* next = (n > 0 && (all || n % K != 0)) ? state(n - 1) : nullptr;
-#define LAUNCH(D, R, KK, MODE, U, X, REC, OUT, XH, NEXT, RECOUT)                                             \
-    hipLaunchKernelGGL((k_adjoint<D, R, KK, MODE>), ag, abk, (uint32_t)ashm, st, c->plumes, c->tiles, c->S,   \
-                       c->cell_start, (const R*)(U), (const R*)L.lam[li], (const R*)(X), (const uint4*)(REC), \
-                       (R*)(OUT), (R*)(XH), (const R*)(NEXT), (uint4*)(RECOUT), ac, L.gpart)
         if (pc) {
-#define CALL(D, R, KK)                                                                                    \
-    LAUNCH(D, R, KK, kAdjHalf, L.lam[li], state(n), arecs[0], L.mu_s, L.ch_s, nullptr, arecs[1]);            \
-    LAUNCH(D, R, KK, kAdjFull, L.mu_s, L.ch_s, arecs[1], L.lam[1 - li], nullptr, next, arecs[0])
-            ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
-#undef CALL
+            if ((rc = run(kAdjHalf, L.lam[li], L.lam[li], state(n), arecs[0], L.mu_s, L.ch_s, nullptr, arecs[1])) ||
+                (rc = run(kAdjFull, L.mu_s, L.lam[li], L.ch_s, arecs[1], L.lam[1 - li], nullptr, next, arecs[0])))
+                return rc;
         } else {
-#define CALL(D, R, KK) \
-    LAUNCH(D, R, KK, kAdjEuler, L.lam[li], state(n), arecs[ri], L.lam[1 - li], nullptr, next, arecs[1 - ri])
-            ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
-#undef CALL
+            if ((rc = run(kAdjEuler, L.lam[li], L.lam[li], state(n), arecs[ri], L.lam[1 - li], nullptr, next,
+                          arecs[1 - ri])))
+                return rc;
             ri = 1 - ri;
         }
-#undef LAUNCH
-        HIPCHK(hipGetLastError());
         li = 1 - li;
     }
     // leave the context at step nsteps (the forward run counted its steps)
     HIPCHK(launch_set_state(pl.dim, pl.real_bytes, c->S, state(nsteps), N, st));
-    return reduce_to_host(c, L, pl.ntiles * asubs, h_J, h_grad);
+    return reduce_to_host(c, L, parts, h_J, h_grad);
 }
 
 // The adjoint of a velocity field over snapshots of the whole state.

@@ -35,32 +35,12 @@
 // kernels then take two passes.
 #include <hip/hip_ext.h>
 
+#include "ade_list.h"
 #include "ade_pair.h"
 
 namespace ade {
 
 namespace {
-
-// rows before the entries: the counts, which only a second target needs
-template <int T>
-constexpr uint32_t kCountRows = T == 2 ? 1u : 0u;
-
-template <int DIM>
-struct Entry {
-    static constexpr int kPerRow = DIM == 2 ? 2 : 1;
-};
-
-// rows of nb batches
-template <int DIM>
-__device__ __forceinline__ uint32_t batch_rows(uint32_t nb) {
-    return nb * (kListBatch / Entry<DIM>::kPerRow);
-}
-
-// a lane's share of its group's m entries
-template <int G>
-__device__ __forceinline__ uint32_t lane_share(uint32_t m, uint32_t lj) {
-    return m > lj ? (m - lj + G - 1) / G : 0u;
-}
 
 __device__ __forceinline__ uint32_t wave_max(uint32_t v) {
 #pragma unroll
@@ -261,153 +241,57 @@ __global__ __launch_bounds__(64) void k_list(ListBuild a, const PlumeDev* __rest
 template <int DIM, typename real, int KERN, int MODE, int G, int T, bool ZC>
 __device__ __forceinline__ void list_item(const PairLaunch& a, const PlumeDev* __restrict__ plumes,
                                           const TileDev* __restrict__ tiles, uint32_t w) {
-    constexpr int B = kListBatch, kPer = Entry<DIM>::kPerRow, RB = B / kPer;
-    constexpr uint32_t kGroups = kWave / G, kTargets = kGroups * T, kWaves = kTile / kTargets;
+    constexpr uint32_t kWaves = kTile / (kWave / G * T);
     // the wavefront's number among all: a workgroup holds a whole number of them
     const uint32_t wv = __builtin_amdgcn_readfirstlane(w * ((uint32_t)a.block / kWave) + threadIdx.x / kWave);
     const TileDev t = tiles[wv / kWaves];
-    const uint32_t i0 = t.start + (wv % kWaves) * kTargets;
+    const uint32_t i0 = t.start + (wv % kWaves) * (kTile / kWaves);
     if (i0 >= t.end) return;  // the whole wavefront: ragged last tile
     const PlumeDev P = plumes[t.plume];
     const ListPlume lp = a.lplumes[t.plume];
     if (lp.rows == 0u) return;  // a plume without lists: its row windows are walked
-    const uint32_t wave = (i0 - P.poff) / kTargets;
-    const uint32_t lane = threadIdx.x & (kWave - 1), g = lane / G, lj = lane % G;
-    const uint32_t* __restrict__ rows = a.list + ((size_t)lp.row0 + (size_t)wave * lp.rows) * kWave;
-    const ListWave head = a.waves[lp.wave0 + wave];
-    const uint32_t words = T == 2 ? rows[lane] : 0u;
-
-    const uint32_t ia = i0 + T * g, ib = ia + T - 1;
-    const bool actA = ia < t.end, actB = T == 2 && ib < t.end;
-    const uint32_t iA = actA ? ia : i0, iB = actB ? ib : iA;
+    const ListTargets<G, T> q(i0, t.end);
     const uint32_t* __restrict__ px = a.spos[0];
     const uint32_t* __restrict__ py = a.spos[1];
     const uint32_t* __restrict__ pz = a.spos[2];
     const real* __restrict__ Cp = static_cast<const real*>(a.Cpair);
     const uint4* __restrict__ rec = a.rec;
     constexpr bool kRec = Rec<DIM, real>::kStageable;
-    // 2D: entries count from the wavefront's base; a window past the end of
-    // the plume goes on at its start
-    const uint32_t base = head.base;
-    const bool wraps = DIM == 2 && P.n > 65536u && base + 65536u > P.n;
-    const char* rec0 = reinterpret_cast<const char*>(rec) + (DIM == 2 ? (size_t)P.poff * kRecBytes : 0);
-
-    // a target, from its record where there is one
-    auto target = [&](uint32_t k) {
+    // a particle, from its record where there is one
+    auto part = [&](uint32_t k) {
         if constexpr (kRec) return unpack<DIM, real>(rec[k]);
         else return Cand<real>{px[k], py[k], (DIM == 3) ? pz[k] : 0u, Cp[k]};
     };
+    auto fetch = [&](uint32_t k) {  // 32-bit byte offset from a uniform base
+        if constexpr (kRec) return unpack<DIM, real>(*reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(rec) + k));
+        else return part(k / kRecBytes);
+    };
     const PairTerm<DIM, real, KERN, ZC> term = make_term<DIM, real, KERN, ZC>(P);
-    const bool merged = T == 1 || !(head.nb & ListWave::kTwoPasses);
     real accA = (real)0, accB = (real)0;
-    uint32_t row = kCountRows<T>;
-    const int npass = merged ? 1 : 2;
-    for (int pass = 0; pass < npass; ++pass) {
-        const bool second = pass == 1;
-        const uint32_t k0 = second ? iB : iA, k1 = merged ? iB : k0;
-        const Cand<real> T0 = target(k0), T1 = target(k1);
+    walk_lists<DIM, G, T>(a.list, a.waves, lp, P, i0, q, fetch, [&](uint32_t k0, uint32_t k1, bool second, auto&& walk) {
+        const Cand<real> T0 = part(k0), T1 = part(k1);
         const real bx = (real)(int32_t)(T1.x - T0.x);
         const real by = (real)(int32_t)(T1.y - T0.y);
         const real bz = (DIM == 3) ? (real)(int32_t)(T1.z - T0.z) : (real)0;
-        const uint32_t own = lane_share<G>(second ? words >> 16 : words & 0xffffu, lj);
-        const uint32_t nb = second ? head.nb2 : head.nb & ~ListWave::kTwoPasses;
-        // batches in which every lane has entries of its own: the second
-        // target needs no end-of-list test there (T = 1 needs none at all)
-        const uint32_t nfull = T == 1 ? nb : second ? head.full >> 16 : head.full & 0xffffu;
         real acc0 = (real)0, acc1 = (real)0;
-        const uint32_t* __restrict__ L = rows + (size_t)row * kWave;  // uniform; the lane is added to the load
-        auto walk = [&](auto wrap) {
-            constexpr bool kWrap = decltype(wrap)::value;
-            const char* recb = rec0 + (DIM == 2 && !kWrap ? (size_t)base * kRecBytes : 0);
-            uint32_t e0[RB], e1[RB];
-            Cand<real> c0[B], c1[B];
-            auto load = [&](uint32_t(&e)[RB], uint32_t it) {
-#pragma unroll
-                for (int r = 0; r < RB; ++r) e[r] = L[(it * RB + r) * kWave + lane];
-            };
-            auto fetch = [&](Cand<real>(&c)[B], const uint32_t(&e)[RB]) {
-#pragma unroll
-                for (int q = 0; q < B; ++q) {
-                    uint32_t k;
-                    if (DIM == 2) {
-                        const uint32_t word = e[q / kPer];
-                        if (kWrap) {
-                            uint32_t i = ((q & 1) ? word >> 16 : word & 0xffffu) + base;
-                            i = min(i, i - P.n);
-                            k = i * kRecBytes;
-                        } else {
-                            k = (q & 1) ? (word >> 12) & 0xffff0u : (word << 4) & 0xffff0u;
-                        }
-                    } else {
-                        k = e[q];
-                    }
-                    if constexpr (kRec) {
-                        c[q] = unpack<DIM, real>(*reinterpret_cast<const uint4*>(recb + k));
-                    } else {
-                        k /= kRecBytes;
-                        c[q] = Cand<real>{px[k], py[k], (DIM == 3) ? pz[k] : 0u, Cp[k]};
-                    }
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            auto one = [&](const Cand<real>& c, bool keep) {
-                const real dx = (real)(int32_t)(T0.x - c.x);
-                const real dy = (real)(int32_t)(T0.y - c.y);
-                const real dz = (DIM == 3) ? (real)(int32_t)(T0.z - c.z) : (real)0;
-                term.sep(dx, dy, dz, T0.C, c.C, true, acc0);
-                if (T == 2) term.sep(dx + bx, dy + by, dz + bz, T1.C, c.C, keep, acc1);
-            };
-            auto eval = [&](const Cand<real>(&c)[B], uint32_t it) {
-                if (it < nfull) {
-#pragma unroll
-                    for (int q = 0; q < B; ++q) one(c[q], true);
-                } else {
-#pragma unroll
-                    for (int q = 0; q < B; ++q) one(c[q], it * B + q < own);
-                }
-            };
-            // entries two batches ahead of their evaluation, records one (the
-            // lists end with room for the entries read past the last batch)
-            load(e0, 0u);
-            load(e1, 1u);
-            fetch(c0, e0);
-            load(e0, 2u);
-            for (uint32_t it = 1;; it += 2) {
-                if (it >= nb) {
-                    eval(c0, it - 1);
-                    break;
-                }
-                fetch(c1, e1);
-                load(e1, it + 2);
-                eval(c0, it - 1);
-                if (it + 1 >= nb) {
-                    eval(c1, it);
-                    break;
-                }
-                fetch(c0, e0);
-                load(e0, it + 3);
-                eval(c1, it);
-            }
-        };
-        if (nb > 0) {
-            if (DIM == 2 && wraps) walk(std::integral_constant<bool, true>{});
-            else walk(std::integral_constant<bool, false>{});
-        }
-        row += batch_rows<DIM>(nb);
+        walk([&](const Cand<real>& c, bool keep) {
+            const real dx = (real)(int32_t)(T0.x - c.x);
+            const real dy = (real)(int32_t)(T0.y - c.y);
+            const real dz = (DIM == 3) ? (real)(int32_t)(T0.z - c.z) : (real)0;
+            term.sep(dx, dy, dz, T0.C, c.C, true, acc0);
+            if (T == 2) term.sep(dx + bx, dy + by, dz + bz, T1.C, c.C, keep, acc1);
+        });
         if (second) {
             accB = acc0;
         } else {
             accA = acc0;
             accB = acc1;
         }
-    }
-    // the lanes of a group combine their sums (fixed order: deterministic)
-    if (G >= 2) accA += __shfl_xor(accA, 1, kWave);
-    if (G >= 4) accA += __shfl_xor(accA, 2, kWave);
-    if (T == 2 && G >= 2) accB += __shfl_xor(accB, 1, kWave);
-    if (T == 2 && G >= 4) accB += __shfl_xor(accB, 2, kWave);
-    if (lj == 0 && actA) finish_target<DIM, real, KERN, MODE>(a, P, target(iA), iA, accA);
-    if (T == 2 && lj == (G == 1 ? 0u : 1u) && actB) finish_target<DIM, real, KERN, MODE>(a, P, target(iB), iB, accB);
+    });
+    accA = group_sum<G>(accA);
+    if (T == 2) accB = group_sum<G>(accB);
+    if (q.lj == 0 && q.actA) finish_target<DIM, real, KERN, MODE>(a, P, part(q.iA), q.iA, accA);
+    if (T == 2 && q.lj == (G == 1 ? 0u : 1u) && q.actB) finish_target<DIM, real, KERN, MODE>(a, P, part(q.iB), q.iB, accB);
 }
 
 template <int DIM, typename real, int KERN, int MODE, int G, int T, bool ZC>
