@@ -12,7 +12,15 @@ __device__ __forceinline__ double fmar(double a, double b, double c) { return __
 // r2 >= 1 in grid units, so the hardware reciprocal square root needs no
 // denormal scaling
 __device__ __forceinline__ float rsqrt_r(float x) { return __builtin_amdgcn_rsqf(x); }
-__device__ __forceinline__ double rsqrt_r(double x) { return 1.0 / sqrt(x); }
+// FP64: the hardware estimate y (relative error e / 2 of order 2^-28) and one
+// step of the series x^(-1/2) = y (1 - e)^(-1/2) = y (1 + e/2 + 3 e^2/8 + ...),
+// e = 1 - x y^2, whose next term is below 2^-80: six instructions where 1 /
+// sqrt(x) takes about thirty (x = 0 gives NaN, which every caller selects away)
+__device__ __forceinline__ double rsqrt_r(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    const double e = __builtin_fma(-(x * y), y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
 
 // x clamped to [0, 1] (NaN to 0): for FP32 the clamp bit of the instruction
 // that forms x

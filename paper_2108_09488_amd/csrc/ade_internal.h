@@ -159,6 +159,7 @@ struct PairLaunch {
     const uint32_t* list;
     const ListPlume* lplumes;
     const ListWave* waves;
+    const uint4* list_pos;  // 3D FP64: positions as 16-byte records
     hipEvent_t ev0, ev1;    // if set: events stamped at the kernel's start and end
 };
 
@@ -188,6 +189,7 @@ struct ListBuild {
     const uint32_t* cell_start;
     uint32_t* list;
     ListWave* waves;
+    uint4* pos;             // 3D FP64: positions as 16-byte records, written with the lists
     uint32_t* over;         // per plume: set when its lists do not fit
 };
 hipError_t launch_list(int dim, int real_bytes, const ListBuild& a, hipStream_t s);

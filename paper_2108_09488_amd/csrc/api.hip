@@ -138,7 +138,8 @@ ListPlan list_plan(const Plan& pl, int lanes, int targets) {
     }
     if (L.rows == 0) return L;
     auto part = [](size_t n) { return (n * 4 + 255) & ~size_t(255); };
-    L.bytes = part((L.rows + kListSlack) * 64) + part(L.waves * 4);
+    L.bytes = part((L.rows + kListSlack) * 64) + part(L.waves * 4) +
+              (pl.dim == 3 && pl.real_bytes == 8 ? part((size_t)pl.N * 4) : 0);
     if (L.bytes > kListBudget) L.bytes = 0;
     return L;
 }
@@ -627,12 +628,14 @@ static int take_events(ade_ctx* c, hipEvent_t& e0, hipEvent_t& e1) {
 struct ListArrays {
     uint32_t* list;
     ListWave* waves;
+    uint4* pos;
 };
 static ListArrays list_arrays(const ade_ctx* c, const ListPlan& L) {
     Bump b(c->list_mem);
     ListArrays q;
     q.list = b.take<uint32_t>((L.rows + kListSlack) * 64);
     q.waves = b.take<ListWave>(L.waves);
+    q.pos = c->plan.dim == 3 && c->plan.real_bytes == 8 ? b.take<uint4>((size_t)c->plan.N) : nullptr;
     return q;
 }
 static int shape_of(const ade_tuning& t) { return 4 * t.lanes + targets_of(t); }
@@ -688,6 +691,7 @@ static int enqueue_lists(ade_ctx* c) {
     a.cell_start = c->cell_start;
     a.list = q.list;
     a.waves = q.waves;
+    a.pos = q.pos;
     a.over = c->flags + 1;
     HIPCHK(launch_list(pl.dim, pl.real_bytes, a, c->stream));
     return ADE_OK;
@@ -774,6 +778,7 @@ PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void
         a.list = q.list;
         a.lplumes = c->lplumes;
         a.waves = q.waves;
+        a.list_pos = q.pos;
     }
     a.plumes = c->plumes;
     a.tiles = c->pair_tiles;

@@ -231,6 +231,11 @@ __global__ __launch_bounds__(64) void k_list(ListBuild a, const PlumeDev* __rest
         }
     }
     if (T == 2) out[lane] = words;
+    if (!Rec<DIM, real>::kStageable && lj == 0) {  // 3D FP64: the targets' position records
+        auto pack = [&](uint32_t k) { a.pos[k] = make_uint4(a.spos[0][k], a.spos[1][k], a.spos[2][k], 0u); };
+        if (actA) pack(iA);
+        if (T == 2 && actB) pack(iB);
+    }
     if (lane == 0) a.waves[lp.wave0 + wave] = head;
     if (bad) a.over[t.plume] = 1u;
 }
@@ -251,21 +256,16 @@ __device__ __forceinline__ void list_item(const PairLaunch& a, const PlumeDev* _
     const ListPlume lp = a.lplumes[t.plume];
     if (lp.rows == 0u) return;  // a plume without lists: its row windows are walked
     const ListTargets<G, T> q(i0, t.end);
-    const uint32_t* __restrict__ px = a.spos[0];
-    const uint32_t* __restrict__ py = a.spos[1];
-    const uint32_t* __restrict__ pz = a.spos[2];
     const real* __restrict__ Cp = static_cast<const real*>(a.Cpair);
-    const uint4* __restrict__ rec = a.rec;
     constexpr bool kRec = Rec<DIM, real>::kStageable;
-    // a particle, from its record where there is one
-    auto part = [&](uint32_t k) {
-        if constexpr (kRec) return unpack<DIM, real>(rec[k]);
-        else return Cand<real>{px[k], py[k], (DIM == 3) ? pz[k] : 0u, Cp[k]};
-    };
+    const uint4* __restrict__ rec = kRec ? a.rec : a.list_pos;
+    // a particle, from its record (3D FP64: its position record and its C)
     auto fetch = [&](uint32_t k) {  // 32-bit byte offset from a uniform base
-        if constexpr (kRec) return unpack<DIM, real>(*reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(rec) + k));
-        else return part(k / kRecBytes);
+        const uint4 r = *reinterpret_cast<const uint4*>(reinterpret_cast<const char*>(rec) + k);
+        if constexpr (kRec) return unpack<DIM, real>(r);
+        else return Cand<real>{r.x, r.y, r.z, *reinterpret_cast<const real*>(reinterpret_cast<const char*>(Cp) + k / 2u)};
     };
+    auto part = [&](uint32_t k) { return fetch(k * kRecBytes); };
     const PairTerm<DIM, real, KERN, ZC> term = make_term<DIM, real, KERN, ZC>(P);
     real accA = (real)0, accB = (real)0;
     walk_lists<DIM, G, T>(a.list, a.waves, lp, P, i0, q, fetch, [&](uint32_t k0, uint32_t k1, bool second, auto&& walk) {
