@@ -44,14 +44,16 @@
 
 namespace ade {
 
-// Kernel shape of Eq. (7) without its normalisation, as a function of q = r / H.
+// Kernel shape of Eq. (7) without its normalisation at distance r, as two
+// factors: (1 - q)^6 and (1 + 6 q + 35/3 q^2) for C4, (1 - q)^4 and (1 + 4 q) for
+// C2, q = r / H.
 template <typename real, int KERN>
-__device__ __forceinline__ real kernel_shape(real q) {
-    real omq = (real)1 - q;
-    omq = pos_unit(omq);
+__device__ __forceinline__ void kernel_factors(real r, real invHu, real& a, real& b) {
+    const real q = r * invHu;
+    const real omq = pos_unit(fmar(-r, invHu, (real)1));
     const real o2 = omq * omq;
-    if (KERN == 4) return o2 * o2 * o2 * fmar(q, fmar((real)(35.0 / 3.0), q, (real)6), (real)1);
-    return o2 * o2 * fmar((real)4, q, (real)1);
+    a = (KERN == 4) ? o2 * (o2 * o2) : o2 * o2;
+    b = (KERN == 4) ? fmar(q, fmar((real)(35.0 / 3.0), q, (real)6), (real)1) : fmar((real)4, q, (real)1);
 }
 
 template <int DIM>
@@ -62,15 +64,23 @@ __device__ __forceinline__ uint32_t to_fixed(double x, double L) {
 // ---------------------------------------------------------------------------
 // sensors
 // ---------------------------------------------------------------------------
+// One wavefront per sensor: its lanes list the row windows together, evaluate 64
+// candidates at a time, and add the terms up in the order of the windows, one
+// after the other (a lane per sensor waited for its windows' records in turn: 27
+// against 8 us for 64 sensors; the sums are the same).
 template <int DIM, typename real, int KERN>
 __global__ __launch_bounds__(256) void k_sensor_fwd(const PlumeDev* __restrict__ plumes,
                                                    const double* __restrict__ xs, int ns,
                                                    StateArrays S, const FrameStep* __restrict__ frame,
                                                    const uint32_t* __restrict__ cs,
                                                    real* __restrict__ pred, real* __restrict__ den) {
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= ns) return;
+    // the windows of a wavefront's sensor: first record and records before it
+    __shared__ uint2 win[256 / kWave][2 * kMaxRowOffsets + 1];
+    const int s = (int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+    if (s >= ns) return;  // the whole wavefront
+    uint2* w = win[threadIdx.x / kWave];
     const PlumeDev P = plumes[0];
+    const uint32_t lane = threadIdx.x & (kWave - 1);
     uint32_t u[3] = {0u, 0u, 0u};
     for (int c = 0; c < DIM; ++c) u[c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L) - frame_shift(P, frame, c);
     const Target T = make_target<DIM>(P, u[0], u[1], u[2]);
@@ -80,26 +90,49 @@ __global__ __launch_bounds__(256) void k_sensor_fwd(const PlumeDev* __restrict__
     const uint32_t* pz = S.pos[2];
     const real* C = static_cast<const real*>(S.C);
     const int span = 2 * P.R + 1, noff = (DIM == 3) ? span * span : span;
+    uint32_t total = 0;
+    for (int j0 = 0; j0 < noff; j0 += kWave) {
+        const int j = j0 + (int)lane;
+        RowRanges r{0u, 0u, 0u, 0u};
+        if (j < noff) r = row_ranges<DIM>(P, cs, T, j, span);
+        const uint32_t n0 = r.e0 > r.s0 ? r.e0 - r.s0 : 0u, n1 = r.e1 > r.s1 ? r.e1 - r.s1 : 0u;
+        const uint32_t incl = wave_inclusive_scan(n0 + n1), at = total + incl - n0 - n1;
+        if (j < noff) {
+            w[2 * j] = make_uint2(r.s0, at);
+            w[2 * j + 1] = make_uint2(r.s1, at + n0);
+        }
+        total += (uint32_t)__shfl((int)incl, kWave - 1, kWave);
+    }
+    __builtin_amdgcn_wave_barrier();  // (the LDS writes of a wavefront take effect in program order)
+    asm volatile("" ::: "memory");
     real num = 0, dsum = 0;
-    for (int j = 0; j < noff; ++j) {
-        const RowRanges r = row_ranges<DIM>(P, cs, T, j, span);
-        for (int part = 0; part < 2; ++part) {
-            const uint32_t b0 = part ? r.s1 : r.s0, b1 = part ? r.e1 : r.e0;
-            for (uint32_t b = b0; b < b1; ++b) {
-                const real dx = (real)(int32_t)(T.ux - px[b]);
-                const real dy = (real)(int32_t)(T.uy - py[b]);
-                const real dz = (DIM == 3) ? (real)(int32_t)(T.uz - pz[b]) : (real)0;
-                real r2 = dx * dx;
-                r2 = fmar(dy, dy, r2);
-                if (DIM == 3) r2 = fmar(dz, dz, r2);
-                if (r2 <= H2) {
-                    const real w = kernel_shape<real, KERN>(sqrt(r2) * invHu);
-                    num = fmar(w, C[b], num);
-                    dsum += w;
-                }
+    uint32_t q = 0;  // the window of this lane's candidate (they ascend)
+    for (uint32_t k0 = 0; k0 < total; k0 += kWave) {
+        const uint32_t k = k0 + lane;
+        real fa = 0, fb = 0, Cb = 0;
+        if (k < total) {
+            while (q + 1 < 2u * (uint32_t)noff && w[q + 1].y <= k) ++q;
+            const uint32_t b = w[q].x + (k - w[q].y);
+            const real dx = (real)(int32_t)(T.ux - px[b]);
+            const real dy = (real)(int32_t)(T.uy - py[b]);
+            const real dz = (DIM == 3) ? (real)(int32_t)(T.uz - pz[b]) : (real)0;
+            real r2 = dx * dx;
+            r2 = fmar(dy, dy, r2);
+            if (DIM == 3) r2 = fmar(dz, dz, r2);
+            if (r2 <= H2) {
+                kernel_factors<real, KERN>(sqrt(r2), invHu, fa, fb);
+                Cb = C[b];
             }
         }
+        // a candidate outside the support adds exact zeros
+        const int n = (int)min(total - k0, (uint32_t)kWave);
+        for (int l = 0; l < n; ++l) {
+            const real al = __shfl(fa, l, kWave), bl = __shfl(fb, l, kWave);
+            num = fmar(al * bl, __shfl(Cb, l, kWave), num);
+            dsum = fmar(al, bl, dsum);
+        }
     }
+    if (lane != 0) return;
     pred[s] = dsum > (real)0 ? num / dsum : (real)0;
     if (den) den[s] = dsum;
 }
@@ -131,26 +164,57 @@ __global__ __launch_bounds__(256) void k_sensor_seed(const PlumeDev* __restrict_
                                                     real* __restrict__ lam) {
     __shared__ uint32_t su[256][3];
     __shared__ real sr[256];
+    __shared__ uint32_t scan[256 / kWave];
+    __shared__ int ext[6];  // the workgroup's particles relative to its first: smallest and largest per axis
     const PlumeDev P = plumes[0];
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t i0 = blockIdx.x * blockDim.x, i = i0 + threadIdx.x;
     const bool active = i < N;
-    uint32_t u[3] = {0u, 0u, 0u};
+    uint32_t u[3] = {0u, 0u, 0u}, u0[3];
     if (active)
         for (int c = 0; c < DIM; ++c) u[c] = S.pos[c][i];
+    if (threadIdx.x < 6) ext[threadIdx.x] = 0;
+    __syncthreads();
+    for (int c = 0; c < DIM; ++c) {
+        u0[c] = S.pos[c][i0];
+        if (active) {
+            atomicMin(&ext[2 * c], (int)(u[c] - u0[c]));
+            atomicMax(&ext[2 * c + 1], (int)(u[c] - u0[c]));
+        }
+    }
+    __syncthreads();
+    // whether a sensor can be within the support of a particle of the workgroup
+    // (consecutive in cell order, so close together): along every axis, at the
+    // separation or one box length from it
+    auto near = [&](const uint32_t (&q)[3]) {
+        bool in = true;
+        for (int c = 0; c < DIM; ++c) {
+            const int64_t d = (int32_t)(q[c] - u0[c]), lo = (int64_t)ext[2 * c] - P.hx, hi = (int64_t)ext[2 * c + 1] + P.hx;
+            const int64_t box = int64_t(1) << 32;
+            in = in && ((d >= lo && d <= hi) || (d - box >= lo && d - box <= hi) || (d + box >= lo && d + box <= hi));
+        }
+        return in;
+    };
     const real H2 = h2_of<real>(P), invHu = (real)P.invHu;
     real acc = 0;
     for (int s0 = 0; s0 < ns; s0 += 256) {
-        __syncthreads();
         const int s = s0 + threadIdx.x;
+        uint32_t q[3] = {0u, 0u, 0u};
+        bool keep = false;
         if (s < ns) {
-            for (int c = 0; c < DIM; ++c)
-                su[threadIdx.x][c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L) - frame_shift(P, frame, c);
-            sr[threadIdx.x] = rw[s];
+            for (int c = 0; c < DIM; ++c) q[c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L) - frame_shift(P, frame, c);
+            keep = near(q);
+        }
+        // the sensors kept, in their order (the scan's barriers also separate
+        // the last chunk's reads from these writes)
+        uint32_t cnt;
+        const uint32_t at = block_exclusive_scan(keep ? 1u : 0u, scan, cnt);
+        if (keep) {
+            for (int c = 0; c < DIM; ++c) su[at][c] = q[c];
+            sr[at] = rw[s];
         }
         __syncthreads();
-        const int cnt = min(256, ns - s0);
         if (active) {
-            for (int k = 0; k < cnt; ++k) {
+            for (uint32_t k = 0; k < cnt; ++k) {
                 // separation sensor - particle, as in the forward interpolation
                 const real dx = (real)(int32_t)(su[k][0] - u[0]);
                 const real dy = (real)(int32_t)(su[k][1] - u[1]);
@@ -158,9 +222,14 @@ __global__ __launch_bounds__(256) void k_sensor_seed(const PlumeDev* __restrict_
                 real r2 = dx * dx;
                 r2 = fmar(dy, dy, r2);
                 if (DIM == 3) r2 = fmar(dz, dz, r2);
-                if (r2 <= H2) acc = fmar(sr[k], kernel_shape<real, KERN>(sqrt(r2) * invHu), acc);
+                if (r2 <= H2) {
+                    real fa, fb;
+                    kernel_factors<real, KERN>(sqrt(r2), invHu, fa, fb);
+                    acc = fmar(sr[k], fa * fb, acc);
+                }
             }
         }
+        __syncthreads();
     }
     if (active) lam[frame ? i : S.id[i]] = acc;
 }
@@ -715,7 +784,7 @@ int check_sensor_args(const ade_ctx* c, const double* d_xs, int32_t ns) {
 int launch_sensor_fwd(ade_ctx* c, const double* d_xs, int32_t ns, const StateArrays& S,
                       const uint32_t* cs, void* pred, void* den) {
     const Plan& pl = c->plan;
-    dim3 g((ns + 255) / 256), b(256);
+    dim3 g((ns + 3) / 4), b(256);
 #define CALL(D, R, K)                                                                        \
     hipLaunchKernelGGL((k_sensor_fwd<D, R, K>), g, b, 0, c->stream, c->plumes, d_xs, ns, S, frame_of(c), cs, \
                        (R*)pred, (R*)den)
