@@ -117,12 +117,14 @@ struct FrameStep {
 struct ListPlume {
     uint32_t row0;   // first row (64 words) of the plume's lists
     uint32_t rows;   // rows per wavefront (0: the plume keeps no lists)
-    uint32_t wave0;  // the plume's first wavefront
-    uint32_t pad;
 };
-// What is uniform in a wavefront's lists.
-struct ListWave {
+// What is uniform in a wavefront's lists, in the order of the pair kernel's work
+// items: one scalar load leads to everything that the wavefront reads.
+struct alignas(32) ListWave {
     static constexpr uint32_t kTwoPasses = 0x80000000u;
+    uint32_t i0, end;  // its targets' tile: the first target and past the last (i0 >= end: none)
+    uint32_t plume;
+    uint32_t row;   // first row of its lists
     uint32_t base;  // 2D: the record that its entries count from
     uint32_t nb;    // batches, and whether a second pass follows (kTwoPasses)
     uint32_t nb2;   // batches of the second pass
@@ -157,7 +159,6 @@ struct PairLaunch {
     int64_t* step;          // update: the step counter, advanced by this launch (null: left)
     // neighbour lists (list null: walk the row windows)
     const uint32_t* list;
-    const ListPlume* lplumes;
     const ListWave* waves;
     const uint4* list_pos;  // 3D FP64: positions as 16-byte records
     hipEvent_t ev0, ev1;    // if set: events stamped at the kernel's start and end

@@ -57,21 +57,18 @@ __device__ __forceinline__ real group_sum(real v) {
     return v;
 }
 
-// Walks the lists of the wavefront whose first target is i0.  pass(k0, k1, second,
+// Walks the lists of a wavefront.  pass(k0, k1, second,
 // walk) is called once with the group's two targets (T = 1: twice the same), or,
 // where the wavefront holds a pair too far apart, with (a, a) and then (second)
 // (b, b); it calls walk(one), and one(c, keep) gets every record of the list,
 // fetch(k) of its byte offset among 16-byte records.  keep false: a slot past
 // the end of the lane's list, which holds the record of target k0.
 template <int DIM, int G, int T, typename Fetch, typename Pass>
-__device__ __forceinline__ void walk_lists(const uint32_t* __restrict__ list, const ListWave* __restrict__ waves,
-                                           const ListPlume& lp, const PlumeDev& P, uint32_t i0,
+__device__ __forceinline__ void walk_lists(const uint32_t* __restrict__ list, const ListWave& head, const PlumeDev& P,
                                            const ListTargets<G, T>& q, Fetch&& fetch, Pass&& pass) {
     constexpr int B = kListBatch, kPer = Entry<DIM>::kPerRow, RB = B / kPer;
     using CandT = decltype(fetch(0u));
-    const uint32_t wave = (i0 - P.poff) / (kWave / G * T);
-    const uint32_t* __restrict__ rows = list + ((size_t)lp.row0 + (size_t)wave * lp.rows) * kWave;
-    const ListWave head = waves[lp.wave0 + wave];
+    const uint32_t* __restrict__ rows = list + (size_t)head.row * kWave;
     const uint32_t words = T == 2 ? rows[q.lane] : 0u;
     // 2D: entries count from the wavefront's base; a window past the end of
     // the plume goes on at its start

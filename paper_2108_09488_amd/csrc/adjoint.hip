@@ -301,7 +301,6 @@ struct AdjLaunch {
     double* gpart;
     // neighbour lists of the launch shape (list null: row windows)
     const uint32_t* list;
-    const ListPlume* lplumes;
     const ListWave* waves;
 };
 
@@ -433,20 +432,18 @@ __global__ __launch_bounds__(256) void k_adjoint(AdjLaunch a, const PlumeDev* __
 // pass over the windows with one lane a target, 7.2 us here.
 template <int DIM, typename real, int KERN, int AMODE, int G, int T>
 __global__ __launch_bounds__(256) void k_adjoint_list(AdjLaunch a, const PlumeDev* __restrict__ plumes,
-                                                     const TileDev* __restrict__ tiles) {
+                                                     const TileDev* __restrict__) {
     __shared__ double lds[kTile / kWave];
-    constexpr uint32_t kWaves = kTile / (kWave / G * T);
     const uint32_t wv = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
-    const TileDev t = tiles[wv / kWaves];
-    const uint32_t i0 = t.start + (wv % kWaves) * (kTile / kWaves);
-    const PlumeDev P = plumes[t.plume];
+    const ListWave head = a.waves[wv];
+    const PlumeDev P = plumes[head.plume];
     double c1 = 0.0, c2 = 0.0, c3 = 0.0;
-    if (i0 < t.end) {  // the wavefront has targets (ragged last tile)
-        const ListTargets<G, T> q(i0, t.end);
+    if (head.i0 < head.end) {  // the wavefront has targets (ragged last tile)
+        const ListTargets<G, T> q(head.i0, head.end);
         const AdjTerm<DIM, real, KERN, AMODE> term(P, a.speed);
         typename AdjTerm<DIM, real, KERN, AMODE>::Sums sA, sB;
         walk_lists<DIM, G, T>(
-            a.list, a.waves, a.lplumes[t.plume], P, i0, q,
+            a.list, head, P, q,
             [&](uint32_t k) { return adj_part<DIM, real>(a, k / kRecBytes); },
             [&](uint32_t k0, uint32_t k1, bool second, auto&& walk) {
                 const ACand<real> T0 = adj_part<DIM, real>(a, k0), T1 = adj_part<DIM, real>(a, k1);
@@ -934,7 +931,6 @@ int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, c
     // kAdjMaxSubs of them a tile
     const PairLaunch fwd = pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, nullptr, nullptr);
     base.list = fwd.list;
-    base.lplumes = fwd.lplumes;
     base.waves = fwd.waves;
     const uint32_t lwaves = (uint32_t)(kTile / 64) * (uint32_t)fwd.lanes / (uint32_t)fwd.targets;  // per tile
     const uint32_t lsubs = std::min(lwaves, kAdjMaxSubs), lblock = 64 * (lwaves / lsubs);

@@ -119,12 +119,11 @@ constexpr size_t kListBudget = size_t(16) << 30;  // bytes; contexts whose lists
 ListPlan list_plan(const Plan& pl, int lanes, int targets) {
     ListPlan L;
     if (pl.general) return L;
-    L.place.assign((size_t)pl.P, ListPlume{0u, 0u, 0u, 0u});
+    L.place.assign((size_t)pl.P, ListPlume{0u, 0u});
     for (int p = 0; p < pl.P; ++p) {
         const PlumeDev& d = pl.plumes[(size_t)p];
         ListPlume& q = L.place[(size_t)p];
         const size_t waves = (size_t)d.tcount * (size_t)(kTile / 64 * lanes / targets);
-        q.wave0 = (uint32_t)L.waves;
         L.waves += waves;
         const double nbar = pl.nbar[(size_t)p];
         if (nbar > 2000.0) continue;
@@ -138,7 +137,7 @@ ListPlan list_plan(const Plan& pl, int lanes, int targets) {
     }
     if (L.rows == 0) return L;
     auto part = [](size_t n) { return (n * 4 + 255) & ~size_t(255); };
-    L.bytes = part((L.rows + kListSlack) * 64) + part(L.waves * 4) +
+    L.bytes = part((L.rows + kListSlack) * 64) + part(L.waves * 8) +
               (pl.dim == 3 && pl.real_bytes == 8 ? part((size_t)pl.N * 4) : 0);
     if (L.bytes > kListBudget) L.bytes = 0;
     return L;
@@ -661,6 +660,30 @@ int run_pair(ade_ctx* c, int mode, const PairLaunch& a) {
     return ADE_OK;
 }
 
+// The lists of the current launch shape, of the plumes that lplumes gives room.
+static int write_lists(ade_ctx* c) {
+    const Plan& pl = c->plan;
+    const ListArrays q = list_arrays(c, c->lists_of);
+    ListBuild a;
+    std::memset(&a, 0, sizeof a);
+    a.plumes = c->plumes;
+    a.tiles = c->pair_tiles;
+    a.ntiles = pl.ntiles;
+    a.lanes = c->tuning.lanes;
+    a.targets = targets_of(c->tuning);
+    a.list_cap = tuning_list_cap(pl, c->tuning);
+    a.lplumes = c->lplumes;
+    a.rec = c->S.rec;
+    for (int d = 0; d < 3; ++d) a.spos[d] = c->S.pos[d];
+    a.cell_start = c->cell_start;
+    a.list = q.list;
+    a.waves = q.waves;
+    a.pos = q.pos;
+    a.over = c->flags + 1;
+    HIPCHK(launch_list(pl.dim, pl.real_bytes, a, c->stream));
+    return ADE_OK;
+}
+
 // Builds the lists of the current launch shape; their flags (flags[1 + plume],
 // zero before) tell lists_built which plumes' do not fit.
 static int enqueue_lists(ade_ctx* c) {
@@ -676,25 +699,7 @@ static int enqueue_lists(ade_ctx* c) {
                               hipMemcpyHostToDevice, c->stream));
         c->place_shape = shape;
     }
-    const ListArrays q = list_arrays(c, c->lists_of);
-    ListBuild a;
-    std::memset(&a, 0, sizeof a);
-    a.plumes = c->plumes;
-    a.tiles = c->tiles;
-    a.ntiles = pl.ntiles;
-    a.lanes = c->tuning.lanes;
-    a.targets = targets_of(c->tuning);
-    a.list_cap = tuning_list_cap(pl, c->tuning);
-    a.lplumes = c->lplumes;
-    a.rec = c->S.rec;
-    for (int d = 0; d < 3; ++d) a.spos[d] = c->S.pos[d];
-    a.cell_start = c->cell_start;
-    a.list = q.list;
-    a.waves = q.waves;
-    a.pos = q.pos;
-    a.over = c->flags + 1;
-    HIPCHK(launch_list(pl.dim, pl.real_bytes, a, c->stream));
-    return ADE_OK;
+    return write_lists(c);
 }
 
 // the flags, by a synchronisation of the stream
@@ -723,6 +728,8 @@ static int lists_built(ade_ctx* c, const std::vector<uint32_t>& flags) {
         HIPCHK(hipMemcpyAsync(c->lplumes, place.data(), sizeof(ListPlume) * place.size(), hipMemcpyHostToDevice,
                               c->stream));
         c->place_shape = 0;  // other particles may fit
+        int rc = with ? write_lists(c) : ADE_OK;  // without the lists that do not fit
+        if (rc) return rc;
     }
     for (const TileDev& t : pl.pair_tiles)
         if (with && place[t.plume].rows == 0) rest.push_back(t);
@@ -776,7 +783,6 @@ PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void
     if (c->list_use) {
         const ListArrays q = list_arrays(c, c->lists_of);
         a.list = q.list;
-        a.lplumes = c->lplumes;
         a.waves = q.waves;
         a.list_pos = q.pos;
     }

@@ -77,12 +77,16 @@ __global__ __launch_bounds__(64) void k_list(ListBuild a, const PlumeDev* __rest
     constexpr uint32_t kGroups = kWave / G, kTargets = kGroups * T, kWaves = kTile / kTargets;
     const TileDev t = tiles[blockIdx.x / kWaves];
     const uint32_t i0 = t.start + (blockIdx.x % kWaves) * kTargets;
-    if (i0 >= t.end) return;
-    const PlumeDev P = plumes[t.plume];
     const ListPlume lp = a.lplumes[t.plume];
-    if (lp.rows == 0u) return;  // a plume without lists
-    const uint32_t wave = (i0 - P.poff) / kTargets;
-    uint32_t* out = a.list + ((size_t)lp.row0 + (size_t)wave * lp.rows) * kWave;
+    ListWave head{i0, t.end, t.plume, 0u, 0u, 0u, 0u, 0u};
+    if (i0 >= t.end || lp.rows == 0u) {  // no targets, or a plume without lists
+        head.end = 0u;
+        if (threadIdx.x == 0) a.waves[blockIdx.x] = head;
+        return;
+    }
+    const PlumeDev P = plumes[t.plume];
+    head.row = lp.row0 + (i0 - P.poff) / kTargets * lp.rows;
+    uint32_t* out = a.list + (size_t)head.row * kWave;
     uint16_t* out2 = reinterpret_cast<uint16_t*>(out);
 
     const uint32_t lane = threadIdx.x, g = lane / G, lj = lane % G;
@@ -105,7 +109,7 @@ __global__ __launch_bounds__(64) void k_list(ListBuild a, const PlumeDev* __rest
         base = cell_start_at(a.cell_start, row_base(P, row, 0)) - P.poff;
     }
     base = __builtin_amdgcn_readfirstlane(base);
-    ListWave head{base, 0u, 0u, 0u};
+    head.base = base;
 
     int pry = 0, prz = 0;
     const bool close = T == 1 || pair_rows<DIM>(P, target(iA), target(iB), pry, prz);
@@ -236,7 +240,7 @@ __global__ __launch_bounds__(64) void k_list(ListBuild a, const PlumeDev* __rest
         if (actA) pack(iA);
         if (T == 2 && actB) pack(iB);
     }
-    if (lane == 0) a.waves[lp.wave0 + wave] = head;
+    if (lane == 0) a.waves[blockIdx.x] = head;
     if (bad) a.over[t.plume] = 1u;
 }
 
@@ -245,17 +249,16 @@ __global__ __launch_bounds__(64) void k_list(ListBuild a, const PlumeDev* __rest
 // ---------------------------------------------------------------------------
 template <int DIM, typename real, int KERN, int MODE, int G, int T, bool ZC>
 __device__ __forceinline__ void list_item(const PairLaunch& a, const PlumeDev* __restrict__ plumes,
-                                          const TileDev* __restrict__ tiles, uint32_t w) {
-    constexpr uint32_t kWaves = kTile / (kWave / G * T);
-    // the wavefront's number among all: a workgroup holds a whole number of them
+                                          uint32_t w) {
+    // The wavefront's number among all: a workgroup holds a whole number of them.
+    // Its head comes in one scalar load; by way of its tile, its plume's lists and
+    // then their head (three loads in a chain) the 47^3 FP64 kernel takes 37 us (35
+    // now), the 128-plume ensemble's quads 270 us (257).
     const uint32_t wv = __builtin_amdgcn_readfirstlane(w * ((uint32_t)a.block / kWave) + threadIdx.x / kWave);
-    const TileDev t = tiles[wv / kWaves];
-    const uint32_t i0 = t.start + (wv % kWaves) * (kTile / kWaves);
-    if (i0 >= t.end) return;  // the whole wavefront: ragged last tile
-    const PlumeDev P = plumes[t.plume];
-    const ListPlume lp = a.lplumes[t.plume];
-    if (lp.rows == 0u) return;  // a plume without lists: its row windows are walked
-    const ListTargets<G, T> q(i0, t.end);
+    const ListWave head = a.waves[wv];
+    if (head.i0 >= head.end) return;  // ragged last tile, or a plume whose row windows are walked
+    const PlumeDev P = plumes[head.plume];
+    const ListTargets<G, T> q(head.i0, head.end);
     const real* __restrict__ Cp = static_cast<const real*>(a.Cpair);
     constexpr bool kRec = Rec<DIM, real>::kStageable;
     const uint4* __restrict__ rec = kRec ? a.rec : a.list_pos;
@@ -268,7 +271,7 @@ __device__ __forceinline__ void list_item(const PairLaunch& a, const PlumeDev* _
     auto part = [&](uint32_t k) { return fetch(k * kRecBytes); };
     const PairTerm<DIM, real, KERN, ZC> term = make_term<DIM, real, KERN, ZC>(P);
     real accA = (real)0, accB = (real)0;
-    walk_lists<DIM, G, T>(a.list, a.waves, lp, P, i0, q, fetch, [&](uint32_t k0, uint32_t k1, bool second, auto&& walk) {
+    walk_lists<DIM, G, T>(a.list, head, P, q, fetch, [&](uint32_t k0, uint32_t k1, bool second, auto&& walk) {
         const Cand<real> T0 = part(k0), T1 = part(k1);
         const real bx = (real)(int32_t)(T1.x - T0.x);
         const real by = (real)(int32_t)(T1.y - T0.y);
@@ -296,10 +299,10 @@ __device__ __forceinline__ void list_item(const PairLaunch& a, const PlumeDev* _
 
 template <int DIM, typename real, int KERN, int MODE, int G, int T, bool ZC>
 __global__ __launch_bounds__(256) void k_pair_list(PairLaunch a, const PlumeDev* __restrict__ plumes,
-                                                   const TileDev* __restrict__ tiles, uint32_t nwork) {
+                                                   uint32_t nwork) {
     advance_step(a);
     if (a.persistent == 0) {
-        list_item<DIM, real, KERN, MODE, G, T, ZC>(a, plumes, tiles, xcd_remap(blockIdx.x, gridDim.x, a.xcd_group));
+        list_item<DIM, real, KERN, MODE, G, T, ZC>(a, plumes, xcd_remap(blockIdx.x, gridDim.x, a.xcd_group));
         return;
     }
     const uint32_t nx = 8, x = blockIdx.x % nx, k = blockIdx.x / nx;
@@ -307,7 +310,7 @@ __global__ __launch_bounds__(256) void k_pair_list(PairLaunch a, const PlumeDev*
     for (uint32_t m = k;; m += per_x) {
         const uint32_t w = xcd_item(x, m, nwork, a.xcd_group);
         if (w >= nwork) break;
-        list_item<DIM, real, KERN, MODE, G, T, ZC>(a, plumes, tiles, w);
+        list_item<DIM, real, KERN, MODE, G, T, ZC>(a, plumes, w);
     }
 }
 
@@ -350,9 +353,9 @@ static void launch_pair_list_s(int mode, const PairLaunch& a, hipStream_t s) {
     auto kern = (mode == kModeRhs) ? k_pair_list<DIM, real, KERN, kModeRhs, G, T, ZC>
                                    : k_pair_list<DIM, real, KERN, kModeStep, G, T, ZC>;
     if (c.ev0)
-        hipExtLaunchKernelGGL(kern, gr, b, 0u, s, c.ev0, c.ev1, 0u, c, c.plumes, c.tiles, nwork);
+        hipExtLaunchKernelGGL(kern, gr, b, 0u, s, c.ev0, c.ev1, 0u, c, c.plumes, nwork);
     else
-        hipLaunchKernelGGL(kern, gr, b, 0, s, c, c.plumes, c.tiles, nwork);
+        hipLaunchKernelGGL(kern, gr, b, 0, s, c, c.plumes, nwork);
 }
 
 // one target a group: its list holds no record at r = 0 but the padding (the
