@@ -136,4 +136,64 @@ struct Rec {
     }
 };
 
+// Candidate record of a velocity-field particle: its position words, then C, the
+// velocity and the reciprocals of the tensor components in the working precision,
+// padded to a multiple of 32 bytes (2D FP32: {x, y, C, v_x} {v_y, 1/D_xx, 1/D_xy,
+// 1/D_yy}, 32 bytes; 3D FP32 and 2D FP64 64; 3D FP64 96, its position in four words).
+template <int DIM, typename real>
+struct GenRec {
+    static constexpr int kVals = 1 + DIM + (DIM == 2 ? 3 : 6);
+    static constexpr int kPer = sizeof(real) / 4;
+    static constexpr int kPos = (kPer == 2 && DIM == 3) ? 4 : DIM;  // doubles on even words
+    static constexpr int kWords = kPos + kVals * kPer;
+    static constexpr int kQuads = (kWords + 7) / 8 * 2;
+    static __device__ __forceinline__ real value(const uint32_t* w, int j) {
+        if constexpr (sizeof(real) == 4) return __uint_as_float(w[kPos + j]);
+        else return __hiloint2double((int)w[kPos + 2 * j + 1], (int)w[kPos + 2 * j]);
+    }
+    // the words of record k: 16-byte loads and one for the rest
+    static __device__ __forceinline__ void load(const uint4* __restrict__ rec, uint32_t k, uint32_t (&w)[kWords]) {
+        // 2D FP32: a 32-bit byte offset from a uniform base (such a context
+        // holds fewer than 2^27 particles)
+        const char* base = reinterpret_cast<const char*>(rec) +
+                           (kQuads == 2 ? (size_t)(k << 5) : (size_t)k * (kQuads * 16));
+#pragma unroll
+        for (int q = 0; q < kWords / 4; ++q) {
+            const uint4 v = *reinterpret_cast<const uint4*>(base + 16 * q);
+            w[4 * q] = v.x;
+            w[4 * q + 1] = v.y;
+            w[4 * q + 2] = v.z;
+            w[4 * q + 3] = v.w;
+        }
+        constexpr int kRest = kWords / 4 * 4;
+        if constexpr (kWords % 4 == 2) {
+            const uint2 v = *reinterpret_cast<const uint2*>(base + 4 * kRest);
+            w[kRest] = v.x;
+            w[kRest + 1] = v.y;
+        } else if constexpr (kWords % 4 == 1) {
+            w[kRest] = *reinterpret_cast<const uint32_t*>(base + 4 * kRest);
+        }
+    }
+    // vals: velocity and reciprocals
+    static __device__ __forceinline__ void store(uint4* __restrict__ rec, uint32_t k, const uint32_t* u, real C,
+                                                 const real* vals) {
+        uint32_t w[kQuads * 4] = {};
+#pragma unroll
+        for (int c = 0; c < DIM; ++c) w[c] = u[c];
+#pragma unroll
+        for (int j = 0; j < kVals; ++j) {
+            const real v = j == 0 ? C : vals[j > 0 ? j - 1 : 0];
+            if constexpr (sizeof(real) == 4) {
+                w[kPos + j] = __float_as_uint((float)v);
+            } else {
+                w[kPos + 2 * j] = (uint32_t)__double2loint((double)v);
+                w[kPos + 2 * j + 1] = (uint32_t)__double2hiint((double)v);
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kQuads; ++q)
+            rec[(size_t)k * kQuads + q] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+    }
+};
+
 }  // namespace ade

@@ -76,8 +76,8 @@ struct StateArrays {
     // velocity field with the predictor-corrector: C^n carried through the
     // predictor's build (null otherwise)
     void* Cb;
-    // velocity field in 2D FP32, sorted buffer S only (null otherwise): a
-    // 32-byte record per particle, {x, y, C, v_x} {v_y, 1/D_xx, 1/D_xy, 1/D_yy}
+    // velocity field, sorted buffer S only (null otherwise): the candidate
+    // records of the pair sum (GenRec, ade_device.h)
     uint4* grec;
 };
 
@@ -222,6 +222,7 @@ struct GenLaunch {
     void* out;              // rhs mode: id-order output
     hipEvent_t ev0, ev1;    // if set: events stamped at the kernel's start and end
 };
+hipError_t launch_gen_rec(int dim, int real_bytes, StateArrays S, uint32_t N, hipStream_t s);
 hipError_t launch_setvel(int dim, int real_bytes, const PlumeDev* plumes, const TileDev* tiles, uint32_t ntiles,
                          const double* v, uint32_t N, StateArrays U, hipStream_t s);
 // Adjoint pass of the velocity-field Euler step over a state snapshot S:

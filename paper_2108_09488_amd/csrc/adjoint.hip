@@ -643,7 +643,7 @@ void take_snap(char* base, size_t& off, const ade_ctx* c, Snap& s) {
     s.step = (int64_t*)take(8);
     for (int d = 0; d < 3; ++d) s.vel[d] = c->S.vel[d] ? take(N * pl.real_bytes) : nullptr;
     for (int d = 0; d < 6; ++d) s.rD[d] = c->S.rD[d] ? take(N * pl.real_bytes) : nullptr;
-    s.grec = c->S.grec ? (uint4*)take(N * 32) : nullptr;
+    s.grec = keeps_gen_rec(pl) ? (uint4*)take(N * 32) : nullptr;
 }
 
 void adj_layout(const ade_ctx* c, int64_t nsteps, int32_t K, int32_t ns, char* base, AdjLayout& L) {
@@ -741,6 +741,9 @@ int copy_state(const ade_ctx* c, const Snap& dst, const Snap& src) {
         hipLaunchKernelGGL(k_copy_snap_x, dim3((xitems + 255) / 256), dim3(256), 0, c->stream, a);
         HIPCHK(hipGetLastError());
     }
+    // the live state's records, where snapshots do not hold them
+    if (pl.general && !keeps_gen_rec(pl) && dst.C == c->S.C)
+        HIPCHK(launch_gen_rec(pl.dim, pl.real_bytes, c->S, N, c->stream));
     return ADE_OK;
 }
 
@@ -754,7 +757,7 @@ Snap live(ade_ctx* c) {
     s.step = c->step;
     for (int d = 0; d < 3; ++d) s.vel[d] = c->S.vel[d];
     for (int d = 0; d < 6; ++d) s.rD[d] = c->S.rD[d];
-    s.grec = c->S.grec;
+    s.grec = keeps_gen_rec(c->plan) ? c->S.grec : nullptr;
     return s;
 }
 

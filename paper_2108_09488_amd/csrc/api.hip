@@ -92,15 +92,17 @@ bool default_tuning(const Plan& pl, ade_tuning& out) {
             ok = true;
         }
     if (!ok) return false;
-    // a velocity field: four lanes per target in the largest workgroup
-    // whose lists fit, or in 2D FP32 for plumes of thousands of
+    // a velocity field: four lanes per target in workgroups of one wavefront
+    // (41^3 FP32 105 against 116 us for 256 threads, which hold their list
+    // space until the slowest wavefront ends; after hundreds of steps of a
+    // converging flow 512^2 49 against 89 us; 512^2, 61^3 and 128^2 from the
+    // lattice the same), or in 2D FP32 for plumes of thousands of
     // neighbours four lanes per two targets, block 128 (10^6 particles,
     // 31k neighbours: 44 against 64 ms per update launch; on the 512^2
     // plumes of 46 and 111 neighbours the same as, or 3% slower than,
     // one target a quad).  Its autotuner may choose otherwise.
     if (pl.general) {
-        for (int bb : {64, 128, 256})
-            if (gen_tuning_fits(pl, ade_tuning{bb, 4, 0, 0, 1})) out = ade_tuning{bb, 4, 0, 0, 1};
+        if (gen_tuning_fits(pl, ade_tuning{64, 4, 0, 0, 1})) out = ade_tuning{64, 4, 0, 0, 1};
         const ade_tuning q{128, 4, 0, 0, 2};
         if (pl.nbar_max > 2000.0 && gen_tuning_fits(pl, q)) out = q;
     }
@@ -472,7 +474,7 @@ void layout(Bump& b, ade_ctx* c, const Plan& pl) {
         s.key = !sorted ? b.take<uint32_t>(N) : nullptr;
         for (int d = 0; d < 3; ++d) s.vel[d] = (pl.general && d < pl.dim) ? b.take_bytes(N * rb) : nullptr;
         for (int d = 0; d < 6; ++d) s.rD[d] = (pl.general && d < (pl.dim == 2 ? 3 : 6)) ? b.take_bytes(N * rb) : nullptr;
-        s.grec = (sorted && pl.general && pl.dim == 2 && pl.real_bytes == 4) ? b.take<uint4>(2 * N) : nullptr;
+        s.grec = (sorted && pl.general) ? b.take<uint4>(gen_rec_quads(pl) * N) : nullptr;
         s.Cb = (pl.general && pl.integrator == ADE_PC) ? b.take_bytes(N * rb) : nullptr;
     };
     state(c->S, true);
@@ -1426,7 +1428,7 @@ std::vector<Section> state_sections(const ade_ctx* c) {
         if (S.vel[d]) v.push_back({S.vel[d], N * rb});
     for (int d = 0; d < 6; ++d)
         if (S.rD[d]) v.push_back({S.rD[d], N * rb});
-    if (S.grec) v.push_back({S.grec, N * 32});
+    if (keeps_gen_rec(pl)) v.push_back({S.grec, N * 32});
     v.push_back({c->cell_start, ((size_t)pl.ncell + 1) * 4});
     v.push_back({c->step, pl.general ? size_t(8) : sizeof(FrameStep)});
     return v;
@@ -1495,6 +1497,8 @@ int ade_load_state(ade_ctx* c, const void* h_buf, size_t bytes) {
     HIPCHK(hipMemsetAsync(c->count, 0, sizeof(uint32_t) * cell_pad(pl.ncell), c->stream));
     HIPCHK(hipMemsetAsync(c->lists.ovf_count, 0, sizeof(uint32_t) * (2 + 1 + (size_t)pl.P), c->stream));
     HIPCHK(hipStreamSynchronize(c->stream));
+    if (pl.general && !keeps_gen_rec(pl))
+        HIPCHK(launch_gen_rec(pl.dim, pl.real_bytes, c->S, (uint32_t)pl.N, c->stream));
     c->initialized = true;
     c->built = true;
     c->vel_set = true;

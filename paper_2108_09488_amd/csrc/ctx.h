@@ -39,6 +39,14 @@ struct Plan {
     std::vector<TileDev> pair_tiles;  // the tiles in the pair kernel's order (costliest plumes first)
 };
 
+// 16-byte words of a velocity field's candidate record (GenRec::kQuads)
+inline size_t gen_rec_quads(const Plan& pl) {
+    return pl.real_bytes == 4 ? (pl.dim == 2 ? 2 : 4) : (pl.dim == 2 ? 4 : 6);
+}
+// whether saved states and snapshots hold the records; elsewhere they are made
+// again from the arrays
+inline bool keeps_gen_rec(const Plan& pl) { return pl.general && pl.dim == 2 && pl.real_bytes == 4; }
+
 // The neighbour lists of a plan for a launch shape: each plume's place, and the
 // sizes of the arrays they take (bytes 0: no plume keeps any).
 struct ListPlan {

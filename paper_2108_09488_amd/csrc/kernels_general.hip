@@ -15,17 +15,21 @@
 // (ade_walk.h), or in 2D FP32 the four lanes of a quad walk the merged list of
 // two neighbouring targets and evaluate every record for both.  Each
 // particle carries the reciprocals of its tensor components, so a harmonic
-// mean costs one add and one reciprocal; in 2D FP32 a candidate is one
-// 32-byte record, elsewhere it is read from the structure-of-arrays state.
+// mean costs one add and one reciprocal, and a candidate is one record of 32
+// to 96 bytes (GenRec).
 #include <hip/hip_ext.h>
 
 #include "ade_walk.h"
 
 namespace ade {
 
-// candidate records per lane per batch of the walk (2: the kernel stays at
-// 64 VGPRs; 4 measured about 13% slower in both update and rhs mode)
-constexpr int kGenBatch = 2;
+// Candidates per lane per batch of the walk: two, or one where the candidate is
+// an FP64 record.  FP32 in 2D: four measured about 13% slower in both update and
+// rhs mode; FP64 records, two against one: 99 and 87 us (512^2), 78 and 77 (31^3).
+template <typename real, bool RECORD>
+constexpr int gen_batch() {
+    return RECORD && sizeof(real) == 8 ? 1 : 2;
+}
 
 template <int DIM>
 struct GenDims {
@@ -61,6 +65,23 @@ __host__ __device__ inline void tensor_of(double aL, double aT, double Dm, const
         Dt[4] = comp(1, 2);
         Dt[5] = comp(2, 2);
     }
+}
+
+// the candidate records of the sorted state S, from its arrays
+template <int DIM, typename real>
+__global__ __launch_bounds__(256) void k_gen_rec(StateArrays S, uint32_t N) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= N) return;
+    uint32_t u[3] = {0u, 0u, 0u};
+    real w[DIM + GenDims<DIM>::kT];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+        u[c] = S.pos[c][i];
+        w[c] = static_cast<const real*>(S.vel[c])[i];
+    }
+#pragma unroll
+    for (int q = 0; q < GenDims<DIM>::kT; ++q) w[DIM + q] = static_cast<const real*>(S.rD[q])[i];
+    GenRec<DIM, real>::store(S.grec, i, u, static_cast<const real*>(S.C)[i], w);
 }
 
 // Velocities (double, SoA dim x N in id order) into the hashed buffer U,
@@ -103,25 +124,26 @@ struct GPart {
     real r[GenDims<DIM>::kT];
 };
 
-// 2D FP32 reads the particle's 32-byte record, the other cases the
-// structure-of-arrays state.
-template <int DIM, typename real>
+// Read from the particle's record (RECORD), or from the structure-of-arrays
+// state.  The records' loads return 16 bytes a lane: read as 13 separate
+// components, the 3D FP32 kernel was bound by the vector cache's return path
+// (busy 98% of its 528 us at 61^3 particles, 18 cycles a load, the VALU 36%); with
+// the records it takes 310 us.
+template <int DIM, typename real, bool RECORD>
 __device__ __forceinline__ GPart<DIM, real> load_part(const StateArrays& S, uint32_t k) {
     GPart<DIM, real> p;
-    if constexpr (DIM == 2 && sizeof(real) == 4) {
-        // 32-bit byte offset from a uniform base (a velocity-field context in
-        // 2D FP32 holds fewer than 2^27 particles)
-        const char* base = reinterpret_cast<const char*>(S.grec) + (k << 5);
-        const uint4 a = *reinterpret_cast<const uint4*>(base), b = *reinterpret_cast<const uint4*>(base + 16);
-        p.x = a.x;
-        p.y = a.y;
-        p.z = 0u;
-        p.C = __uint_as_float(a.z);
-        p.v[0] = __uint_as_float(a.w);
-        p.v[1] = __uint_as_float(b.x);
-        p.r[0] = __uint_as_float(b.y);
-        p.r[1] = __uint_as_float(b.z);
-        p.r[2] = __uint_as_float(b.w);
+    if constexpr (RECORD) {
+        using R = GenRec<DIM, real>;
+        uint32_t w[R::kWords];
+        R::load(S.grec, k, w);
+        p.x = w[0];
+        p.y = w[1];
+        p.z = (DIM == 3) ? w[2] : 0u;
+        p.C = R::value(w, 0);
+#pragma unroll
+        for (int d = 0; d < DIM; ++d) p.v[d] = R::value(w, 1 + d);
+#pragma unroll
+        for (int q = 0; q < GenDims<DIM>::kT; ++q) p.r[q] = R::value(w, 1 + DIM + q);
     } else {
         p.x = S.pos[0][k];
         p.y = S.pos[1][k];
@@ -317,6 +339,10 @@ __device__ __forceinline__ void gen_finish(const GenLaunch& g, const PlumeDev& P
 template <int DIM, typename real, int KERN, int MODE, int LANES>
 __global__ __launch_bounds__(256) void k_pair_gen(GenLaunch g) {
     extern __shared__ uint2 lds_list[];
+    // one lane a target in 2D FP64 reads the arrays: consecutive lanes' candidates
+    // are close to consecutive records (112 against 135 us at 512^2; with four lanes
+    // the records take 87 us, the arrays 97)
+    constexpr bool kRecord = !(DIM == 2 && sizeof(real) == 8 && LANES == 1);
     const uint32_t tpb = blockDim.x / LANES, subs = kTile / tpb;
     const TileDev t = g.tiles[blockIdx.x / subs];
     const uint32_t i0 = t.start + (blockIdx.x % subs) * tpb;
@@ -330,7 +356,7 @@ __global__ __launch_bounds__(256) void k_pair_gen(GenLaunch g) {
     const uint32_t i = active ? i0 + lt : i0;
 
     const StateArrays& S = g.S;
-    const GPart<DIM, real> A = load_part<DIM, real>(S, i);
+    const GPart<DIM, real> A = load_part<DIM, real, kRecord>(S, i);
     const Target T = make_target<DIM>(P, A.x, A.y, A.z);
 
     // every lane of a target writes the same list
@@ -342,14 +368,14 @@ __global__ __launch_bounds__(256) void k_pair_gen(GenLaunch g) {
     const real invHu = (real)P.invHu;
     const real gam = (real)(DIM + 2);
     real disp = 0, conv = 0;
-    auto fetch = [&](uint32_t k) { return load_part<DIM, real>(S, k / kRecBytes); };
+    auto fetch = [&](uint32_t k) { return load_part<DIM, real, kRecord>(S, k / kRecBytes); };
     auto eval = [&](const GPart<DIM, real>& c, bool keep) {
         const real dx = (real)(int32_t)(T.ux - c.x);
         const real dy = (real)(int32_t)(T.uy - c.y);
         const real dz = (DIM == 3) ? (real)(int32_t)(T.uz - c.z) : (real)0;
         gen_term<DIM, real, KERN>(A, c, dx, dy, dz, keep, invHu, gam, disp, conv);
     };
-    walk_lanes<LANES, kGenBatch>(list, tpb, total, lj, i, fetch, eval);
+    walk_lanes<LANES, gen_batch<real, kRecord>()>(list, tpb, total, lj, i, fetch, eval);
     // the lanes of a target combine their sums (fixed order: deterministic)
     if (LANES >= 2) {
         disp += __shfl_xor(disp, 1, kWave);
@@ -400,14 +426,14 @@ __global__ __launch_bounds__(256) void k_pair_gen42(GenLaunch g) {
     uint2* list = lds_list + lq;
     const real invHu = (real)P.invHu;
     const real gam = (real)(DIM + 2);
-    auto fetch = [&](uint32_t k) { return load_part<DIM, real>(S, k / kRecBytes); };
+    auto fetch = [&](uint32_t k) { return load_part<DIM, real, true>(S, k / kRecBytes); };
     real dispA = 0, convA = 0, dispB = 0, convB = 0;
     const int npass = merged ? 1 : 2;
     for (int pass = 0; pass < npass; ++pass) {
         // the pass's pair: (a, b), or (a, a) and then (b, b)
         const bool second = pass == 1;
         const uint32_t k0 = second ? iB : iA, k1 = merged ? iB : k0;
-        const GPart<DIM, real> A0 = load_part<DIM, real>(S, k0), A1 = load_part<DIM, real>(S, k1);
+        const GPart<DIM, real> A0 = load_part<DIM, real, true>(S, k0), A1 = load_part<DIM, real, true>(S, k1);
         const Target T0 = make_target<DIM>(P, A0.x, A0.y, A0.z), T1 = make_target<DIM>(P, A1.x, A1.y, A1.z);
         const int ry = merged ? pry : 0, rz = merged ? prz : 0;
         const real bx = (real)(int32_t)(T1.ux - T0.ux);
@@ -459,7 +485,7 @@ __global__ __launch_bounds__(256) void k_pair_gen42(GenLaunch g) {
     const bool fa = lj == 0 && actA, fb = lj == 1 && actB;
     if (!fa && !fb) return;
     const uint32_t i = fa ? iA : iB;
-    const GPart<DIM, real> A = load_part<DIM, real>(S, i);
+    const GPart<DIM, real> A = load_part<DIM, real, true>(S, i);
     gen_finish<DIM, real, KERN, MODE>(g, P, make_target<DIM>(P, A.x, A.y, A.z), A, i, fa ? dispA : dispB,
                                       fa ? convA : convB);
 }
@@ -503,6 +529,7 @@ __global__ __launch_bounds__(256) void k_adjoint_gen(AdjGenLaunch g) {
     extern __shared__ uint2 lds_list[];
     __shared__ double lds[kTile / kWave];
     constexpr int NT = GenDims<DIM>::kT;
+    constexpr bool kRecord = DIM == 2 && sizeof(real) == 4;  // the snapshots that keep records
     const uint32_t tpb = blockDim.x / LANES, subs = kTile / tpb;
     const TileDev t = g.tiles[blockIdx.x / subs];
     const uint32_t i0 = t.start + (blockIdx.x % subs) * tpb;
@@ -515,7 +542,7 @@ __global__ __launch_bounds__(256) void k_adjoint_gen(AdjGenLaunch g) {
 
     const StateArrays& S = g.S;
     const real* __restrict__ lam_s = static_cast<const real*>(g.lam_s);
-    const GPart<DIM, real> A = load_part<DIM, real>(S, i);
+    const GPart<DIM, real> A = load_part<DIM, real, kRecord>(S, i);
     const real la = lam_s[i];
     const Target T = make_target<DIM>(P, A.x, A.y, A.z);
     real Da[NT], dA[3][NT];
@@ -537,7 +564,7 @@ __global__ __launch_bounds__(256) void k_adjoint_gen(AdjGenLaunch g) {
     };
     auto fetch = [&](uint32_t k) {
         k /= kRecBytes;
-        return Cand{load_part<DIM, real>(S, k), lam_s[k]};
+        return Cand{load_part<DIM, real, kRecord>(S, k), lam_s[k]};
     };
     // the Dcal-type bracket Gamma x^T M x / r^2 - tr M of a symmetric tensor M
     // (stored components), times r^2 / r^2 in grid units
@@ -603,7 +630,7 @@ __global__ __launch_bounds__(256) void k_adjoint_gen(AdjGenLaunch g) {
             gk[th] = fmar(bracket(dh, dx, dy, dz, ir2), dC, gk[th]);
         }
     };
-    walk_lanes<LANES, kGenBatch>(list, tpb, total, lj, i, fetch, eval);
+    walk_lanes<LANES, gen_batch<real, kRecord>()>(list, tpb, total, lj, i, fetch, eval);
     // the lanes of a target combine their sums (fixed order: deterministic)
     real red[5] = {al, cv, gk[0], gk[1], gk[2]};
 #pragma unroll
@@ -681,6 +708,15 @@ hipError_t launch_adjoint_gen(int dim, int real_bytes, int kernel, int mode, con
                        : launch_adj_gen_t<3, double, 2>(mode, a, block, s);
 }
 
+hipError_t launch_gen_rec(int dim, int real_bytes, StateArrays S, uint32_t N, hipStream_t s) {
+    const dim3 gr((N + 255) / 256), b(256);
+    if (dim == 2 && real_bytes == 4) hipLaunchKernelGGL((k_gen_rec<2, float>), gr, b, 0, s, S, N);
+    else if (dim == 2) hipLaunchKernelGGL((k_gen_rec<2, double>), gr, b, 0, s, S, N);
+    else if (real_bytes == 4) hipLaunchKernelGGL((k_gen_rec<3, float>), gr, b, 0, s, S, N);
+    else hipLaunchKernelGGL((k_gen_rec<3, double>), gr, b, 0, s, S, N);
+    return hipGetLastError();
+}
+
 hipError_t launch_setvel(int dim, int real_bytes, const PlumeDev* plumes, const TileDev* tiles, uint32_t ntiles,
                          const double* v, uint32_t N, StateArrays U, hipStream_t s) {
     dim3 gr(ntiles), b(kTile);
@@ -697,7 +733,7 @@ static hipError_t launch_gen_l(int mode, const GenLaunch& g, hipStream_t s) {
     if (block != 64 && block != 128 && block != 256) return hipErrorInvalidValue;
     const size_t shm = (size_t)(block / LANES) * (size_t)g.list_cap * 8u;
     if (shm > kPairLdsMax) return hipErrorInvalidValue;
-    if (DIM == 2 && sizeof(real) == 4 && !g.S.grec) return hipErrorInvalidValue;
+    if (!g.S.grec) return hipErrorInvalidValue;
     dim3 gr(g.ntiles * (kTile / (block / LANES))), b(block);
     auto kern = (mode == kModeStep)   ? k_pair_gen<DIM, real, KERN, kModeStep, LANES>
                 : (mode == kModeHalf) ? k_pair_gen<DIM, real, KERN, kModeHalf, LANES>
