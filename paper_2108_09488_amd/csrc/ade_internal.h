@@ -200,11 +200,12 @@ hipError_t launch_pair_list(int dim, int real_bytes, int kernel, int mode, const
 hipError_t launch_init(int dim, int real_bytes, const PlumeDev* plumes, const TileDev* tiles,
                        uint32_t ntiles, const double* x, const void* C, uint32_t N,
                        StateArrays U, CellLists lists, hipStream_t s);
-hipError_t launch_scan(CellLists lists, uint32_t* cell_start, uint32_t* partial, uint32_t ncell,
+// nout: entries of cell_start to write, ncell + 1 up to cell_pad(ncell)
+hipError_t launch_scan(CellLists lists, uint32_t* cell_start, uint32_t nout, uint32_t* partial, uint32_t ncell,
                        hipStream_t s);
 hipError_t launch_place(int dim, int real_bytes, StateArrays U, StateArrays S, CellLists lists,
-                        const uint32_t* cell_start, uint32_t N, int64_t* step, int inc_step,
-                        hipStream_t s);
+                        const uint32_t* cell_start, uint32_t N, const int64_t* step, int64_t* step_out,
+                        uint32_t* inv, hipStream_t s);
 // Velocity field (per-particle velocities, general Eq. 4): the pair sum with
 // per-pair harmonic means and the convective term, one lane per target.
 struct GenLaunch {
@@ -237,7 +238,9 @@ struct AdjGenLaunch {
     const uint32_t* cell_start;
     const void* lam_s;  // the vector the pass applies the operator to, in the snapshot's cell order
     const void* lam_id; // corrector pass: lambda^(n+1) in id order
-    void* lam_out;      // the pass's output in id order
+    void* lam_out;      // the pass's output in id order (null: not written)
+    void* lam_next;     // its output in the cell order of the next pass's state (null: not written),
+    const uint32_t* inv;  // where particle id is in that order
     double* gpart;
 };
 // passes: Euler (lambda + dt L lambda), and the predictor-corrector's two:

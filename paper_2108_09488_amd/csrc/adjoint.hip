@@ -741,9 +741,6 @@ int copy_state(const ade_ctx* c, const Snap& dst, const Snap& src) {
         hipLaunchKernelGGL(k_copy_snap_x, dim3((xitems + 255) / 256), dim3(256), 0, c->stream, a);
         HIPCHK(hipGetLastError());
     }
-    // the live state's records, where snapshots do not hold them
-    if (pl.general && !keeps_gen_rec(pl) && dst.C == c->S.C)
-        HIPCHK(launch_gen_rec(pl.dim, pl.real_bytes, c->S, N, c->stream));
     return ADE_OK;
 }
 
@@ -1003,90 +1000,136 @@ int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, c
     return reduce_to_host(c, L, parts, h_J, h_grad);
 }
 
-// The adjoint of a velocity field over snapshots of the whole state.
+// The adjoint of a velocity field over kept states.  A state is built where it is
+// kept: the checkpoint at the start of each segment but the last, and all states of
+// the last segment, by the forward run; the other states of a segment when the
+// reverse sweep comes to it.  (Copied from the context's own arrays, and with the
+// last segment run twice, a 128^2 adjoint of 60 steps made 68 more copies of two
+// launches and 22 more steps of four.)
+// The pass at a state hands lambda on in the order of the next pass's state, found
+// from the inverse order that the placement leaves in the kept state's unused
+// candidate records; 3D FP64 keeps none and gathers in a launch of its own.
 int adjoint_field(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, const double* d_xs, int32_t ns,
                   const void* d_obs, double* h_J, double* h_grad) {
     int rc = ADE_OK;
     const Plan& pl = c->plan;
     const uint32_t N = (uint32_t)pl.N;
     hipStream_t st = c->stream;
-    const Snap cur = live(c);
-    const int64_t nck = (nsteps + K - 1) / K;
+    const int64_t nck = (nsteps + K - 1) / K, last0 = (nck - 1) * K;
+    const bool pc = pl.integrator == ADE_PC;
     if ((size_t)kGenAdjBlock / 4 * (size_t)pl.list_cap * 8u > kPairLdsMax)
         return fail(ADE_EINVAL, "candidate lists of the adjoint do not fit in LDS");
 
-    // forward run with checkpoints
+    // the arrays of a kept state; records that it has no room for are those of the
+    // last build
+    auto kept = [&](const Snap& s) {
+        GenState g{snap_arrays(c, s), s.cs, (uint32_t)pl.ncell + 1, s.step, reinterpret_cast<uint32_t*>(s.rec)};
+        g.S.rec = nullptr;
+        if (!keeps_gen_rec(pl)) g.S.grec = c->S.grec;
+        return g;
+    };
+    // state n + 1 into `to` from state n, its half-step state into `half`
+    auto step = [&](const GenState& from, const GenState& half, const GenState& to) -> int {
+        if (!pc) {
+            if ((rc = run_gen(c, kModeStep, nullptr, from))) return rc;
+        } else {
+            if ((rc = run_gen(c, kModeHalf, nullptr, from)) || (rc = enqueue_build_into(c, half, nullptr))) return rc;
+            GenState mid = half;
+            mid.step = from.step;
+            if ((rc = run_gen(c, kModeFull, nullptr, mid))) return rc;
+        }
+        return enqueue_build_into(c, to, from.step);
+    };
+    const Snap first = last0 == 0 ? L.seg[0] : L.ck[0];
+    if ((rc = copy_state(c, first, live(c)))) return rc;
+    auto forward_home = [&](int64_t n) {
+        if (n == nsteps) return gen_live(c);
+        if (n >= last0) return kept(L.seg[(size_t)(n - last0)]);
+        return n % K == 0 ? kept(L.ck[(size_t)(n / K)]) : gen_live(c);
+    };
     for (int64_t n = 0; n < nsteps; ++n) {
-        if (n % K == 0 && (rc = copy_state(c, L.ck[(size_t)(n / K)], cur))) return rc;
-        if ((rc = enqueue_steps(c, 1))) return rc;
+        const GenState half = pc && n >= last0 ? kept(L.segh[(size_t)(n - last0)]) : gen_live(c);
+        if ((rc = step(forward_home(n), half, forward_home(n + 1)))) return rc;
     }
-    if ((rc = copy_state(c, L.ck[(size_t)nck], cur))) return rc;
     if ((rc = misfit_and_seed(c, L, c->S, d_xs, ns, d_obs, L.lam[0]))) return rc;
 
-    // lambda of id order in a snapshot's cell order
-    auto gather = [&](const StateArrays& S, const void* lam) -> int {
+    // lambda of id order in a state's cell order
+    auto gather = [&](const StateArrays& S, const void* lam, void* out) -> int {
         dim3 g((N + 255) / 256), b(256);
         if (pl.real_bytes == 4)
-            hipLaunchKernelGGL((k_adj_gather<float>), g, b, 0, st, S, (const float*)lam, N, (float*)L.lam_s);
+            hipLaunchKernelGGL((k_adj_gather<float>), g, b, 0, st, S, (const float*)lam, N, (float*)out);
         else
-            hipLaunchKernelGGL((k_adj_gather<double>), g, b, 0, st, S, (const double*)lam, N, (double*)L.lam_s);
+            hipLaunchKernelGGL((k_adj_gather<double>), g, b, 0, st, S, (const double*)lam, N, (double*)out);
         HIPCHK(hipGetLastError());
+        return ADE_OK;
+    };
+    // a pass at state `at` over `in` (its cell order); the output goes to next in
+    // the order that inv gives, and to `id` in id order
+    auto pass = [&](int mode, const GenState& at, const void* in, const void* lam_id, void* id, void* next,
+                    const uint32_t* inv) -> int {
+        AdjGenLaunch g;
+        g.plumes = c->plumes;
+        g.tiles = c->tiles;
+        g.ntiles = pl.ntiles;
+        g.list_cap = pl.list_cap;
+        g.S = at.S;
+        g.cell_start = at.cell_start;
+        g.lam_s = in;
+        g.lam_id = lam_id;
+        g.lam_out = id;
+        g.lam_next = inv ? next : nullptr;
+        g.inv = inv;
+        g.gpart = L.gpart;
+        HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, mode, g, kGenAdjBlock, st));
         return ADE_OK;
     };
 
     // reverse sweep, segment by segment
-    int li = 0;
-    const bool pc = pl.integrator == ADE_PC;
-    for (int64_t sgi = nck - 1; sgi >= 0; --sgi) {
-        const int64_t n0 = sgi * K, n1 = std::min<int64_t>(n0 + K, nsteps);
-        if ((rc = copy_state(c, cur, L.ck[(size_t)sgi]))) return rc;
-        for (int64_t n = n0; n < n1; ++n) {
-            if ((rc = copy_state(c, L.seg[(size_t)(n - n0)], cur))) return rc;
-            if (pc) {  // the step in its stages, keeping the half-step state
-                if ((rc = run_gen(c, kModeHalf, nullptr)) || (rc = enqueue_build(c, 0))) return rc;
-                if ((rc = copy_state(c, L.segh[(size_t)(n - n0)], cur))) return rc;
-                if ((rc = run_gen(c, kModeFull, nullptr)) || (rc = enqueue_build(c, 1))) return rc;
-            } else if ((rc = enqueue_steps(c, 1))) {
+    void* sorted[2] = {L.lam_s, L.lam[1]};  // Euler: lambda in cell order, in turn (id order: lam[0])
+    int li = 0;  // predictor-corrector: lambda in id order in lam[li], in cell order in lam_s
+    for (int64_t n0 = last0; n0 >= 0; n0 -= K) {
+        const int64_t n1 = std::min<int64_t>(n0 + K, nsteps);
+        auto home = [&](int64_t n) {
+            return kept(n == n0 && n0 != last0 ? L.ck[(size_t)(n0 / K)] : L.seg[(size_t)(n - n0)]);
+        };
+        auto half = [&](int64_t n) { return pc ? kept(L.segh[(size_t)(n - n0)]) : gen_live(c); };
+        if (n0 != last0) {
+            if (!keeps_gen_rec(pl)) HIPCHK(launch_gen_rec(pl.dim, pl.real_bytes, home(n0).S, N, st));
+            for (int64_t n = n0; n + 1 < n1; ++n)
+                if ((rc = step(home(n), half(n), home(n + 1)))) return rc;
+            if (pc && ((rc = run_gen(c, kModeHalf, nullptr, home(n1 - 1))) ||
+                       (rc = enqueue_build_into(c, half(n1 - 1), nullptr))))
                 return rc;
-            }
         }
+        bool ready = false;  // lambda is in the cell order of the next pass
         for (int64_t n = n1 - 1; n >= n0; --n) {
-            const Snap sn = L.seg[(size_t)(n - n0)];
-            const StateArrays Sa = snap_arrays(c, sn);
-            AdjGenLaunch ga;
-            ga.plumes = c->plumes;
-            ga.tiles = c->tiles;
-            ga.ntiles = pl.ntiles;
-            ga.list_cap = pl.list_cap;
-            ga.S = Sa;
-            ga.cell_start = sn.cs;
-            ga.lam_s = L.lam_s;
-            ga.lam_id = nullptr;
-            ga.lam_out = L.lam[1 - li];
-            ga.gpart = L.gpart;
+            const GenState at = home(n);
+            // state 0 was copied, without its inverse order
+            const uint32_t* inv = n > 0 ? at.inv : nullptr;
             if (pc) {
                 // y = L2 lambda at the half-step state (its own cells and
                 // order), then lambda^n = lambda + dt y + dt^2/2 L1 y here
-                const Snap sh = L.segh[(size_t)(n - n0)];
-                AdjGenLaunch gh = ga;
-                gh.S = snap_arrays(c, sh);
-                gh.cell_start = sh.cs;
-                gh.lam_out = L.y;
-                if ((rc = gather(gh.S, L.lam[li]))) return rc;
-                HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenHalf, gh, kGenAdjBlock, st));
-                if ((rc = gather(Sa, L.y))) return rc;
-                ga.lam_id = L.lam[li];
-                HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenFull, ga, kGenAdjBlock, st));
+                const GenState mid = half(n);
+                if (!ready && (rc = gather(mid.S, L.lam[li], L.lam_s))) return rc;
+                if ((rc = pass(kAdjGenHalf, mid, L.lam_s, nullptr, inv ? nullptr : L.y, L.y, inv))) return rc;
+                if (!inv && (rc = gather(at.S, L.y, L.lam_s))) return rc;
+                const uint32_t* inv_next = n > n0 ? half(n - 1).inv : nullptr;
+                if ((rc = pass(kAdjGenFull, at, inv ? L.y : L.lam_s, L.lam[li], L.lam[1 - li], L.lam_s, inv_next)))
+                    return rc;
+                li = 1 - li;
+                ready = inv_next != nullptr;
             } else {
-                if ((rc = gather(Sa, L.lam[li]))) return rc;
-                HIPCHK(launch_adjoint_gen(pl.dim, pl.real_bytes, pl.kernel, kAdjGenEuler, ga, kGenAdjBlock, st));
+                if (!ready && (rc = gather(at.S, L.lam[0], sorted[0]))) return rc;
+                const uint32_t* inv_next = n - 1 > 0 && n > n0 ? home(n - 1).inv : nullptr;
+                if ((rc = pass(kAdjGenEuler, at, sorted[0], nullptr, inv_next ? nullptr : L.lam[0], sorted[1], inv_next)))
+                    return rc;
+                if (inv_next) std::swap(sorted[0], sorted[1]);
+                ready = inv_next != nullptr;
             }
-            HIPCHK(hipGetLastError());
-            li = 1 - li;
         }
     }
-    // leave the context at step nsteps
-    if ((rc = copy_state(c, cur, L.ck[(size_t)nck]))) return rc;
+    // the context is at step nsteps; its records, where the sweep made others
+    if (!keeps_gen_rec(pl) && nck > 1) HIPCHK(launch_gen_rec(pl.dim, pl.real_bytes, c->S, N, st));
     return reduce_to_host(c, L, pl.ntiles * kAdjMaxSubs, h_J, h_grad);
 }
 

@@ -769,9 +769,12 @@ int settle_lists(ade_ctx* c) {
 }
 
 // the same for the velocity-field pair kernel
-int run_gen(ade_ctx* c, int mode, void* out) {
+int run_gen(ade_ctx* c, int mode, void* out, const GenState& at) {
     const Plan& pl = c->plan;
     GenLaunch g = gen_args(c, out);
+    g.S = at.S;
+    g.cell_start = at.cell_start;
+    g.step = at.step;
     int rc = take_events(c, g.ev0, g.ev1);
     if (rc) return rc;
     HIPCHK(launch_pair_gen(pl.dim, pl.real_bytes, pl.kernel, mode, g, c->stream));
@@ -811,11 +814,17 @@ PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void
 }
 
 // counting sort of the hashed U buffer into S (cell order) and cell_start
-int enqueue_build(ade_ctx* c, int inc_step) {
+int enqueue_build(ade_ctx* c, int inc_step) { return enqueue_build_into(c, gen_live(c), inc_step ? c->step : nullptr); }
+
+GenState gen_live(const ade_ctx* c) {
+    return GenState{c->S, c->cell_start, (uint32_t)cell_pad(c->plan.ncell), c->step, nullptr};
+}
+
+int enqueue_build_into(ade_ctx* c, const GenState& to, const int64_t* step) {
     const Plan& pl = c->plan;
-    HIPCHK(launch_scan(c->lists, c->cell_start, (uint32_t*)c->scan_partial, (uint32_t)pl.ncell, c->stream));
-    HIPCHK(launch_place(pl.dim, pl.real_bytes, c->U, c->S, c->lists, c->cell_start, (uint32_t)pl.N, c->step,
-                        inc_step, c->stream));
+    HIPCHK(launch_scan(c->lists, to.cell_start, to.ncs, (uint32_t*)c->scan_partial, (uint32_t)pl.ncell, c->stream));
+    HIPCHK(launch_place(pl.dim, pl.real_bytes, c->U, to.S, c->lists, to.cell_start, (uint32_t)pl.N, step,
+                        step ? to.step : nullptr, to.inv, c->stream));
     return ADE_OK;
 }
 
@@ -861,12 +870,12 @@ int enqueue_steps(ade_ctx* c, int64_t n) {
         if (pl.general && pl.integrator == ADE_PC) {
             // velocity field, predictor-corrector: the corrector's positions
             // x^(1/2) have their own relative geometry, so they get a cell build
-            if ((rc = run_gen(c, kModeHalf, nullptr))) return rc;
+            if ((rc = run_gen(c, kModeHalf, nullptr, gen_live(c)))) return rc;
             if ((rc = enqueue_build(c, 0))) return rc;
-            if ((rc = run_gen(c, kModeFull, nullptr))) return rc;
+            if ((rc = run_gen(c, kModeFull, nullptr, gen_live(c)))) return rc;
             if ((rc = enqueue_build(c, 1))) return rc;
         } else if (pl.general) {  // velocity field: explicit Euler
-            if ((rc = run_gen(c, kModeStep, nullptr))) return rc;
+            if ((rc = run_gen(c, kModeStep, nullptr, gen_live(c)))) return rc;
             if ((rc = enqueue_build(c, 1))) return rc;
         } else if (pl.integrator == ADE_PC) {
             if ((rc = enqueue_uniform(c, c->S.C, c->S.rec, c->S.C, c->S.rec, true))) return rc;
@@ -1102,7 +1111,7 @@ int ade_rhs(ade_ctx* c, void* d_rhs) {
     if (!c || !d_rhs) return fail(ADE_EINVAL, "null argument");
     if (!c->built) return fail(ADE_ESTATE, "ade_rhs before ade_build_cells");
     const Plan& pl = c->plan;
-    if (pl.general) return run_gen(c, kModeRhs, d_rhs);
+    if (pl.general) return run_gen(c, kModeRhs, d_rhs, gen_live(c));
     int rc = settle_lists(c);
     if (rc) return rc;
     return run_pair(c, kModeRhs, pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, d_rhs, nullptr));

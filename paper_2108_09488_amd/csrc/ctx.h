@@ -131,11 +131,22 @@ inline const FrameStep* frame_of(const ade_ctx* c) {
 }
 // counting sort of the hashed U buffer into S and the cell-start table
 int enqueue_build(ade_ctx* c, int inc_step);
+// A velocity field's sorted state: the context's own, or one kept by the adjoint.
+struct GenState {
+    StateArrays S;
+    uint32_t* cell_start;
+    uint32_t ncs;   // entries of cell_start
+    int64_t* step;  // its step counter
+    uint32_t* inv;  // where particle id is in its order (null: not kept)
+};
+GenState gen_live(const ade_ctx* c);
+// the counting sort into `to`; its step counter becomes *step + 1 (step null: left)
+int enqueue_build_into(ade_ctx* c, const GenState& to, const int64_t* step);
 // n explicit steps (velocity field: pair sum, update and rebuild each)
 int enqueue_steps(ade_ctx* c, int64_t n);
 // launch arguments of the velocity-field pair kernel over the sorted state of c
 GenLaunch gen_args(ade_ctx* c, void* out);
 // enqueue the velocity-field pair kernel (timed when timing is on)
-int run_gen(ade_ctx* c, int mode, void* out);
+int run_gen(ade_ctx* c, int mode, void* out, const GenState& at);
 
 }  // namespace ade

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(256) void k_cscan_reduce(const uint4* __restrict__ 
 
 __global__ __launch_bounds__(256) void k_cscan_final(uint4* __restrict__ count,
                                                     const uint32_t* __restrict__ partial,
-                                                    uint4* __restrict__ cell_start, uint32_t direct) {
+                                                    uint4* __restrict__ cell_start, uint32_t nout, uint32_t direct) {
     __shared__ uint32_t lds[256 / kWave];
     const uint32_t pre = chunk_prefix(partial, direct, lds);
     const uint32_t j0 = (blockIdx.x * 256 + threadIdx.x) * kCellVec;
@@ -145,12 +145,20 @@ __global__ __launch_bounds__(256) void k_cscan_final(uint4* __restrict__ count,
         o.z = o.y + c[k].y;
         o.w = o.z + c[k].z;
         run = o.w + c[k].w;
-        cell_start[j0 + k] = o;
+        const uint32_t e = 4u * (j0 + k);
+        if (e + 4u <= nout) {
+            cell_start[j0 + k] = o;
+        } else {  // the last entries of a table without padding
+            uint32_t* cs = reinterpret_cast<uint32_t*>(cell_start);
+            if (e < nout) cs[e] = o.x;
+            if (e + 1u < nout) cs[e + 1u] = o.y;
+            if (e + 2u < nout) cs[e + 2u] = o.z;
+        }
         count[j0 + k] = make_uint4(0u, 0u, 0u, 0u);
     }
 }
 
-hipError_t launch_scan(CellLists lists, uint32_t* cell_start, uint32_t* partial, uint32_t ncell,
+hipError_t launch_scan(CellLists lists, uint32_t* cell_start, uint32_t nout, uint32_t* partial, uint32_t ncell,
                        hipStream_t s) {
     const uint32_t nchunks = (uint32_t)(cell_pad(ncell) / kCellChunk);
     uint4* cnt = reinterpret_cast<uint4*>(lists.count);
@@ -158,7 +166,7 @@ hipError_t launch_scan(CellLists lists, uint32_t* cell_start, uint32_t* partial,
     hipLaunchKernelGGL(k_cscan_reduce, dim3(nchunks), dim3(256), 0, s, cnt, partial, lists.ovf_count);
     if (!direct) hipLaunchKernelGGL((k_scan_prefix<uint32_t>), dim3(1), dim3(kPrefixBlock), 0, s, partial, nchunks);
     hipLaunchKernelGGL(k_cscan_final, dim3(nchunks), dim3(256), 0, s, cnt, partial,
-                       reinterpret_cast<uint4*>(cell_start), direct);
+                       reinterpret_cast<uint4*>(cell_start), nout, direct);
     return hipGetLastError();
 }
 
@@ -216,14 +224,14 @@ hipError_t launch_scan64(int64_t* data, uint32_t n, int64_t* partial, hipStream_
 // (and, for a cell of more than kBucket particles, the overflow list), so the sorted
 // order is a pure function of the positions.  Writes the sorted state S and
 // its candidate records (and, for a velocity field, its velocity and
-// tensor); advances the step counter if asked.
+// tensor), and if asked the step counter and where each particle went.
 // ---------------------------------------------------------------------------
 template <int DIM, typename real>
 __global__ __launch_bounds__(256) void k_place(StateArrays U, StateArrays S, CellLists L,
                                               const uint32_t* __restrict__ cell_start, uint32_t N,
-                                              int64_t* step, int inc_step) {
+                                              const int64_t* step, int64_t* step_out, uint32_t* inv) {
     const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (inc_step && i == 0) *step += 1;
+    if (step_out && i == 0) *step_out = *step + 1;
     if (i >= N) return;
     const uint32_t key = U.key[i];
     const uint32_t my = U.id[i];
@@ -255,7 +263,8 @@ __global__ __launch_bounds__(256) void k_place(StateArrays U, StateArrays S, Cel
     const real C = static_cast<const real*>(U.C)[i];
     static_cast<real*>(S.C)[d] = C;
     S.id[d] = my;
-    if (Rec<DIM, real>::kStageable) S.rec[d] = Rec<DIM, real>::pack(u[0], u[1], u[2], C);
+    if (inv) inv[my] = d;
+    if (Rec<DIM, real>::kStageable && S.rec) S.rec[d] = Rec<DIM, real>::pack(u[0], u[1], u[2], C);
     if (U.vel[0]) {  // velocity field: the particle's velocity and tensor travel with it
         real w[DIM + (DIM == 2 ? 3 : 6)];
 #pragma unroll
@@ -348,17 +357,17 @@ hipError_t launch_init(int dim, int real_bytes, const PlumeDev* plumes, const Ti
 }
 
 hipError_t launch_place(int dim, int real_bytes, StateArrays U, StateArrays S, CellLists lists,
-                        const uint32_t* cell_start, uint32_t N, int64_t* step, int inc_step,
-                        hipStream_t s) {
+                        const uint32_t* cell_start, uint32_t N, const int64_t* step, int64_t* step_out,
+                        uint32_t* inv, hipStream_t s) {
     dim3 g((N + 255) / 256), b(256);
     if (dim == 2 && real_bytes == 4)
-        hipLaunchKernelGGL((k_place<2, float>), g, b, 0, s, U, S, lists, cell_start, N, step, inc_step);
+        hipLaunchKernelGGL((k_place<2, float>), g, b, 0, s, U, S, lists, cell_start, N, step, step_out, inv);
     else if (dim == 2)
-        hipLaunchKernelGGL((k_place<2, double>), g, b, 0, s, U, S, lists, cell_start, N, step, inc_step);
+        hipLaunchKernelGGL((k_place<2, double>), g, b, 0, s, U, S, lists, cell_start, N, step, step_out, inv);
     else if (real_bytes == 4)
-        hipLaunchKernelGGL((k_place<3, float>), g, b, 0, s, U, S, lists, cell_start, N, step, inc_step);
+        hipLaunchKernelGGL((k_place<3, float>), g, b, 0, s, U, S, lists, cell_start, N, step, step_out, inv);
     else
-        hipLaunchKernelGGL((k_place<3, double>), g, b, 0, s, U, S, lists, cell_start, N, step, inc_step);
+        hipLaunchKernelGGL((k_place<3, double>), g, b, 0, s, U, S, lists, cell_start, N, step, step_out, inv);
     return hipGetLastError();
 }
 

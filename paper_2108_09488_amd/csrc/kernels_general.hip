@@ -653,19 +653,22 @@ __global__ __launch_bounds__(256) void k_adjoint_gen(AdjGenLaunch g) {
         // (L u)_a / vphi: 1/2 of the sum of Dcal terms = 2 al (al sums Dcal / 4)
         const real Lx = fmar(la * (real)(P.L * (1.0 / 4294967296.0)), cv, (real)2 * al);
         const uint32_t id = S.id[i];
+        real out;
         if (AMODE == kAdjGenEuler) {
-            static_cast<real*>(g.lam_out)[id] = fmar((real)sd, Lx, la);
+            out = fmar((real)sd, Lx, la);
             m = 2.0 * sd * (double)la;
         } else if (AMODE == kAdjGenHalf) {
-            static_cast<real*>(g.lam_out)[id] = (real)P.vphi * Lx;  // y = L lambda
+            out = (real)P.vphi * Lx;  // y = L lambda
             m = 2.0 * sd * (double)la;
         } else {
             // lambda + dt y + dt^2/2 L y, with la = y here
             const real lam = static_cast<const real*>(g.lam_id)[id];
             const real dt = (real)P.dt;
-            static_cast<real*>(g.lam_out)[id] = fmar(dt, la, fmar((real)(0.5 * P.dt * sd), Lx, lam));
+            out = fmar(dt, la, fmar((real)(0.5 * P.dt * sd), Lx, lam));
             m = P.dt * sd * (double)la;
         }
+        if (g.lam_out) static_cast<real*>(g.lam_out)[id] = out;
+        if (g.lam_next) static_cast<real*>(g.lam_next)[g.inv[id]] = out;
     }
 #pragma unroll
     for (int th = 0; th < 3; ++th) {

@@ -61,3 +61,42 @@ def test_records_follow_the_state(dim, rb, n_side, integrator):
         assert d.info()["step"] == a.info()["step"] == 5
         for c in (a, b, d):
             c.close()
+
+
+@pytest.mark.parametrize("integrator", [_lib.ADE_EULER, _lib.ADE_PC])
+@pytest.mark.parametrize("dim,rb,n_side", [(2, 4, 21), (2, 8, 16), (3, 4, 10), (3, 8, 9)])
+def test_field_adjoint_of_any_checkpoint_interval(dim, rb, n_side, integrator):
+    """The states that the adjoint keeps and runs again depend on the checkpoint
+    interval, what it computes does not: J, the gradient and the state it leaves
+    are the same bits for every interval, and the state is that of the steps."""
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    spec = I.config("cfg1" if dim == 2 else "cfg3", n_side=n_side, real_bytes=rb, h_over_dp=1.4, jitter=0.1,
+                    dt=2.0 ** -12)
+    x = spec.positions()
+    real = np.float32 if rb == 4 else np.float64
+    C = spec.concentration(x).astype(real)
+    v = I.velocity_field(x, spec.L, quantum=2.0 ** -20).astype(real).astype(np.float64)
+    xs = torch.from_numpy(np.ascontiguousarray(x[:, :7]))
+    obs = torch.full((7,), 0.25, dtype=torch.float32 if rb == 4 else torch.float64)
+    ctx = Context([params_from_spec(spec, integrator=integrator, flags=_lib.ADE_VELOCITY_FIELD)], [spec.n])
+
+    def start():
+        ctx.init(torch.from_numpy(x), torch.from_numpy(C)).set_velocities(torch.from_numpy(v)).build()
+
+    for nsteps in (1, 2, 5):
+        start()
+        ctx.step(nsteps)
+        want = (ctx.read_C().cpu().numpy(), ctx.read_x().cpu().numpy(), ctx.rhs().cpu().numpy())
+        first = None
+        for K in (nsteps, 1, 2, 3, 9):
+            print(f"[case] field adjoint dim={dim} rb={rb} integ={integrator} steps={nsteps} K={K}", flush=True)
+            start()
+            J, g = ctx.adjoint(nsteps, K, xs, obs)
+            assert ctx.info()["step"] == nsteps
+            for a, b in zip((ctx.read_C(), ctx.read_x(), ctx.rhs()), want):
+                assert np.array_equal(a.cpu().numpy(), b), (nsteps, K)
+            got = (J, *[float(t) for t in g])
+            first = first or got
+            assert got == first, (nsteps, K)
+            assert np.isfinite(got).all() and any(t != 0.0 for t in got[1:])
+    ctx.close()
