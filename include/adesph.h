@@ -120,12 +120,15 @@ typedef struct {
  * candidate for both.  The summation order, and so the last bits of the
  * result, depend on lanes and targets (and on whether the plume has neighbour
  * lists) and on nothing else here.  A new
- * context starts with the fewest lanes per particle that keep about 4
- * wavefronts per SIMD: block 64 with two targets per lane from 2^19
- * particles on, else 256 threads with 1 (from 2^18), 2 (from 2^17) or 4
- * lanes per target; a 3D context, or one with a plume of more than 2000
+ * context starts with 256 threads and 1 (from 2^18 particles), 2 (from 2^17) or 4
+ * lanes per target, about 4 wavefronts per SIMD; in FP32 with 32 or more expected
+ * neighbours per particle with block 128 and two targets per lane from 2^18 on,
+ * and with 80 or more with block 64 and 4 lanes per two targets between 2^17 and
+ * 2^19.  A 3D context, or one with a plume of more than 2000
  * expected neighbours per particle, starts with 4 lanes per two targets in
- * FP32 (block 64 in 3D, 128 in 2D) or per target in FP64, xcd_group 128;
+ * FP32 (block 128 in 2D and from 2^19 particles on, else 64; a 3D one of fewer
+ * than 2^17 particles with 256 threads and 4 lanes per target) or per target in
+ * FP64, xcd_group 128;
  * when the lists do not fit, the first of {256,2}, {256,4}, {128,4}, {64,4}
  * lanes per target, or block 64 with two targets per lane, that does. */
 typedef struct {
@@ -144,7 +147,8 @@ typedef struct {
  * particles each (host-only, pure).  For a uniform flow it has room for
  * neighbour lists: about 2 bytes (2D) or 4 bytes (3D) per neighbour and
  * particle with a margin, for plumes of at most 2000 expected neighbours per
- * particle; none when a context's lists would pass 16 GiB. */
+ * particle; none when a context's lists would pass 16 GiB, or in 2D when 2 bytes
+ * for each neighbour of each particle come to more than 384 MiB (768 MiB in FP64). */
 int ade_workspace_bytes(const ade_params *params, const int64_t *counts, int32_t nplumes,
                         size_t *bytes);
 
@@ -158,7 +162,8 @@ int ade_workspace_bytes(const ade_params *params, const int64_t *counts, int32_t
  * where the context's cell tables would pass the 160 MiB budget, since the
  * default x cells then widen for the whole context), the same lanes and
  * targets, and neighbour lists in both or in neither (a context whose lists
- * would pass 16 GiB keeps none): these fix the order of every sum. */
+ * would take too much, ade_workspace_bytes, keeps none): these fix the order of
+ * every sum. */
 int ade_create(const ade_params *params, const int64_t *counts, int32_t nplumes, void *d_ws,
                size_t ws_bytes, void *stream, ade_ctx **out);
 
@@ -182,8 +187,8 @@ int ade_init_particles(ade_ctx *ctx, const double *d_x, const void *d_C);
  * takes the launch shapes block {64, 128, 256} x lanes {1, 2, 4} with one
  * target per group of lanes, and in 2D FP32 also four lanes per two targets
  * (targets = 2), no persistent grid, through ade_set_tuning or ade_autotune.
- * A new context starts with 4 lanes per target in the largest block whose
- * lists fit, or in 2D FP32 with a plume of more than 2000 expected
+ * A new context starts with block 64 and 4 lanes per target, or in 2D FP32
+ * with a plume of more than 2000 expected
  * neighbours per particle with block 128 and four lanes per two targets.  A 2D FP32 velocity-field context holds at most 2^27 - 256
  * particles (its 32-byte candidate records take 32-bit byte offsets).
  * ade_adjoint takes it
@@ -198,8 +203,10 @@ int ade_set_velocities(ade_ctx *ctx, const double *d_v);
  * state is gathered into cell order.  Needed once after init.  A uniform flow
  * moves every particle of a plume by the same displacement, so the order and
  * the cells, taken in the plume's frame, hold for the whole run, and so do
- * the neighbour lists built with them, which the steps walk (a plume whose
- * lists do not fit their room walks the cells); a velocity field rebuilds its
+ * its neighbour lists, which the steps walk (a plume whose
+ * lists do not fit their room walks the cells); they are built here if the
+ * context's previous particles were stepped, else by the first call that steps,
+ * which then synchronises the stream.  A velocity field rebuilds its
  * cells every step.  For a uniform flow it also checks whether two particles of
  * a plume share a position (and synchronises the stream for that): the sum
  * of Eq. (4) leaves out pairs at r = 0, and when no two particles coincide
@@ -217,7 +224,8 @@ int ade_coincident(const ade_ctx *ctx, int32_t *out);
 
 /* nsteps explicit steps (pair sum of Eqs. 4-5, update of C and x; with a
  * velocity field the rebuild of the cells).  The state is in the same buffers
- * after every call, so a caller may capture the call into a graph of its own.
+ * after every call, so a caller may capture the call into a graph of its own
+ * (captured steps walk the cells, not the neighbour lists).
  * With ADE_CHECK_FINITE on any plume of the context, the concentrations are
  * checked after the last step (the stream is synchronised) and a NaN or an
  * infinity returns ADE_ENONFINITE (the steps have run). */
@@ -228,7 +236,7 @@ int ade_step(ade_ctx *ctx, int64_t nsteps);
 int ade_step_graph(ade_ctx *ctx, int64_t nsteps);
 
 /* rhs of Eq. (4) at the current state, written in particle-id order to
- * d_rhs (N reals). */
+ * d_rhs (N reals).  It walks the cells, also where steps walk neighbour lists. */
 int ade_rhs(ade_ctx *ctx, void *d_rhs);
 
 /* Current concentrations / positions in particle-id order. */

@@ -62,27 +62,38 @@ bool tuning_fits(const Plan& pl, const ade_tuning& t) {
     return pair_lds_bytes(t.block, t.lanes, tuning_list_cap(pl, t)) <= kPairLdsMax;
 }
 
-// default launch shape: the fewest lanes per particle that still give
-// the chip about 4 wavefronts per SIMD (4096 wavefronts of 64 lanes, i.e.
-// 2^18 lanes): two targets per lane from 2^19 particles on (the fastest
-// shape on the 2D sweep), one lane per target from 2^18, two lanes from
-// 2^17, else four; then the next shapes whose candidate lists fit in LDS.
-// Plumes of thousands of neighbours per particle, and 3D plumes, take
-// four lanes per target, or in FP32 four lanes per two neighbouring
-// targets: the targets of a wavefront then walk nearly the same candidate
-// ranges and share their cache lines, and a pair of targets shares every
-// record it fetches (the autotuner's choice on the 10^6-particle,
-// 31k-neighbour problem: 19.3 ms per pair launch against 22.8 ms for one
-// target a quad; on the 128^3 plume 0.88-0.90 ms against 0.90-0.92).
+// Default launch shape.  Below 2^18 particles the lanes per particle that give
+// the chip about 4 wavefronts per SIMD (2^18 lanes): four, and two from 2^17 on.
+// From there on, in FP32, a lane serves one target of few neighbours (the pair
+// launch at 12 and 28 neighbours: 16.2 and 27.1 us at 1024^2, two targets a lane
+// 20.4 and 28.7; the 256-plume ensemble 199 against 206) and two of more (50
+// neighbours: 13.5 against 14.5 us at 512^2, 38.2 against 44.5 at 1024^2); from 80 on
+// a quad of lanes serves two while there are fewer than 2^19 particles (113
+// neighbours: 24.2 against 25.9 us at 512^2, 16.8 against 18.3 at 384^2; at 1024^2 81
+// and 80).  FP64 takes one target a lane (1024^2, 50 neighbours: 62 against 67 us).
+// Plumes of thousands of neighbours per particle, and 3D plumes, take four lanes
+// per target, or in FP32 four lanes per two neighbouring targets: the targets of
+// a wavefront then walk nearly the same candidate ranges and share their cache
+// lines, and a pair of targets shares every record it fetches (10^6 particles,
+// 31k neighbours: 19.3 ms per pair launch against 22.8 ms for one target a quad;
+// 128^3 496 against 651 us).  A 3D plume of fewer than 2^17 particles has too few
+// pairs of targets to fill the chip (32^3: 8.1 us, in pairs 10.2), and from 2^19 on
+// workgroups of two wavefronts are 2% faster (96^3 212 against 217 us).
+// Then the next shapes whose candidate lists fit in LDS.
 bool default_tuning(const Plan& pl, ade_tuning& out) {
     const int64_t N = pl.N;
-    const bool quads = pl.nbar_max > 2000.0 || pl.dim == 3;
-    const int qtargets = pl.real_bytes == 4 ? 2 : 1;
-    const ade_tuning first = quads ? ade_tuning{pl.dim == 3 ? 64 : 128, 4, 128, 0, qtargets}
-                             : N >= (1 << 19) ? ade_tuning{64, 1, 0, 0, 2}
-                             : N >= (1 << 18) ? ade_tuning{256, 1, 0, 0, 1}
-                             : N >= (1 << 17) ? ade_tuning{256, 2, 0, 0, 1}
-                                              : ade_tuning{256, 4, 0, 0, 1};
+    double mean = 0.0;  // expected neighbours of a particle
+    for (int p = 0; p < pl.P; ++p) mean += pl.nbar[(size_t)p] * (double)pl.plumes[(size_t)p].n / (double)N;
+    const bool fp32 = pl.real_bytes == 4, dense = pl.nbar_max > 2000.0;
+    ade_tuning first;
+    if (dense) first = ade_tuning{128, 4, 128, 0, fp32 ? 2 : 1};
+    else if (pl.dim == 3 && fp32 && N < (1 << 17)) first = ade_tuning{256, 4, 0, 0, 1};
+    else if (pl.dim == 3) first = ade_tuning{fp32 && N >= (1 << 19) ? 128 : 64, 4, 128, 0, fp32 ? 2 : 1};
+    else if (N < (1 << 17)) first = ade_tuning{256, 4, 0, 0, 1};
+    else if (fp32 && mean >= 80.0 && N < (1 << 19)) first = ade_tuning{64, 4, 0, 0, 2};
+    else if (N < (1 << 18)) first = ade_tuning{256, 2, 0, 0, 1};
+    else if (fp32 && mean >= 32.0) first = ade_tuning{128, 1, 0, 0, 2};
+    else first = ade_tuning{256, 1, 0, 0, 1};
     const ade_tuning defaults[6] = {first, {256, 2, 0, 0, 1}, {256, 4, 0, 0, 1}, {128, 4, 0, 0, 1},
                                     {64, 4, 0, 0, 1}, {64, 1, 0, 0, 2}};
     bool ok = false;
@@ -117,10 +128,20 @@ bool default_tuning(const Plan& pl, ade_tuning& out) {
 // the expected entries (two targets share up to 1.31 times one's) and a margin;
 // a plume whose particles need more walks the row windows.
 constexpr size_t kListBudget = size_t(16) << 30;  // bytes; contexts whose lists would take more keep none
+// In 2D a step's reading of the lists has to stay near the 256 MB of the last-level
+// cache: with one target a group, 2 bytes per neighbour, the 256-plume ensemble reads
+// 290 MB a step and gains (235 -> 200 us), 2048^2 with 50 neighbours 420 MB and breaks
+// even (189, lists 191 us), with 113 neighbours 950 MB and loses (373, lists 410 us).
+// FP64 evaluates a pair at half the rate.
+constexpr double kListReadMax = 96.0 * 1048576.0;  // bytes a step per byte of the working precision
 
 ListPlan list_plan(const Plan& pl, int lanes, int targets) {
     ListPlan L;
     if (pl.general) return L;
+    double read = 0.0;  // bytes
+    for (int p = 0; p < pl.P; ++p)
+        if (pl.nbar[(size_t)p] <= 2000.0) read += 2.0 * pl.nbar[(size_t)p] * (double)pl.plumes[(size_t)p].n;
+    if (pl.dim == 2 && read > kListReadMax * (double)pl.real_bytes) return L;
     L.place.assign((size_t)pl.P, ListPlume{0u, 0u});
     for (int p = 0; p < pl.P; ++p) {
         const PlumeDev& d = pl.plumes[(size_t)p];
@@ -741,6 +762,8 @@ static int lists_built(ade_ctx* c, const std::vector<uint32_t>& flags) {
     if (full || !rest.empty()) HIPCHK(hipStreamSynchronize(c->stream));
     c->list_on = with;
     c->win_ntiles = (uint32_t)rest.size();
+    // a captured step holds the other kernels, or the tiles of other plumes
+    if (c->graph_lists != with || c->graph_tiles || !rest.empty()) drop_graph(c);
     return ADE_OK;
 }
 
@@ -757,12 +780,13 @@ int settle_lists(ade_ctx* c) {
             return ADE_OK;
         }
     }
+    c->list_used = true;
     if (c->list_shape != shape_of(c->tuning)) {
         std::vector<uint32_t> h;
-        HIPCHK(hipMemsetAsync(c->flags + 1, 0, sizeof(uint32_t) * (size_t)c->plan.P, c->stream));
+        if (c->list_shape != 0)
+            HIPCHK(hipMemsetAsync(c->flags + 1, 0, sizeof(uint32_t) * (size_t)c->plan.P, c->stream));
         int rc = enqueue_lists(c);
         if (rc || (rc = read_flags(c, h)) || (rc = lists_built(c, h))) return rc;
-        drop_graph(c);  // captured over other lists
     }
     c->list_use = c->list_on;
     return ADE_OK;
@@ -1001,11 +1025,13 @@ int ade_set_velocities(ade_ctx* c, const double* d_v) {
 }
 
 // What a build leaves to find out, the flags being zero (synchronises the
-// stream): whether two
-// particles of a plume share a position, and the neighbour lists.  With a
-// uniform flow every particle of a plume moves by the same displacement, so
-// both hold for the whole run; a velocity-field context keeps its own kernels
-// and is not checked.
+// stream): whether two particles of a plume share a position, and the neighbour
+// lists.  With a uniform flow every particle of a plume moves by the same
+// displacement, so both hold for the whole run; a velocity-field context keeps its
+// own kernels and is not checked.  The lists cost about two pair launches and only
+// steps read them, so they are built here, where their flags come with the same
+// synchronisation, when the context's last particles were stepped, and else by the
+// first call that reads them (settle_lists).
 static int after_build(ade_ctx* c) {
     const Plan& pl = c->plan;
     bool found = true;
@@ -1013,11 +1039,12 @@ static int after_build(ade_ctx* c) {
         std::vector<uint32_t> h;
         HIPCHK(launch_coincident(pl.dim, c->plumes, c->tiles, pl.ntiles, c->S, c->cell_start, c->flags,
                                  c->stream));
-        int rc = enqueue_lists(c);
-        if (rc || (rc = read_flags(c, h)) || (rc = lists_built(c, h))) return rc;
+        const bool lists = c->list_bytes > 0 && c->list_used;
+        c->list_used = false;
+        c->list_shape = 0;
+        int rc = lists ? enqueue_lists(c) : ADE_OK;
+        if (rc || (rc = read_flags(c, h)) || (lists && (rc = lists_built(c, h)))) return rc;
         found = h[0] != 0;
-        // a captured step holds the other kernels
-        if (c->graph_lists != c->list_on || c->win_ntiles > 0) drop_graph(c);
     }
     if (found != c->coincident) drop_graph(c);  // here too
     c->coincident = found;
@@ -1086,6 +1113,7 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
         HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         c->capturing = true;
         c->graph_lists = c->list_use;
+        c->graph_tiles = c->list_use && c->win_ntiles > 0;
         rc = enqueue_steps(c, kGraphSteps);
         c->capturing = false;
         hipGraph_t g = nullptr;
@@ -1112,8 +1140,9 @@ int ade_rhs(ade_ctx* c, void* d_rhs) {
     if (!c->built) return fail(ADE_ESTATE, "ade_rhs before ade_build_cells");
     const Plan& pl = c->plan;
     if (pl.general) return run_gen(c, kModeRhs, d_rhs, gen_live(c));
-    int rc = settle_lists(c);
-    if (rc) return rc;
+    // over the row windows: one launch does not pay for lists, and the sum is the
+    // same bits whether steps built them or not
+    c->list_use = false;
     return run_pair(c, kModeRhs, pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, d_rhs, nullptr));
 }
 

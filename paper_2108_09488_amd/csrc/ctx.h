@@ -93,7 +93,9 @@ struct ade_ctx {
     uint32_t win_ntiles = 0;
     bool list_on = false;    // some plume has lists
     bool list_use = false;   // the kernels of the current call read them
+    bool list_used = false;  // a call on the particles of the last build read them, or would have
     bool graph_lists = false;  // the captured steps read lists
+    bool graph_tiles = false;  // and walk the windows of win_tiles
     uint32_t h_total = 0;  // host copy of N for the cell-start sentinel
     bool initialized = false, built = false;
     // two particles of a plume share a position (the pair kernels then test

@@ -44,10 +44,14 @@ def _context(specs, xs, stream=None):
     (2, 8, 257, 5, 1.3), (3, 4, 13, 2, 1.7), (3, 4, 8, 0, 1.3), (3, 8, 9, 1, 1.5)])
 def test_rhs_of_every_shape(dim, rb, n_side, drop, hod):
     """Ragged last tiles (drop: particles left out at the end), whole tiles,
-    and plumes past 65536 particles."""
+    and plumes past 65536 particles: the right-hand side of a call, over the
+    row windows, and that of a step, over the lists, from one of a dt so long
+    that it outweighs C a hundred times."""
     spec = I.config("cfg2_h20_r10" if dim == 2 else "cfg3", n_side=n_side, real_bytes=rb, h_over_dp=hod,
                     v=(0.6, 0.8, 0.0))
     x = spec.positions()[:, :spec.n - drop]
+    C0 = spec.concentration(x)
+    spec.dt = float(100.0 * np.linalg.norm(C0) / np.linalg.norm(_oracle(spec, x, C0)))
     c, C = _context([spec], [x])
     ref = _oracle(spec, x, C)
     tol = 1e-5 if rb == 4 else 1e-12
@@ -60,6 +64,9 @@ def test_rhs_of_every_shape(dim, rb, n_side, drop, hod):
             continue  # its candidate lists do not fit in LDS
         print(f"[case] lists dim={dim} rb={rb} n={x.shape[1]} shape=({lanes},{targets})", flush=True)
         assert _rel(c.rhs().double().cpu().numpy(), ref) < tol, (lanes, targets)
+        c.step(1)
+        assert _rel((c.read_C().double().cpu().numpy() - C) / spec.dt, ref) < tol, (lanes, targets)
+        c.init(torch.from_numpy(x), torch.from_numpy(C)).build()
     c.close()
 
 
@@ -124,3 +131,28 @@ def test_captured_calls_walk_the_windows(dim, n_side):
             assert _rel(c.read_C().double().cpu().numpy(), eager) < 1e-6, (lanes, targets, k)
             c.set_tuning(block=64, lanes=lanes, targets=targets)
     c.close()
+
+
+def test_steps_of_the_graph_follow_the_lists():
+    """The captured steps of a context whose second plume now fits its lists and
+    now does not, each time as a fresh context runs them."""
+    stream = torch.cuda.Stream()
+    a = I.config("cfg2_h20_r10", n_side=40)
+    b = I.config("cfg2_h20_r10", n_side=48)
+    xs = {"lattice": b.positions(), "clustered": I.clustered(8, 2, 36, 0.02, b.L)[:, :b.n]}
+    assert xs["clustered"].shape == xs["lattice"].shape
+    ctx = None
+    for name in ("lattice", "clustered", "lattice", "lattice", "clustered", "clustered"):
+        print(f"[case] graph over {name}", flush=True)
+        if ctx is None:
+            ctx, C = _context([a, b], [a.positions(), xs[name]], stream)
+        else:
+            x = np.concatenate([a.positions(), xs[name]], axis=1)
+            C = np.concatenate([a.concentration(a.positions()), b.concentration(xs[name])])
+            ctx.init(torch.from_numpy(x), torch.from_numpy(C.astype(np.float32).astype(np.float64))).build()
+        fresh, _ = _context([a, b], [a.positions(), xs[name]], stream)
+        ctx.step_graph(20)
+        fresh.step(20)
+        assert np.array_equal(ctx.read_C().cpu().numpy(), fresh.read_C().cpu().numpy())
+        fresh.close()
+    ctx.close()
