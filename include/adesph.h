@@ -231,7 +231,8 @@ int ade_coincident(const ade_ctx *ctx, int32_t *out);
  * infinity returns ADE_ENONFINITE (the steps have run). */
 int ade_step(ade_ctx *ctx, int64_t nsteps);
 
-/* The same steps replayed from a HIP graph holding 16 captured steps, the rest
+/* The same steps replayed from a HIP graph holding 16 captured steps (a uniform
+ * flow: from 512 steps on), the rest
  * launched one by one (the finite check as for ade_step, after them all). */
 int ade_step_graph(ade_ctx *ctx, int64_t nsteps);
 

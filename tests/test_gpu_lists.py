@@ -135,7 +135,8 @@ def test_captured_calls_walk_the_windows(dim, n_side):
 
 def test_steps_of_the_graph_follow_the_lists():
     """The captured steps of a context whose second plume now fits its lists and
-    now does not, each time as a fresh context runs them."""
+    now does not, each time as a fresh context runs them (a run long enough for the
+    graph)."""
     stream = torch.cuda.Stream()
     a = I.config("cfg2_h20_r10", n_side=40)
     b = I.config("cfg2_h20_r10", n_side=48)
@@ -151,8 +152,8 @@ def test_steps_of_the_graph_follow_the_lists():
             C = np.concatenate([a.concentration(a.positions()), b.concentration(xs[name])])
             ctx.init(torch.from_numpy(x), torch.from_numpy(C.astype(np.float32).astype(np.float64))).build()
         fresh, _ = _context([a, b], [a.positions(), xs[name]], stream)
-        ctx.step_graph(20)
-        fresh.step(20)
+        ctx.step_graph(515)
+        fresh.step(515)
         assert np.array_equal(ctx.read_C().cpu().numpy(), fresh.read_C().cpu().numpy())
         fresh.close()
     ctx.close()
