@@ -5,9 +5,9 @@ Workload (default, the headline): the 3D plume -- 128^3 = 2,097,152 particles
 on a lattice jittered by +-0.1 dp, Wendland C4, h = 2 dp (support H = 4 dp,
 ~256 neighbours), alpha_L = 1e-2, alpha_T = 1e-3, D_m = 1e-6, v = (1, 0, 0),
 FP32 state, explicit Euler steps of 5e-5.  One bench step is one step of the
-plume (pair sum of Eqs. 4-5 fused with the update of C and x and the hashing
-of the moved particles, then the cell-list rebuild), replayed from the HIP
-graph of one captured step, inputs resident in HBM.  value = the directed
+plume: the pair sum of Eqs. 4-5 over the neighbour lists fused with the update
+of C; x moves with the plume's frame, in which the cells and the lists of the
+build hold.  Inputs resident in HBM.  value = the directed
 interactions of a step (pairs b != a with 0 < r <= H) times the steps,
 divided by the wall time of the timed region.
 
@@ -42,7 +42,8 @@ FLOPS_PER_INTERACTION_FIELD = {2: 57}
 PEAK_FP32_VECTOR_TFLOPS = 157.3      # MI355X published vector FP32 (packed FMA)
 TRAFFIC_PROFILE = os.path.join(ROOT, "profiles", "pair_kernel_traffic.md")
 TRAFFIC_PROFILE_3D = os.path.join(ROOT, "profiles", "pair_kernel_traffic_3d.md")
-PAIR_SOURCES = ["kernels_pair.hip", "ade_walk.h", "ade_geom.h", "ade_device.h", "ade_internal.h"]
+PAIR_SOURCES = ["kernels_list.hip", "ade_list.h", "ade_pair.h", "kernels_pair.hip", "ade_walk.h", "ade_geom.h",
+                "ade_device.h", "ade_internal.h"]
 PEAK_FP32_NONPACKED_TFLOPS = 78.6    # 256 CU x 4 SIMD x 16 lanes x 2.4 GHz x 2 (FMA)
 # single-issue VALU roof: 256 CU x 64 lanes x 2.4 GHz lane-slots per second, and
 # the issue slots one directed interaction needs (the pair term's operations,
@@ -55,8 +56,18 @@ def valu_issue_frac(dim, interactions, seconds):
     return ISSUE_SLOTS_PER_INTERACTION[dim] * interactions / seconds / VALU_SLOTS_PER_S
 
 
+def list_kernel_name(tuning, dim=2, coincident=False):
+    """The update-mode pair kernel of a launch shape over neighbour lists (FP32,
+    Wendland C4), which the steps of a uniform flow walk; with two targets a
+    list the last template argument as for the row windows."""
+    targets = tuning.get("targets", 1)
+    zc = "true" if coincident and targets == 2 else "false"
+    return f"k_pair_list<{dim}, float, 4, 0, {tuning['lanes']}, {targets}, {zc}>"
+
+
 def step_kernel_name(tuning, dim=2, coincident=False):
-    """The update-mode pair kernel a launch shape runs (FP32, Wendland C4;
+    """The update-mode pair kernel a launch shape runs over row windows (plumes
+    without neighbour lists, captured calls; FP32, Wendland C4;
     the last template argument: whether it tests every candidate for r > 0,
     which it does only in a context where two particles share a position)."""
     zc = "true" if coincident else "false"
@@ -200,7 +211,7 @@ def batched(device, steps, warmup, n_plumes=256):
             "plain_same_nbar": {"workload": "one 512^2 plume, h/dp 1.5, C4, FP32, graph replay",
                                 "neighbours_mean": rinter / ref.n, "interactions_per_s": plain},
             "vs_plain_same_nbar": rate / plain,
-            "roofline": roofline_alu(2, inter, pms / pn, step_kernel_name(tuned, coincident=coincident), pn)}
+            "roofline": roofline_alu(2, inter, pms / pn, list_kernel_name(tuned, coincident=coincident), pn)}
 
 
 def fwd_adjoint(device):
@@ -319,7 +330,7 @@ def headline_3d(device, steps, warmup, shape=None):
     cells = c.info()["cells"]
     coincident = c.coincident()
     c.close()
-    kernel = step_kernel_name(tuned, dim=3, coincident=coincident)
+    kernel = list_kernel_name(tuned, dim=3, coincident=coincident)
     return {"spec": s, "interactions_per_step": inter, "tuning": tuned, "wall": wall, "cells": cells,
             "eager": {"ms_per_step": 1e3 * ewall / steps, "interactions_per_s": inter * steps / ewall,
                       "pair_kernel_ms_per_step": ms / n},
@@ -642,7 +653,7 @@ def main():
         ewall, pair = time_sweep(sweep, args.steps, args.warmup, graph=False)
         coincident = sweep["ctx"].coincident()
         sweep["ctx"].close()
-        kname = step_kernel_name(sweep["tuning"], coincident=coincident)
+        kname = list_kernel_name(sweep["tuning"], coincident=coincident)
         extras["sweep"] = {
             "workload": "2D consistency sweep: 6 plumes x 512^2 particles, jitter 0.1 dp, Wendland C4, "
                         "h/dp {1.3,2,3} x alpha_L/alpha_T {10,100}, FP32, explicit Euler, dt Eq. (10), "
@@ -693,7 +704,7 @@ def main():
         "data": "synthetic",
         "config": {"workload": "3D plume: 128^3 particles, jitter 0.1 dp, Wendland C4, h = 2 dp (support 4 dp), "
                                "alpha_L 1e-2, alpha_T 1e-3, D_m 1e-6, v = (1, 0, 0), FP32 state, explicit Euler, "
-                               "dt 5e-5, graph-replayed steps",
+                               "dt 5e-5",
                    "particles": s3.n, "interactions_per_step": inter3,
                    "neighbours_mean": inter3 / s3.n, "cells": h["cells"], "tuning": h["tuning"]},
         "roofline": h["roofline"],

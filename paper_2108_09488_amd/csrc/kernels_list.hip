@@ -14,7 +14,7 @@
 // and 67%).  The list costs 2 bytes (2D) or 4 (3D) per entry and launch.
 // Measured per update launch against the row windows: 128^3 plume (256
 // neighbours) 870 -> 475 us, the six-plume sweep 96 -> 68 us, the 256-plume
-// ensemble 235 -> 207 us, a 512^2 plume (46 neighbours) 24 -> 13.6 us; the build
+// ensemble 235 -> 201 us, a 512^2 plume (46 neighbours) 24 -> 13.5 us; the build
 // takes about two such launches.  Measured and not taken: the group's records
 // copied to LDS first with one target a group (3D 618 us, sweep 81 us, ensemble
 // 213 us: the copy's latency per workgroup outweighed the cheaper gathers), and
