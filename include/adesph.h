@@ -126,9 +126,9 @@ typedef struct {
  * and with 80 or more with block 64 and 4 lanes per two targets between 2^17 and
  * 2^19.  A 3D context, or one with a plume of more than 2000
  * expected neighbours per particle, starts with 4 lanes per two targets in
- * FP32 (block 128 in 2D and from 2^19 particles on, else 64; a 3D one of fewer
- * than 2^17 particles with 256 threads and 4 lanes per target) or per target in
- * FP64, xcd_group 128;
+ * FP32 (block 256 in 2D, in 3D 128 from 2^19 particles on, else 64; a 2D one of
+ * fewer than 196608 particles, and a 3D one of fewer than 2^17, with 256 threads
+ * and 4 lanes per target) or per target in FP64, xcd_group 128;
  * when the lists do not fit, the first of {256,2}, {256,4}, {128,4}, {64,4}
  * lanes per target, or block 64 with two targets per lane, that does. */
 typedef struct {

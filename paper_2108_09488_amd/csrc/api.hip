@@ -75,8 +75,11 @@ bool tuning_fits(const Plan& pl, const ade_tuning& t) {
 // per target, or in FP32 four lanes per two neighbouring targets: the targets of
 // a wavefront then walk nearly the same candidate ranges and share their cache
 // lines, and a pair of targets shares every record it fetches (10^6 particles,
-// 31k neighbours: 19.3 ms per pair launch against 22.8 ms for one target a quad;
-// 128^3 496 against 651 us).  A 3D plume of fewer than 2^17 particles has too few
+// 31k neighbours: 19.2 ms per pair launch against 22.7 ms for one target a quad;
+// 128^3 496 against 651 us).  Dense 2D plumes take the largest workgroup (four
+// wavefronts walk nearly the same ranges: 400^2 with 5000 neighbours 0.57 ms, block
+// 128 0.67) and below 196608 particles, too few pairs to fill the chip, one target a
+// quad (300^2 with 7900 neighbours 0.54 against 0.65 ms; 500^2 with 15400 2.76 and 2.63).  A 3D plume of fewer than 2^17 particles has too few
 // pairs of targets to fill the chip (32^3: 8.1 us, in pairs 10.2), and from 2^19 on
 // workgroups of two wavefronts are 2% faster (96^3 212 against 217 us).
 // Then the next shapes whose candidate lists fit in LDS.
@@ -86,7 +89,9 @@ bool default_tuning(const Plan& pl, ade_tuning& out) {
     for (int p = 0; p < pl.P; ++p) mean += pl.nbar[(size_t)p] * (double)pl.plumes[(size_t)p].n / (double)N;
     const bool fp32 = pl.real_bytes == 4, dense = pl.nbar_max > 2000.0;
     ade_tuning first;
-    if (dense) first = ade_tuning{128, 4, 128, 0, fp32 ? 2 : 1};
+    const int dtargets = fp32 && N >= 196608 ? 2 : 1;
+    if (dense && pl.dim == 2) first = ade_tuning{256, 4, 128, 0, dtargets};
+    else if (dense) first = ade_tuning{128, 4, 128, 0, fp32 ? 2 : 1};
     else if (pl.dim == 3 && fp32 && N < (1 << 17)) first = ade_tuning{256, 4, 0, 0, 1};
     else if (pl.dim == 3) first = ade_tuning{fp32 && N >= (1 << 19) ? 128 : 64, 4, 128, 0, fp32 ? 2 : 1};
     else if (N < (1 << 17)) first = ade_tuning{256, 4, 0, 0, 1};
@@ -94,7 +99,9 @@ bool default_tuning(const Plan& pl, ade_tuning& out) {
     else if (N < (1 << 18)) first = ade_tuning{256, 2, 0, 0, 1};
     else if (fp32 && mean >= 32.0) first = ade_tuning{128, 1, 0, 0, 2};
     else first = ade_tuning{256, 1, 0, 0, 1};
-    const ade_tuning defaults[6] = {first, {256, 2, 0, 0, 1}, {256, 4, 0, 0, 1}, {128, 4, 0, 0, 1},
+    // (a dense plume of rows so fine that 256 threads' lists do not fit)
+    const ade_tuning smaller = dense ? ade_tuning{128, 4, 128, 0, dtargets} : first;
+    const ade_tuning defaults[7] = {first, smaller, {256, 2, 0, 0, 1}, {256, 4, 0, 0, 1}, {128, 4, 0, 0, 1},
                                     {64, 4, 0, 0, 1}, {64, 1, 0, 0, 2}};
     bool ok = false;
     for (const ade_tuning& t : defaults)
