@@ -233,7 +233,8 @@ int ade_step(ade_ctx *ctx, int64_t nsteps);
 
 /* The same steps replayed from a HIP graph holding 16 captured steps (a uniform
  * flow: from 512 steps on), the rest
- * launched one by one (the finite check as for ade_step, after them all). */
+ * launched one by one (the finite check as for ade_step, after them all).  A call
+ * that the caller captures launches every step, as ade_step does. */
 int ade_step_graph(ade_ctx *ctx, int64_t nsteps);
 
 /* rhs of Eq. (4) at the current state, written in particle-id order to

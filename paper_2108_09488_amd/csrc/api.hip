@@ -774,19 +774,21 @@ static int lists_built(ade_ctx* c, const std::vector<uint32_t>& flags) {
     return ADE_OK;
 }
 
+// whether a caller captures the context's stream into a graph of its own
+static bool in_capture(const ade_ctx* c) {
+    if (!c->stream) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone) return false;
+    (void)hipGetLastError();
+    return true;
+}
+
 // The lists belong to the particles and the launch shape of their build.  A
 // caller's own graph of the call may be replayed after either changed, so a
 // call under capture walks the row windows instead.
 int settle_lists(ade_ctx* c) {
     c->list_use = false;
-    if (c->plan.general || c->list_bytes == 0) return ADE_OK;
-    if (c->stream) {
-        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(c->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) {
-            (void)hipGetLastError();
-            return ADE_OK;
-        }
-    }
+    if (c->plan.general || c->list_bytes == 0 || in_capture(c)) return ADE_OK;
     c->list_used = true;
     if (c->list_shape != shape_of(c->tuning)) {
         std::vector<uint32_t> h;
@@ -1119,11 +1121,13 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
     if (!c->built) return fail(ADE_ESTATE, "ade_step_graph before ade_build_cells");
     if (!c->stream) return fail(ADE_EINVAL, "graph capture needs a non-default stream");
     // the graph holds kGraphSteps steps (an even number: the state ends where
-    // it began); short runs, and the rest, are launched one by one
+    // it began); short runs, and the rest, are launched one by one, and so is
+    // every step of a call that a caller captures: the graph's steps may read
+    // neighbour lists, which the replays of the caller's graph would outlive
     int64_t left = nsteps;
     int rc = settle_lists(c);
     if (rc) return rc;
-    const bool graph = nsteps >= (c->plan.general ? kGraphSteps : kUniformGraphFrom);
+    const bool graph = nsteps >= (c->plan.general ? kGraphSteps : kUniformGraphFrom) && !in_capture(c);
     if (graph && !c->graph_exec) {
         HIPCHK(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
         c->capturing = true;
