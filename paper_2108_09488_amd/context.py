@@ -250,6 +250,7 @@ class Context:
         check(lib().ade_adjoint_workspace_bytes(self._h, int(nsteps), int(ckpt_every), xs.shape[1],
                                                 ct.byref(nb)))
         ws = torch.empty(max(nb.value, 256), dtype=torch.uint8, device=self.device)
+        self._inputs_ready(xs, obs, ws)
         J = ct.c_double()
         g = (ct.c_double * 3)()
         check(lib().ade_adjoint(self._h, int(nsteps), int(ckpt_every), _ptr(xs), xs.shape[1],
