@@ -54,6 +54,7 @@ class Context:
         self.ws_bytes = nb.value
         self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
+        self._inputs_ready(self.ws)  # memory that work on the current stream may still use
         h = ct.c_void_p()
         check(L.ade_create(self._params, self._counts, self.nplumes, _ptr(self.ws),
                            self.ws_bytes, ct.c_void_p(self.stream.cuda_stream), ct.byref(h)))

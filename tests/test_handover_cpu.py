@@ -59,6 +59,15 @@ def _context(own):
     return spec, M.Context([M.params_from_spec(spec)], [spec.n], device="cpu", stream=own)
 
 
+def test_workspace_of_a_context(fake):
+    """A context's workspace may be a block that work on the current stream still
+    uses, and ade_create writes to it at once."""
+    log, _, own = fake
+    _, c = _context(own)
+    waited, recorded = _handed_over(log, "ade_create")
+    assert waited and c.ws.data_ptr() in recorded
+
+
 def test_inputs_of_the_adjoint(fake):
     """Sensors, observations and the workspace of the adjoint."""
     log, _, own = fake
