@@ -49,3 +49,33 @@ def test_a_captured_call_takes_nothing_from_the_contexts_graph():
         assert np.array_equal(c.read_x().cpu().numpy(), xe)
         assert np.linalg.norm(c.read_C().cpu().numpy() - eager) <= 2e-12 * np.linalg.norm(eager)
     c.close()
+
+
+def test_read_outs_captured_on_another_stream():
+    """A caller's capture on a stream that is not the context's takes the context's
+    read-outs in, and they follow the context's state from replay to replay: the
+    bits of the eager calls."""
+    spec, c, x, C = _uniform(torch.cuda.Stream(), rb=4)
+    c.init(torch.from_numpy(x), torch.from_numpy(C)).build().step(2)
+    xs = torch.from_numpy(I.sensors(30, [0.1, 0.1], [0.9, 0.9])).cuda()
+
+    def read():
+        return [c.rhs(), c.read_C(), c.read_x(), c.mass(), c.conc_range(), c.sensor_interp(xs)]
+
+    read()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        outs = read()
+    for k in range(3):
+        print(f"[case] captured read-outs, replay {k}", flush=True)
+        c.step(k + 1)
+        if k == 1:
+            c.init(torch.from_numpy(np.ascontiguousarray(x[:, ::-1])), torch.from_numpy(C)).build()
+        eager = [t.cpu().numpy() for t in read()]
+        torch.cuda.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(outs, eager):
+            assert np.array_equal(a.cpu().numpy(), b)
+    c.close()
