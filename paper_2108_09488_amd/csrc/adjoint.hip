@@ -137,6 +137,51 @@ __global__ __launch_bounds__(256) void k_sensor_fwd(const PlumeDev* __restrict__
     if (den) den[s] = dsum;
 }
 
+// One lane per sensor, for many sensors (kWaveSensors32): the same terms in the same
+// order.
+template <int DIM, typename real, int KERN>
+__global__ __launch_bounds__(256) void k_sensor_lane(const PlumeDev* __restrict__ plumes,
+                                                    const double* __restrict__ xs, int ns,
+                                                    StateArrays S, const FrameStep* __restrict__ frame,
+                                                    const uint32_t* __restrict__ cs,
+                                                    real* __restrict__ pred, real* __restrict__ den) {
+    const int s = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+    if (s >= ns) return;
+    const PlumeDev P = plumes[0];
+    uint32_t u[3] = {0u, 0u, 0u};
+    for (int c = 0; c < DIM; ++c) u[c] = to_fixed<DIM>(xs[(size_t)c * ns + s], P.L) - frame_shift(P, frame, c);
+    const Target T = make_target<DIM>(P, u[0], u[1], u[2]);
+    const real H2 = h2_of<real>(P), invHu = (real)P.invHu;
+    const uint32_t* px = S.pos[0];
+    const uint32_t* py = S.pos[1];
+    const uint32_t* pz = S.pos[2];
+    const real* C = static_cast<const real*>(S.C);
+    const int span = 2 * P.R + 1, noff = (DIM == 3) ? span * span : span;
+    real num = 0, dsum = 0;
+    for (int j = 0; j < noff; ++j) {
+        const RowRanges r = row_ranges<DIM>(P, cs, T, j, span);
+        for (int part = 0; part < 2; ++part) {
+            const uint32_t b0 = part ? r.s1 : r.s0, b1 = part ? r.e1 : r.e0;
+            for (uint32_t b = b0; b < b1; ++b) {
+                const real dx = (real)(int32_t)(T.ux - px[b]);
+                const real dy = (real)(int32_t)(T.uy - py[b]);
+                const real dz = (DIM == 3) ? (real)(int32_t)(T.uz - pz[b]) : (real)0;
+                real r2 = dx * dx;
+                r2 = fmar(dy, dy, r2);
+                if (DIM == 3) r2 = fmar(dz, dz, r2);
+                if (r2 <= H2) {
+                    real fa, fb;
+                    kernel_factors<real, KERN>(sqrt(r2), invHu, fa, fb);
+                    num = fmar(fa * fb, C[b], num);
+                    dsum = fmar(fa, fb, dsum);
+                }
+            }
+        }
+    }
+    pred[s] = dsum > (real)0 ? num / dsum : (real)0;
+    if (den) den[s] = dsum;
+}
+
 // residual weights r_s = 2 (C_s - d_s) / sum_b W_sb and J (FP64, fixed order)
 template <typename real>
 __global__ __launch_bounds__(256) void k_sensor_resid(int ns, const real* __restrict__ pred,
@@ -778,13 +823,26 @@ int check_sensor_args(const ade_ctx* c, const double* d_xs, int32_t ns) {
     return ADE_OK;
 }
 
+// Sensors up to which each has a wavefront; more have a lane each.  A sensor's
+// wavefront costs the same however many there are (it lists the rows with few of its
+// lanes and adds 64 terms one after the other), a kernel of lanes takes the time of the
+// slowest lane until they fill the chip.  The two are equal at about 20000 sensors
+// (FP32, 64^2 to 512^2: 16384 sensors 23 and 28 us with 16 neighbours, 43 and 49 with
+// 46; 32768 39 and 27, 81 and 59; a million-particle or a 3D plume at 33000 to 40000),
+// in FP64 at 11000 (512^2: 8192 sensors 43 and 50 us, 16384 78 and 68; 3D 16000);
+// 262144 sensors of 46 neighbours 604 and 214 us, in FP64 1160 and 225.
+constexpr int kWaveSensors32 = 20480, kWaveSensors64 = 10240;
+
 int launch_sensor_fwd(ade_ctx* c, const double* d_xs, int32_t ns, const StateArrays& S,
                       const uint32_t* cs, void* pred, void* den) {
     const Plan& pl = c->plan;
-    dim3 g((ns + 3) / 4), b(256);
+    const bool lane = ns > (pl.real_bytes == 4 ? kWaveSensors32 : kWaveSensors64);
+    dim3 g(lane ? (ns + 255) / 256 : (ns + 3) / 4), b(256);
 #define CALL(D, R, K)                                                                        \
-    hipLaunchKernelGGL((k_sensor_fwd<D, R, K>), g, b, 0, c->stream, c->plumes, d_xs, ns, S, frame_of(c), cs, \
-                       (R*)pred, (R*)den)
+    do {                                                                                     \
+        auto kern = lane ? k_sensor_lane<D, R, K> : k_sensor_fwd<D, R, K>;                   \
+        hipLaunchKernelGGL(kern, g, b, 0, c->stream, c->plumes, d_xs, ns, S, frame_of(c), cs, (R*)pred, (R*)den); \
+    } while (0)
     ADE_DISPATCH3(pl.dim, pl.real_bytes, pl.kernel, CALL);
 #undef CALL
     HIPCHK(hipGetLastError());
