@@ -222,6 +222,12 @@ int ade_build_cells(ade_ctx *ctx);
  * ADE_VELOCITY_FIELD contexts), else 0. */
 int ade_coincident(const ade_ctx *ctx, int32_t *out);
 
+/* The plumes with neighbour lists: *built those whose lists for the current
+ * particles and launch shape stand, *read those whose lists the last call that
+ * evaluated pair sums (ade_step, ade_step_graph, ade_rhs, ade_adjoint, ade_autotune)
+ * walked, 0 after a build.  Host state only: neither waits for the stream. */
+int ade_lists(const ade_ctx *ctx, int32_t *built, int32_t *read);
+
 /* nsteps explicit steps (pair sum of Eqs. 4-5, update of C and x; with a
  * velocity field the rebuild of the cells).  The state is in the same buffers
  * after every call, so a caller may capture the call into a graph of its own

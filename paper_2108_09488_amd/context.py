@@ -224,6 +224,13 @@ class Context:
         check(lib().ade_coincident(self._h, ct.byref(v)))
         return bool(v.value)
 
+    def lists(self) -> dict:
+        """The plumes whose neighbour lists stand for the current particles and
+        launch shape (built) and whose lists the last call of pair sums walked (read)."""
+        b, r = ct.c_int32(), ct.c_int32()
+        check(lib().ade_lists(self._h, ct.byref(b), ct.byref(r)))
+        return {"built": b.value, "read": r.value}
+
     def timing_start(self):
         """Start HIP-event timing of the pair kernel launches."""
         check(lib().ade_kernel_timing(self._h, 1, None, None))

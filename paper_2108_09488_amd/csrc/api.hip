@@ -1056,7 +1056,7 @@ static int after_build(ade_ctx* c) {
         HIPCHK(launch_coincident(pl.dim, c->plumes, c->tiles, pl.ntiles, c->S, c->cell_start, c->flags,
                                  c->stream));
         const bool lists = c->list_bytes > 0 && c->list_used;
-        c->list_used = false;
+        c->list_used = c->list_use = false;
         c->list_shape = 0;
         int rc = lists ? enqueue_lists(c) : ADE_OK;
         if (rc || (rc = read_flags(c, h)) || (lists && (rc = lists_built(c, h)))) return rc;
@@ -1077,6 +1077,16 @@ int ade_build_cells(ade_ctx* c) {
     if (rc) return rc;
     c->built = true;
     return after_build(c);
+}
+
+int ade_lists(const ade_ctx* c, int32_t* built, int32_t* read) {
+    if (!c || !built || !read) return fail(ADE_EINVAL, "null argument");
+    int32_t n = 0;
+    if (c->list_on && c->list_shape == shape_of(c->tuning))
+        for (const ListPlume& q : c->lists_of.place) n += q.rows != 0;
+    *built = n;
+    *read = c->list_use ? n : 0;
+    return ADE_OK;
 }
 
 int ade_coincident(const ade_ctx* c, int32_t* out) {

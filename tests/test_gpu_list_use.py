@@ -1,0 +1,161 @@
+"""Which calls walk neighbour lists, and which plumes have them (ade_lists): the
+checks of test_gpu_lists.py hold just as well where nothing but row windows is
+walked."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2108_09488_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(1, 1), (2, 1), (4, 1), (1, 2), (4, 2)]
+
+
+def _context(specs, xs, stream=None):
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    c = Context([params_from_spec(s) for s in specs], [x.shape[1] for x in xs], stream=stream)
+    return _init(c, specs, xs)
+
+
+def _init(c, specs, xs):
+    x = np.concatenate(xs, axis=1)
+    C = np.concatenate([s.concentration(v) for s, v in zip(specs, xs)])
+    return c.init(torch.from_numpy(x), torch.from_numpy(C)).build()
+
+
+@pytest.mark.parametrize("dim,rb,n_side,drop,hod", [
+    (2, 4, 23, 0, 1.3), (2, 4, 16, 1, 2.0), (2, 8, 16, 0, 1.5), (2, 8, 33, 3, 2.5), (2, 4, 300, 0, 1.5),
+    (2, 8, 257, 5, 1.3), (3, 4, 13, 2, 1.7), (3, 4, 8, 0, 1.3), (3, 8, 9, 1, 1.5)])
+def test_lattices_keep_lists_in_every_shape(dim, rb, n_side, drop, hod):
+    """The plumes of test_gpu_lists.py: every launch shape (in FP64 but four lanes to
+    two targets) is accepted, steps read the lists and right-hand sides do not.  In the
+    smallest 3D plume the pairs of targets at the ends of rows of 9 are too far apart
+    for their room, so two targets a lane walk the row windows there."""
+    from paper_2108_09488_amd import _lib
+    spec = I.config("cfg2_h20_r10" if dim == 2 else "cfg3", n_side=n_side, real_bytes=rb, h_over_dp=hod,
+                    v=(0.6, 0.8, 0.0))
+    x = spec.positions()[:, :spec.n - drop]
+    c = _context([spec], [x])
+    for lanes, targets in SHAPES:
+        if (lanes, targets, rb) == (4, 2, 8):
+            with pytest.raises(_lib.AdeError):
+                c.set_tuning(block=64, lanes=lanes, targets=targets)
+            continue
+        c.set_tuning(block=64, lanes=lanes, targets=targets)
+        print(f"[case] list use dim={dim} rb={rb} n={x.shape[1]} shape=({lanes},{targets})", flush=True)
+        assert c.lists() == {"built": 0, "read": 0}
+        n = 0 if (n_side, targets) == (9, 2) else 1
+        c.step(3)
+        assert c.lists() == {"built": n, "read": n}, (lanes, targets)
+        c.rhs()
+        assert c.lists() == {"built": n, "read": 0}, (lanes, targets)
+        c.step(1)
+        assert c.lists() == {"built": n, "read": n}, (lanes, targets)
+        _init(c, [spec], [x])
+        assert c.lists()["read"] == 0
+    c.close()
+
+
+def _squeezed(spec):
+    """The lattice of half the side in a corner of the box: four times the expected
+    neighbours, more than the lists have room for."""
+    return I.quantize(0.5 * spec.positions(), spec.L)
+
+
+def _oracle(spec, x, C):
+    return O.rhs(O.model_from_spec(spec), x, C, v_uniform=spec.velocity(), mass=spec.mass, rho=spec.rho0)
+
+
+@pytest.mark.parametrize("rb", [4, 8])
+def test_particles_without_room_walk_the_windows(rb):
+    """Of a lattice and a squeezed plume the first keeps lists, together and alone;
+    each evolves as it does alone, bit for bit, and its step is the oracle's within
+    the bounds of test_gpu_lists.py."""
+    a = I.config("cfg2_h20_r10", n_side=40, real_bytes=rb)
+    b = I.config("cfg2_h20_r10", n_side=48, real_bytes=rb)
+    for s, x in ((a, a.positions()), (b, _squeezed(b))):
+        C = s.concentration(x)
+        s.dt = float(100.0 * np.linalg.norm(C) / np.linalg.norm(_oracle(s, x, C)))
+    P, Q = (a, a.positions()), (b, _squeezed(b))
+    for lanes, targets in [(4, 1), (1, 2), (2, 1)]:
+        alone = {}
+        for key, plumes, n in (("a", [P], 1), ("b", [Q], 0), ("ab", [P, Q], 1), ("bab", [Q, P, Q], 1)):
+            print(f"[case] without room rb={rb} shape=({lanes},{targets}) {key}", flush=True)
+            c = _context([s for s, _ in plumes], [x for _, x in plumes])
+            c.set_tuning(block=64, lanes=lanes, targets=targets)
+            before = c.read_C().double().cpu().numpy()
+            c.step(1)
+            one = c.read_C().double().cpu().numpy()
+            c.step(3)
+            assert c.lists() == {"built": n, "read": n}
+            last = c.read_C().cpu().numpy()
+            c.close()
+            off = 0
+            for which, (s, x) in zip(key, plumes):
+                sl = slice(off, off + x.shape[1])
+                off += x.shape[1]
+                if len(key) == 1:
+                    alone[which] = last
+                    got, ref = (one - before) / s.dt, _oracle(s, x, before)
+                    assert np.linalg.norm(got - ref) < (1e-5 if rb == 4 else 1e-12) * np.linalg.norm(ref)
+                assert np.array_equal(last[sl], alone[which]), (key, lanes, targets)
+
+
+def test_the_graph_follows_the_lists():
+    """Runs long enough for the graph of a context whose second plume now has
+    lists and now has not, each as a fresh context steps them."""
+    stream = torch.cuda.Stream()
+    a = I.config("cfg2_h20_r10", n_side=24)
+    b = I.config("cfg2_h20_r10", n_side=32)
+    xs = {"lattice": b.positions(), "squeezed": _squeezed(b)}
+    ctx = _context([a, b], [a.positions(), xs["lattice"]], stream)
+    for name in ("lattice", "squeezed", "lattice", "lattice", "squeezed", "squeezed"):
+        print(f"[case] graph over {name}", flush=True)
+        _init(ctx, [a, b], [a.positions(), xs[name]])
+        ctx.step_graph(515)
+        n = 2 if name == "lattice" else 1
+        assert ctx.lists() == {"built": n, "read": n}
+        fresh = _context([a, b], [a.positions(), xs[name]], stream)
+        fresh.step(515)
+        assert np.array_equal(ctx.read_C().cpu().numpy(), fresh.read_C().cpu().numpy())
+        fresh.close()
+    ctx.close()
+
+
+@pytest.mark.parametrize("dim,n_side", [(2, 40), (3, 13)])
+def test_captured_calls_read_none(dim, n_side):
+    """Under capture no list is read, whether lists stand or not, in any shape."""
+    stream = torch.cuda.Stream()
+    spec = I.config("cfg2_h20_r10" if dim == 2 else "cfg3", n_side=n_side, h_over_dp=1.5)
+    c = _context([spec], [spec.positions()], stream)
+    for lanes, targets in SHAPES:
+        c.set_tuning(block=64, lanes=lanes, targets=targets)
+        for stand in (0, 1):
+            if stand:
+                c.step(3)
+            torch.cuda.synchronize()
+            g = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(g, stream=stream):
+                c.step(3)
+                assert c.lists() == {"built": stand, "read": 0}
+            del g
+    c.close()
+
+
+def test_velocity_fields_and_dense_plumes_have_none():
+    from paper_2108_09488_amd import _lib
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    spec = I.config("cfg2_h20_r10", n_side=24)
+    x = spec.positions()
+    c = Context([params_from_spec(spec, flags=_lib.ADE_VELOCITY_FIELD)], [spec.n])
+    c.init(torch.from_numpy(x), torch.from_numpy(spec.concentration(x)))
+    c.set_velocities(torch.ones(2, spec.n, dtype=torch.float64)).build().step(3)
+    assert c.lists() == {"built": 0, "read": 0}
+    c.close()
+    dense = I.config("cfg2_h20_r10", n_side=90, h_over_dp=14.0)
+    c = _context([dense], [dense.positions()])
+    c.step(3)
+    assert c.lists() == {"built": 0, "read": 0}
+    c.close()
