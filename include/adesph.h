@@ -161,9 +161,9 @@ int ade_workspace_bytes(const ade_params *params, const int64_t *counts, int32_t
  * alone when both runs have the same cell grid (cell_rows, and cell_xsub
  * where the context's cell tables would pass the 160 MiB budget, since the
  * default x cells then widen for the whole context), the same lanes and
- * targets, and neighbour lists in both or in neither (a context whose lists
- * would take too much, ade_workspace_bytes, keeps none): these fix the order of
- * every sum. */
+ * targets, and neighbour lists read by the same steps (a context whose lists
+ * would take too much, ade_workspace_bytes, keeps none; the first two steps of a
+ * large one, ade_step): these fix the order of every sum. */
 int ade_create(const ade_params *params, const int64_t *counts, int32_t nplumes, void *d_ws,
                size_t ws_bytes, void *stream, ade_ctx **out);
 
@@ -204,10 +204,10 @@ int ade_set_velocities(ade_ctx *ctx, const double *d_v);
  * moves every particle of a plume by the same displacement, so the order and
  * the cells, taken in the plume's frame, hold for the whole run, and so do
  * its neighbour lists, which the steps walk (a plume whose
- * lists do not fit their room walks the cells); they are built here if the
- * context's previous particles were stepped, else by the first call that steps,
- * which then synchronises the stream.  A velocity field rebuilds its
- * cells every step.  For a uniform flow it also checks whether two particles of
+ * lists do not fit their room walks the cells); they are built by the first call
+ * that reads them, which then synchronises the stream, or here if the steps of the
+ * context's last two sets of particles read them and it has at most 2^24 expected
+ * pairs.  A velocity field rebuilds its cells every step.  For a uniform flow it also checks whether two particles of
  * a plume share a position (and synchronises the stream for that): the sum
  * of Eq. (4) leaves out pairs at r = 0, and when no two particles coincide
  * the only candidate at r = 0 is a target's own record, whose term is zero,
@@ -231,7 +231,11 @@ int ade_lists(const ade_ctx *ctx, int32_t *built, int32_t *read);
 /* nsteps explicit steps (pair sum of Eqs. 4-5, update of C and x; with a
  * velocity field the rebuild of the cells).  The state is in the same buffers
  * after every call, so a caller may capture the call into a graph of its own
- * (captured steps walk the cells, not the neighbour lists).
+ * (captured steps walk the cells, not the neighbour lists).  In a uniform-flow
+ * context of 2^20 or more pairs (particles times expected neighbours) a call that
+ * ends at most two Euler steps, or one step of ADE_PC, behind the build walks the
+ * cells too, since so few steps do not pay for lists; its last bits are then those
+ * of the order of the cells, and not of a call of more steps.
  * With ADE_CHECK_FINITE on any plume of the context, the concentrations are
  * checked after the last step (the stream is synchronised) and a NaN or an
  * infinity returns ADE_ENONFINITE (the steps have run). */

@@ -1055,6 +1055,7 @@ int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, c
     }
     // leave the context at step nsteps (the forward run counted its steps)
     HIPCHK(launch_set_state(pl.dim, pl.real_bytes, c->S, state(nsteps), N, st));
+    c->since += nsteps;
     return reduce_to_host(c, L, parts, h_J, h_grad);
 }
 

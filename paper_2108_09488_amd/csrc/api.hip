@@ -246,7 +246,7 @@ int plan_grid(const ade_params* params, const int64_t* counts, int32_t nplumes, 
     pl.nbar.clear();
     pl.tiles.clear();
     pl.list_cap = pl.list_cap_pair = 0;
-    pl.nbar_max = 0.0;
+    pl.nbar_max = pl.pairs = 0.0;
     uint64_t N = 0, cbase = 0;
     for (int p = 0; p < nplumes; ++p) {
         const ade_params& q = params[p];
@@ -423,6 +423,7 @@ int plan_grid(const ade_params* params, const int64_t* counts, int32_t nplumes, 
         pl.list_cap_pair = std::max(pl.list_cap_pair, list_cap_pair_for(pl.dim, span));
         pl.plumes.push_back(d);
         pl.nbar.push_back(nbar);
+        pl.pairs += nbar * (double)d.n;
     }
     pl.N = (int64_t)N;
     pl.ncell = cbase;
@@ -783,12 +784,33 @@ static bool in_capture(const ade_ctx* c) {
     return true;
 }
 
+// Calls that lists do not pay for.  Building them takes about two launches of the
+// pair kernel over the row windows, so calls that end at most two launches behind the
+// step of the build walk the windows (new particles and one Euler step: 128^3 1708 us
+// with lists, 1110 without; 64^3 312 and 231; 2048^2 with 28 neighbours 689 and 408;
+// two steps 2166 and 1964, 367 and 362, 798 and 519; a third costs a window launch of
+// 870 us in 128^3, or the lists' 1440).  The rule counts from the build, not from the
+// call, so that a run stepped one by one has lists from its third launch on, and it
+// knows nothing but the state and the call, so that a loaded state continues as the
+// saved one.  The last bits of such a call differ from those of a longer one.  Below
+// 2^20 expected pairs, where the lists' build is a latency of some 20 us whatever its
+// size (new particles and one step: 128^2 117 us, 256^2 without lists 91), every step reads lists
+// and a run is the same bits in whatever calls it is made.
+constexpr double kWindowPairs = 1048576.0;
+constexpr int kWindowLaunches = 2;
+static bool few_launches(const ade_ctx* c, int64_t nsteps) {
+    const Plan& pl = c->plan;
+    if (nsteps == 0) return true;
+    if (nsteps < 0 || pl.pairs < kWindowPairs) return false;
+    return (double)(c->since + nsteps) * (pl.integrator == ADE_PC ? 2.0 : 1.0) <= (double)kWindowLaunches;
+}
+
 // The lists belong to the particles and the launch shape of their build.  A
 // caller's own graph of the call may be replayed after either changed, so a
 // call under capture walks the row windows instead.
-int settle_lists(ade_ctx* c) {
+int settle_lists(ade_ctx* c, int64_t nsteps) {
     c->list_use = false;
-    if (c->plan.general || c->list_bytes == 0 || in_capture(c)) return ADE_OK;
+    if (c->plan.general || c->list_bytes == 0 || in_capture(c) || few_launches(c, nsteps)) return ADE_OK;
     c->list_used = true;
     if (c->list_shape != shape_of(c->tuning)) {
         std::vector<uint32_t> h;
@@ -1023,6 +1045,7 @@ int ade_init_particles(ade_ctx* c, const double* d_x, const void* d_C) {
     c->built = false;
     c->vel_set = false;
     c->list_shape = 0;
+    c->since = 0;
     if (!c->coincident) drop_graph(c);
     c->coincident = true;  // until the cell build checks the new positions
     return ADE_OK;
@@ -1045,9 +1068,13 @@ int ade_set_velocities(ade_ctx* c, const double* d_v) {
 // lists.  With a uniform flow every particle of a plume moves by the same
 // displacement, so both hold for the whole run; a velocity-field context keeps its
 // own kernels and is not checked.  The lists cost about two pair launches and only
-// steps read them, so they are built here, where their flags come with the same
-// synchronisation, when the context's last particles were stepped, and else by the
-// first call that reads them (settle_lists).
+// steps read them, so they are built by the first call that reads them
+// (settle_lists).  A context whose last two sets of particles were stepped over
+// lists has them built here, where their flags come with the same synchronisation
+// (10 us less a set of particles), unless the build would cost more than that many
+// times over if these are not stepped: up to 2^24 expected pairs (512^2 with 50
+// neighbours: 25 us; 128^3 960 us).
+constexpr double kListAheadPairs = 16777216.0;
 static int after_build(ade_ctx* c) {
     const Plan& pl = c->plan;
     bool found = true;
@@ -1055,7 +1082,8 @@ static int after_build(ade_ctx* c) {
         std::vector<uint32_t> h;
         HIPCHK(launch_coincident(pl.dim, c->plumes, c->tiles, pl.ntiles, c->S, c->cell_start, c->flags,
                                  c->stream));
-        const bool lists = c->list_bytes > 0 && c->list_used;
+        c->list_runs = c->list_used ? std::min(c->list_runs + 1, 2) : 0;
+        const bool lists = c->list_bytes > 0 && c->list_runs == 2 && pl.pairs <= kListAheadPairs;
         c->list_used = c->list_use = false;
         c->list_shape = 0;
         int rc = lists ? enqueue_lists(c) : ADE_OK;
@@ -1120,8 +1148,9 @@ int ade_step(ade_ctx* c, int64_t nsteps) {
     if (!c) return fail(ADE_EINVAL, "null ctx");
     if (nsteps < 0) return fail(ADE_EINVAL, "nsteps must be >= 0");
     if (!c->built) return fail(ADE_ESTATE, "ade_step before ade_build_cells");
-    int rc = settle_lists(c);
+    int rc = settle_lists(c, nsteps);
     if (rc || (rc = enqueue_steps(c, nsteps))) return rc;
+    c->since += nsteps;
     return nsteps > 0 ? check_finite(c) : ADE_OK;
 }
 
@@ -1135,7 +1164,7 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
     // every step of a call that a caller captures: the graph's steps may read
     // neighbour lists, which the replays of the caller's graph would outlive
     int64_t left = nsteps;
-    int rc = settle_lists(c);
+    int rc = settle_lists(c, nsteps);
     if (rc) return rc;
     const bool graph = nsteps >= (c->plan.general ? kGraphSteps : kUniformGraphFrom) && !in_capture(c);
     if (graph && !c->graph_exec) {
@@ -1161,6 +1190,7 @@ int ade_step_graph(ade_ctx* c, int64_t nsteps) {
     }
     for (; graph && left >= kGraphSteps; left -= kGraphSteps) HIPCHK(hipGraphLaunch(c->graph_exec, c->stream));
     if ((rc = enqueue_steps(c, left))) return rc;
+    c->since += nsteps;
     return nsteps > 0 ? check_finite(c) : ADE_OK;
 }
 
@@ -1569,6 +1599,12 @@ int ade_load_state(ade_ctx* c, const void* h_buf, size_t bytes) {
     c->initialized = true;
     c->built = true;
     c->vel_set = true;
+    c->since = 0;
+    if (!pl.general && !first_form) {  // the state ends in (k, k0)
+        FrameStep f;
+        std::memcpy(&f, p - sizeof f, sizeof f);
+        c->since = f.k - f.k0;
+    }
     return after_build(c);
 }
 

@@ -31,6 +31,7 @@ struct Plan {
     int list_cap = 0;       // candidate-list entries per target (largest plume)
     int list_cap_pair = 0;  // the same for a lane's merged list of two targets
     double nbar_max = 0.0;  // largest expected neighbours per particle of a plume
+    double pairs = 0.0;     // expected neighbours of all particles
     bool general = false;   // velocity field: per-particle velocities (ADE_VELOCITY_FIELD)
     bool check_finite = false;  // ADE_CHECK_FINITE on any plume
     std::vector<PlumeDev> plumes;
@@ -88,12 +89,14 @@ struct ade_ctx {
     ade::ListPlume* lplumes = nullptr;
     ade::TileDev* win_tiles = nullptr;  // tiles of the plumes without lists, when some plumes have them
     ade::ListPlan lists_of;  // the lists that are there
-    int list_shape = 0;      // launch shape (lists_shape) they, or their absence, were settled for; 0: not since the build
+    int list_shape = 0;      // launch shape (shape_of) they, or their absence, were settled for; 0: not since the build
     int place_shape = 0;     // launch shape lplumes holds the places of (0: none)
     uint32_t win_ntiles = 0;
     bool list_on = false;    // some plume has lists
     bool list_use = false;   // the kernels of the current call read them
     bool list_used = false;  // a call on the particles of the last build read them, or would have
+    int list_runs = 0;       // sets of particles before these whose steps did, in a row (at most 2)
+    int64_t since = 0;       // steps the host launched since the step of the cells' build
     bool graph_lists = false;  // the captured steps read lists
     bool graph_tiles = false;  // and walk the windows of win_tiles
     uint32_t h_total = 0;  // host copy of N for the cell-start sentinel
@@ -115,9 +118,9 @@ struct ade_ctx {
 
 namespace ade {
 
-// settles whether the kernels of the call read neighbour lists, and builds
-// them for the current launch shape if they are not there
-int settle_lists(ade_ctx* c);
+// settles whether the kernels of a call of nsteps steps (-1: of another call) read
+// neighbour lists, and builds them for the current launch shape if they are not there
+int settle_lists(ade_ctx* c, int64_t nsteps = -1);
 // enqueue a pair kernel (timed when timing is on)
 int run_pair(ade_ctx* c, int mode, const PairLaunch& a);
 // launch arguments of a pair kernel over the sorted particles of c: rec the

@@ -159,3 +159,65 @@ def test_velocity_fields_and_dense_plumes_have_none():
     c.step(3)
     assert c.lists() == {"built": 0, "read": 0}
     c.close()
+
+
+def _cut(spec, integrator, load=False):
+    """A run of five steps one by one: the plumes with lists after each, and the
+    concentrations; load: every step in a context that loads the state before it."""
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    p = [params_from_spec(spec, integrator=integrator)]
+    c = _init(Context(p, [spec.n]), [spec], [spec.positions()])
+    built, out = [], []
+    c.step(0)
+    assert c.lists() == {"built": 0, "read": 0}
+    for _ in range(5):
+        if load:
+            d = Context(p, [spec.n])
+            d.load_state(c.save_state())
+            c.close()
+            c = d
+        c.step(1)
+        built.append(c.lists()["built"])
+        assert c.lists()["read"] == built[-1]
+        out.append(c.read_C().double().cpu().numpy())
+    c.close()
+    return built, out
+
+
+@pytest.mark.parametrize("dim,rb,n_side,integrator,first", [
+    (2, 4, 40, 1, 0), (2, 4, 160, 1, 2), (2, 8, 160, 1, 2), (2, 4, 160, 2, 1), (3, 4, 20, 1, 2), (3, 8, 20, 2, 1)])
+def test_the_first_launches_of_a_large_context(dim, rb, n_side, integrator, first):
+    """From 2^20 expected pairs on (160^2 with 50 neighbours, 20^3 with 268) the first
+    two pair launches walk the row windows; a state loaded in between goes on as the
+    saved one, to the same bits.  Against a run in one call the order of the sums of
+    two launches differs: 1e-6 relative L2 (FP64 1e-14)."""
+    spec = I.config("cfg2_h20_r10" if dim == 2 else "cfg3", n_side=n_side, real_bytes=rb, h_over_dp=2.0, jitter=0.1)
+    print(f"[case] first launches dim={dim} rb={rb} n_side={n_side} integrator={integrator}", flush=True)
+    built, out = _cut(spec, integrator)
+    assert built == [0] * first + [1] * (5 - first)
+    again, loaded = _cut(spec, integrator, load=True)
+    assert again == built
+    for a, b in zip(loaded, out):
+        assert np.array_equal(a, b)
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    c = _init(Context([params_from_spec(spec, integrator=integrator)], [spec.n]), [spec], [spec.positions()])
+    c.step(5)
+    assert c.lists() == {"built": 1, "read": 1}
+    one = c.read_C().double().cpu().numpy()
+    assert np.linalg.norm(one - out[-1]) <= (1e-6 if rb == 4 else 1e-14) * np.linalg.norm(one)
+    assert first > 0 or np.array_equal(one, out[-1])
+    c.close()
+
+
+@pytest.mark.parametrize("n_side,hod,ahead", [(40, 2.0, True), (200, 2.0, True), (512, 2.3, False)])
+def test_lists_are_built_ahead_after_two_runs(n_side, hod, ahead):
+    """With the cells, where the last two sets of particles were stepped over lists
+    and the context has at most 2^24 pairs; a set that was not stepped ends that."""
+    spec = I.config("cfg2_h20_r10", n_side=n_side, h_over_dp=hod)
+    x = spec.positions()
+    c = _context([spec], [x])
+    for steps, built in ((3, 0), (3, 0), (3, 1), (0, 1), (3, 0), (0, 0), (3, 0), (3, 0), (0, 1)):
+        assert c.lists()["built"] == (built if ahead else 0)
+        (c.step(steps) if steps else c.rhs())
+        _init(c, [spec], [x])
+    c.close()
