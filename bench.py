@@ -56,13 +56,15 @@ def valu_issue_frac(dim, interactions, seconds):
     return ISSUE_SLOTS_PER_INTERACTION[dim] * interactions / seconds / VALU_SLOTS_PER_S
 
 
-def list_kernel_name(tuning, dim=2, coincident=False):
+def list_kernel_name(tuning, dim=2, coincident=False, n=1 << 19):
     """The update-mode pair kernel of a launch shape over neighbour lists (FP32,
     Wendland C4), which the steps of a uniform flow walk; with two targets a
-    list the last template argument as for the row windows."""
+    list the last template argument as for the row windows, and in 2D another mode
+    in contexts of n < 2^19 particles (the second target's exact separations)."""
     targets = tuning.get("targets", 1)
     zc = "true" if coincident and targets == 2 else "false"
-    return f"k_pair_list<{dim}, float, 4, 0, {tuning['lanes']}, {targets}, {zc}>"
+    mode = 4 if dim == 2 and targets == 2 and n < 1 << 19 else 0
+    return f"k_pair_list<{dim}, float, 4, {mode}, {tuning['lanes']}, {targets}, {zc}>"
 
 
 def step_kernel_name(tuning, dim=2, coincident=False):

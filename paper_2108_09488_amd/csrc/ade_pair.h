@@ -115,7 +115,7 @@ __device__ __forceinline__ void finish_target(const PairLaunch& a, const PlumeDe
     // the kernel factor's constant and the bracket's sign S (the pair term
     // sums S times the bracket)
     const double kS = kPolyScale<KERN> * P.dterm[4];
-    if (MODE == kModeRhs) {
+    if ((MODE & ~kModeExact) == kModeRhs) {
         static_cast<real*>(a.out)[a.sid[i]] = (real)(kS * P.vphi) * acc;
         return;
     }

@@ -856,6 +856,16 @@ PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void
     a.persistent = c->tuning.persistent;
     a.xcd_group = c->tuning.xcd_group > 0 ? (uint32_t)c->tuning.xcd_group : 32u;
     a.zc = c->coincident ? 1 : 0;
+    // Two targets in 2D FP32 below 2^19 particles: the second target's separations
+    // from its own integers, as one target a group forms them, and not from the
+    // first's with a rounding more, which put the right-hand side 13% further off
+    // (380^2, 113 neighbours: 8.36e-7 relative L2 against 64 bits, 7.32e-7 exact, one
+    // target a quad 7.42e-7; 512^2, 50 neighbours 1.440e-6, 1.391e-6, 1.391e-6).  It
+    // costs 1 to 3% of a launch over lists and 1 to 6% over windows (512^2 14.5 and
+    // 14.7 us, 380^2 rhs 26.6 and 27.9).  Larger contexts keep the cheaper form, whose
+    // error is the same there to 0.1% (1024^2, 50 neighbours; with 113 0.7%) and whose
+    // cost is 3 to 5%, and so do dense plumes (5 to 7%).
+    a.exact = c->plan.dim == 2 && c->plan.real_bytes == 4 && c->plan.N < (1 << 19) && c->plan.nbar_max <= 2000.0;
     a.rec = rec;
     for (int d = 0; d < 3; ++d) a.spos[d] = c->S.pos[d];
     a.sid = c->S.id;

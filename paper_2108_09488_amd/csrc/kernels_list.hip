@@ -282,7 +282,10 @@ __device__ __forceinline__ void list_item(const PairLaunch& a, const PlumeDev* _
             const real dy = (real)(int32_t)(T0.y - c.y);
             const real dz = (DIM == 3) ? (real)(int32_t)(T0.z - c.z) : (real)0;
             term.sep(dx, dy, dz, T0.C, c.C, true, acc0);
-            if (T == 2) term.sep(dx + bx, dy + by, dz + bz, T1.C, c.C, keep, acc1);
+            if constexpr ((MODE & kModeExact) != 0)
+                term.sep((real)(int32_t)(T1.x - c.x), (real)(int32_t)(T1.y - c.y), (real)0, T1.C, c.C, keep, acc1);
+            else if (T == 2)
+                term.sep(dx + bx, dy + by, dz + bz, T1.C, c.C, keep, acc1);
         });
         if (second) {
             accB = acc0;
@@ -342,20 +345,31 @@ hipError_t launch_list(int dim, int real_bytes, const ListBuild& a, hipStream_t 
     return hipGetLastError();
 }
 
-template <int DIM, typename real, int KERN, int G, int T, bool ZC>
-static void launch_pair_list_s(int mode, const PairLaunch& a, hipStream_t s) {
+template <int DIM, typename real, int KERN, int G, int T, bool ZC, int X = 0>
+static void launch_pair_list_x(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t tpb = (uint32_t)a.block / G * T;
     const uint32_t nwork = a.ntiles * (kTile / tpb);
     PairLaunch c = a;
     if (nwork < 8) c.persistent = 0;  // a persistent grid needs a workgroup on every XCD
     const uint32_t grid = (c.persistent > 0) ? max(8u, min(nwork, (uint32_t)c.persistent)) : nwork;
     dim3 gr(grid), b(a.block);
-    auto kern = (mode == kModeRhs) ? k_pair_list<DIM, real, KERN, kModeRhs, G, T, ZC>
-                                   : k_pair_list<DIM, real, KERN, kModeStep, G, T, ZC>;
+    auto kern = (mode == kModeRhs) ? k_pair_list<DIM, real, KERN, kModeRhs + X, G, T, ZC>
+                                   : k_pair_list<DIM, real, KERN, kModeStep + X, G, T, ZC>;
     if (c.ev0)
         hipExtLaunchKernelGGL(kern, gr, b, 0u, s, c.ev0, c.ev1, 0u, c, c.plumes, nwork);
     else
         hipLaunchKernelGGL(kern, gr, b, 0, s, c, c.plumes, nwork);
+}
+
+template <int DIM, typename real, int KERN, int G, int T, bool ZC>
+static void launch_pair_list_s(int mode, const PairLaunch& a, hipStream_t s) {
+    if constexpr (T == 2 && DIM == 2 && sizeof(real) == 4) {
+        if (a.exact) {
+            launch_pair_list_x<DIM, real, KERN, G, T, ZC, kModeExact>(mode, a, s);
+            return;
+        }
+    }
+    launch_pair_list_x<DIM, real, KERN, G, T, ZC>(mode, a, s);
 }
 
 // one target a group: its list holds no record at r = 0 but the padding (the

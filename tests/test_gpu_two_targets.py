@@ -1,0 +1,34 @@
+"""Two targets a group of lanes in 2D FP32 contexts of fewer than 2^19 particles: the
+second target's separations are exact integer differences, as for one target."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2108_09488_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n_side,drop,hod,kernel", [(40, 0, 2.0, 4), (45, 3, 1.3, 2), (150, 1, 3.0, 4), (300, 0, 1.5, 4),
+                                                    (724, 0, 1.3, 4)])
+def test_two_targets_a_lane_sum_as_one(n_side, drop, hod, kernel):
+    """One lane sums its targets' candidates in the order of their rows, whether it
+    holds one target or two, and those that only the other target has add nothing:
+    the same bits, in right-hand sides (row windows) and steps (lists)."""
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    spec = I.config("cfg2_h20_r10", n_side=n_side, h_over_dp=hod, kernel=kernel, jitter=0.1, v=(0.6, 0.8, 0.0))
+    x = np.ascontiguousarray(spec.positions()[:, :spec.n - drop])
+    C = torch.from_numpy(spec.concentration(x).astype(np.float32))
+    c = Context([params_from_spec(spec)], [x.shape[1]])
+    outs = []
+    for targets in (1, 2):
+        print(f"[case] two targets n={x.shape[1]} hod={hod} kernel={kernel} targets={targets}", flush=True)
+        c.set_tuning(block=64, lanes=1, targets=targets)
+        c.init(torch.from_numpy(x), C).build()
+        r = c.rhs().cpu().numpy()
+        c.step(4)
+        assert c.lists() == {"built": 1, "read": 1}
+        outs.append((r, c.read_C().cpu().numpy()))
+    c.close()
+    assert np.array_equal(outs[0][0], outs[1][0])
+    assert np.array_equal(outs[0][1], outs[1][1])
