@@ -22,8 +22,7 @@
 //
 // Layout.  A wavefront's lists are `rows` rows of 64 words, one word per lane:
 // with two targets a group row 0 holds the entry counts of the lane's group, then
-// come the entries, which the group's lanes take in turn (entry p belongs to lane
-// p % G).  Every load of a row is coalesced; what is uniform, ListWave, comes
+// come the entries, which the group's lanes take in turn (entry_lane).  Every load of a row is coalesced; what is uniform, ListWave, comes
 // through the scalar unit.  2D: two 16-bit entries a word,
 // record numbers from the wavefront's base (a window of 65536 records around its
 // targets, modulo the plume's particles).  3D: one 32-bit byte offset a word (a
@@ -213,7 +212,7 @@ __global__ __launch_bounds__(64) void k_list(ListBuild a, const PlumeDev* __rest
                     const uint32_t first = quad_perm<G == 4 ? 0x00 : 0xA0>(lower);  // [0,0,0,0] / [0,0,2,2]
                     const uint32_t last = quad_perm<G == 4 ? 0xFF : 0xF5>(upto);    // [3,3,3,3] / [1,1,3,3]
                     const uint32_t p = m + lower - first;
-                    if (hit) put(p / G, (lane & ~(uint32_t)(G - 1)) + p % G, c.k);
+                    if (hit) put(p / G, (lane & ~(uint32_t)(G - 1)) + entry_lane<G>(p), c.k);
                     m += last - first;
                 }
             });
