@@ -130,7 +130,11 @@ typedef struct {
  * fewer than 196608 particles, and a 3D one of fewer than 2^17, with 256 threads
  * and 4 lanes per target) or per target in FP64, xcd_group 128;
  * when the lists do not fit, the first of {256,2}, {256,4}, {128,4}, {64,4}
- * lanes per target, or block 64 with two targets per lane, that does. */
+ * lanes per target, or block 64 with two targets per lane, that does.  Until a shape
+ * is set or tuned, launches that walk the cells and not neighbour lists (ade_rhs,
+ * captured steps, ade_step) take one target per lane or per two lanes in 2D FP32 contexts
+ * of fewer than 2^19 particles, and in larger ones with two targets per lane, or of
+ * 2^21 particles and more, block 64 with two targets per lane. */
 typedef struct {
     int32_t block;          /* threads per workgroup: 64, 128 or 256          */
     int32_t lanes;          /* lanes per target particle: 1, 2 or 4           */

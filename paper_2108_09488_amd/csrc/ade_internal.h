@@ -97,8 +97,8 @@ struct CellLists {
 // right-hand side; kModeHalf and kModeFull: the predictor and the corrector
 // of the velocity-field predictor-corrector step
 enum PairMode { kModeStep = 0, kModeHalf = 1, kModeRhs = 2, kModeFull = 3 };
-// added to the mode of a two-target kernel in 2D FP32: the second target's
-// separations as PairLaunch::exact has them
+// added to the mode of a two-target kernel over lists in 2D FP32: the second
+// target's separations as PairLaunch::exact has them
 constexpr int kModeExact = 4;
 
 // A uniform flow moves every particle of a plume by the same displacement
@@ -150,8 +150,8 @@ struct PairLaunch {
     int zc;                 // 1: two distinct particles may share a position, so every
                             // candidate is tested for r > 0; 0: the only candidate at
                             // r = 0 is the target's own record (FP32 C4 kernels skip the test)
-    int exact;              // 2D FP32: 1: both targets of a pair form their separations from
-                            // integers (kModeExact); 0: the second's from the first's
+    int exact;              // lists in 2D FP32: 1: both targets of a pair form their separations
+                            // from integers (kModeExact); 0: the second's from the first's
     const uint4* rec;       // candidate records (position + C of Cpair), or null: SoA reads
     const uint32_t* spos[3];
     const uint32_t* sid;

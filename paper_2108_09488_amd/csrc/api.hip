@@ -127,6 +127,30 @@ bool default_tuning(const Plan& pl, ade_tuning& out) {
     return true;
 }
 
+// The shape of launches over row windows (right-hand sides, captured calls, the first
+// steps of large contexts, plumes without lists) beside the default t of the lists, of a
+// uniform flow.  A 2D FP32 plume's windows gain less from a second target a group: each
+// lane has a candidate list of its own to build, half as many lanes stand ready to
+// hide that, and what is in reach of either target is walked for both.  Below 2^19
+// particles one target is as fast or faster (600^2 with 50 and 78 neighbours 27 and 39
+// us, two targets 30 and 44; 113 neighbours: 500^2 36.1 and 35.6, four lanes to two
+// targets) and its sum is closer to 64 bits (right-hand side of 380^2 with 113
+// neighbours 7.42e-7, two targets 8.36e-7); from there on two targets a lane take
+// workgroups of 64 threads (800^2 with 78 neighbours 53 us, of 128 threads 60), also
+// for few neighbours from 2^21 particles on (2048^2 with 21 and 28 neighbours 117 and
+// 135 us, one target 123 and 142; 900^2 31 and 37, one target 27 and 34).
+ade_tuning window_tuning(const Plan& pl, const ade_tuning& t) {
+    const int64_t N = pl.N;
+    if (pl.general || pl.dim != 2 || pl.real_bytes != 4 || pl.nbar_max > 2000.0) return t;
+    ade_tuning w = t;
+    if (N < (1 << 19)) {
+        if (targets_of(t) == 2) w = N < (1 << 18) ? ade_tuning{256, 2, 0, 0, 1} : ade_tuning{256, 1, 0, 0, 1};
+    } else if (targets_of(t) == 2 || N >= (1 << 21)) {
+        w = ade_tuning{64, 1, 0, 0, 2};
+    }
+    return tuning_fits(pl, w) ? w : t;
+}
+
 // Neighbour lists.  A plume keeps them when it has at most 2000 expected
 // neighbours per particle (beyond, its rows of H/4 hold 1.15 candidates per
 // neighbour, and a list entry per candidate costs more than it saves) and, in
@@ -668,6 +692,16 @@ static ListArrays list_arrays(const ade_ctx* c, const ListPlan& L) {
     q.pos = c->plan.dim == 3 && c->plan.real_bytes == 8 ? b.take<uint4>((size_t)c->plan.N) : nullptr;
     return q;
 }
+// the shape fields of a launch
+static void set_shape(const ade_ctx* c, PairLaunch& a, const ade_tuning& t) {
+    a.block = t.block;
+    a.lanes = t.lanes;
+    a.targets = targets_of(t);
+    a.list_cap = tuning_list_cap(c->plan, t);
+    a.persistent = t.persistent;
+    a.xcd_group = t.xcd_group > 0 ? (uint32_t)t.xcd_group : 32u;
+}
+
 static int shape_of(const ade_tuning& t) { return 4 * t.lanes + targets_of(t); }
 
 // launch a pair kernel; when timing is on, events stamped with the kernel's
@@ -681,6 +715,7 @@ int run_pair(ade_ctx* c, int mode, const PairLaunch& a) {
     HIPCHK(launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->stream));
     if (a.list && c->win_ntiles > 0) {  // the plumes without lists
         b.list = nullptr;
+        set_shape(c, b, c->window);
         b.step = nullptr;
         b.tiles = c->win_tiles;
         b.ntiles = c->win_ntiles;
@@ -849,22 +884,16 @@ PairLaunch pair_args(ade_ctx* c, const void* Cpair, const uint4* rec, const void
     a.plumes = c->plumes;
     a.tiles = c->pair_tiles;
     a.ntiles = c->plan.ntiles;
-    a.block = c->tuning.block;
-    a.lanes = c->tuning.lanes;
-    a.targets = targets_of(c->tuning);
-    a.list_cap = tuning_list_cap(c->plan, c->tuning);
-    a.persistent = c->tuning.persistent;
-    a.xcd_group = c->tuning.xcd_group > 0 ? (uint32_t)c->tuning.xcd_group : 32u;
+    set_shape(c, a, c->list_use ? c->tuning : c->window);
     a.zc = c->coincident ? 1 : 0;
     // Two targets in 2D FP32 below 2^19 particles: the second target's separations
     // from its own integers, as one target a group forms them, and not from the
-    // first's with a rounding more, which put the right-hand side 13% further off
-    // (380^2, 113 neighbours: 8.36e-7 relative L2 against 64 bits, 7.32e-7 exact, one
-    // target a quad 7.42e-7; 512^2, 50 neighbours 1.440e-6, 1.391e-6, 1.391e-6).  It
-    // costs 1 to 3% of a launch over lists and 1 to 6% over windows (512^2 14.5 and
-    // 14.7 us, 380^2 rhs 26.6 and 27.9).  Larger contexts keep the cheaper form, whose
-    // error is the same there to 0.1% (1024^2, 50 neighbours; with 113 0.7%) and whose
-    // cost is 3 to 5%, and so do dense plumes (5 to 7%).
+    // first's with a rounding more, which put the sum 13% further off (380^2, 113
+    // neighbours: 8.31e-7 relative L2 against 64 bits, 7.24e-7 exact, over windows with
+    // one target 7.34e-7; 512^2, 50 neighbours 1.442e-6, 1.394e-6, 1.394e-6).  It costs
+    // 1 to 3% of a launch (512^2 14.5 and 14.8 us, 380^2 18.1 and 18.5).  Larger
+    // contexts keep the cheaper form, whose error is the same there to 0.1% (1024^2, 50
+    // neighbours; with 113 0.7%) and which the exact one would slow by 3 to 5%.
     a.exact = c->plan.dim == 2 && c->plan.real_bytes == 4 && c->plan.N < (1 << 19) && c->plan.nbar_max <= 2000.0;
     a.rec = rec;
     for (int d = 0; d < 3; ++d) a.spos[d] = c->S.pos[d];
@@ -1023,6 +1052,8 @@ int ade_create(const ade_params* params, const int64_t* counts, int32_t nplumes,
     }
     Bump b(d_ws);
     layout(b, c, c->plan);
+    c->window = window_tuning(c->plan, c->tuning);
+    if (c->list_bytes == 0) c->tuning = c->window;
     if (b.off + 256 > ws_bytes) {
         delete c;
         return fail(ADE_EWORKSPACE, "workspace too small: need %zu bytes", b.off + 256);
@@ -1379,7 +1410,7 @@ int ade_autotune(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* best) {
     if (!c->built) return fail(ADE_ESTATE, "ade_autotune before ade_build_cells");
     if (c->plan.general) return autotune_gen(c, reps, flags, best);
     const Plan& pl = c->plan;
-    const ade_tuning start = c->tuning;
+    const ade_tuning start = c->tuning, window0 = c->window;
     const int blocks[3] = {64, 128, 256}, pers[2] = {0, 2048}, groups[3] = {8, 32, 128};
     // (lanes, targets): one lane per two targets, 1, 2, 4 lanes per target, or
     // four lanes per two targets (FP32; tuning_fits drops it for FP64)
@@ -1403,7 +1434,7 @@ int ade_autotune(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* best) {
     // the update-mode kernel, as a step runs it, to the second C buffer
     int rc = time_candidates(c, (int)cands.size(), reps, e0, e1,
                              [&](int k) {
-                                 c->tuning = cands[(size_t)k];
+                                 c->tuning = c->window = cands[(size_t)k];
                                  if (settle_lists(c) != ADE_OK) return hipErrorUnknown;
                                  PairLaunch a =
                                      pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, c->aux, c->aux_rec);
@@ -1415,6 +1446,9 @@ int ade_autotune(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* best) {
     hipEventDestroy(e0);
     hipEventDestroy(e1);
     c->tuning = rc ? start : cands[(size_t)kbest];
+    // (kept lanes are also those of the windows)
+    const bool keep = (flags & ADE_TUNE_KEEP_LANES) && shape_of(window0) != shape_of(start);
+    c->window = rc || keep ? window0 : c->tuning;
     drop_graph(c);
     if (rc) return rc;
     if (best) *best = c->tuning;
@@ -1445,7 +1479,7 @@ int ade_set_tuning(ade_ctx* c, const ade_tuning* t) {
                     t->block / t->lanes, pair_lds_bytes(t->block, t->lanes, tuning_list_cap(c->plan, *t)),
                     kPairLdsMax);
     if (t->persistent < 0 || t->persistent > 65536) return fail(ADE_EINVAL, "persistent in 0..65536");
-    c->tuning = *t;
+    c->tuning = c->window = *t;
     drop_graph(c);
     return ADE_OK;
 }

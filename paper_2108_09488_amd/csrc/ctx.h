@@ -55,8 +55,6 @@ struct ListPlan {
     std::vector<ListPlume> place;
 };
 ListPlan list_plan(const Plan& pl, int lanes, int targets);
-// whether a launch shape fits the plan (LDS of the candidate lists)
-bool tuning_fits(const Plan& pl, const ade_tuning& t);
 
 // D of Eq. (3) for a uniform flow (row stride 3); returns its trace.
 double trace_D(int dim, double aL, double aT, double Dm, const double* v, double D[9]);
@@ -67,6 +65,7 @@ struct ade_ctx {
     ade::Plan plan;
     hipStream_t stream = nullptr;
     ade_tuning tuning{256, 2, 0, 0};
+    ade_tuning window{256, 2, 0, 0};  // the shape of launches over row windows (tuning, once it is set)
     ade::PlumeDev* plumes = nullptr;
     ade::TileDev* tiles = nullptr;
     ade::TileDev* pair_tiles = nullptr;

@@ -151,9 +151,8 @@ __device__ __forceinline__ void pair_item(const PairLaunch& a, const PlumeDev* _
 // sum, at least 2^31 in magnitude, rejects it.  Exact in FP64; in FP32 one
 // more rounding, which can move a candidate across r = H only within a
 // rounding of it, where its term is below 1e-35 of a typical one (the
-// neighbour-set export keeps the exact predicate).  EXACT (kModeExact): from its
-// own integer differences, as for one target a lane.
-template <int DIM, bool EXACT, typename Term, typename real, typename Fetch>
+// neighbour-set export keeps the exact predicate).
+template <int DIM, typename Term, typename real, typename Fetch>
 __device__ __forceinline__ void walk_pair(const Term& term, const Target& TA, const Target& TB,
                                           real CA, real CB, uint32_t self, const uint2* list, uint32_t stride,
                                           uint32_t total, Fetch&& fetch, real& accA, real& accB) {
@@ -165,10 +164,7 @@ __device__ __forceinline__ void walk_pair(const Term& term, const Target& TA, co
         const real dy = (real)(int32_t)(TA.uy - c.y);
         const real dz = (DIM == 3) ? (real)(int32_t)(TA.uz - c.z) : (real)0;
         term.sep(dx, dy, dz, CA, c.C, true, accA);
-        if constexpr (EXACT)
-            term.sep((real)(int32_t)(TB.ux - c.x), (real)(int32_t)(TB.uy - c.y), (real)0, CB, c.C, keep, accB);
-        else
-            term.sep(dx + bx, dy + by, dz + bz, CB, c.C, keep, accB);
+        term.sep(dx + bx, dy + by, dz + bz, CB, c.C, keep, accB);
     });
 }
 
@@ -217,7 +213,7 @@ __device__ __forceinline__ void pair_item2(const PairLaunch& a, const PlumeDev* 
     else if (actA) total = build_list<DIM, 1>(P, a.cell_start, TA, list, stride);
     else list[0] = make_uint2(kListEndStart, kListEndEnd);
     const PairTerm<DIM, real, KERN, ZC> term = make_term<DIM, real, KERN, ZC>(P);
-    walk_pair<DIM, (MODE & kModeExact) != 0>(term, TA, TB, CA, CB, iA, list, stride, total, fetch, accA, accB);
+    walk_pair<DIM>(term, TA, TB, CA, CB, iA, list, stride, total, fetch, accA, accB);
     if (actA) finish_target<DIM, real, KERN, MODE>(a, P, Cand<real>{TA.ux, TA.uy, TA.uz, CA}, iA, accA);
     if (merged) finish_target<DIM, real, KERN, MODE>(a, P, Cand<real>{TB.ux, TB.uy, TB.uz, CB}, iB, accB);
 
@@ -311,10 +307,7 @@ __device__ __forceinline__ void pair_item42(const PairLaunch& a, const PlumeDev*
             const real dy = (real)(int32_t)(T0.uy - c.y);
             const real dz = (DIM == 3) ? (real)(int32_t)(T0.uz - c.z) : (real)0;
             term.sep(dx, dy, dz, C0, c.C, true, acc0);
-            if constexpr ((MODE & kModeExact) != 0)
-                term.sep((real)(int32_t)(T1.ux - c.x), (real)(int32_t)(T1.uy - c.y), (real)0, C1, c.C, keep, acc1);
-            else
-                term.sep(dx + bx, dy + by, dz + bz, C1, c.C, keep, acc1);
+            term.sep(dx + bx, dy + by, dz + bz, C1, c.C, keep, acc1);
         });
         if (second) {
             accB = acc0;
@@ -463,7 +456,7 @@ static void launch_pair_l(int mode, const PairLaunch& a, hipStream_t s) {
         hipLaunchKernelGGL(kern, g, b, shm, s, c, c.plumes, c.tiles, nwork);
 }
 
-template <int DIM, typename real, int KERN, bool ZC, int X>
+template <int DIM, typename real, int KERN, bool ZC>
 static void launch_pair_2(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t tpb = 2u * (uint32_t)a.block;
     const uint32_t nwork = a.ntiles * (kTile / tpb);
@@ -472,15 +465,15 @@ static void launch_pair_2(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t grid = (c.persistent > 0) ? max(8u, min(nwork, (uint32_t)c.persistent)) : nwork;
     dim3 g(grid), b(a.block);
     const size_t shm = pair_lds_bytes(a.block, 1, a.list_cap);
-    auto kern = (mode == kModeRhs) ? k_pair2<DIM, real, KERN, kModeRhs + X, ZC>
-                                   : k_pair2<DIM, real, KERN, kModeStep + X, ZC>;
+    auto kern = (mode == kModeRhs) ? k_pair2<DIM, real, KERN, kModeRhs, ZC>
+                                   : k_pair2<DIM, real, KERN, kModeStep, ZC>;
     if (c.ev0)
         hipExtLaunchKernelGGL(kern, g, b, (uint32_t)shm, s, c.ev0, c.ev1, 0u, c, c.plumes, c.tiles, nwork);
     else
         hipLaunchKernelGGL(kern, g, b, shm, s, c, c.plumes, c.tiles, nwork);
 }
 
-template <int DIM, typename real, int KERN, bool ZC, int X>
+template <int DIM, typename real, int KERN, bool ZC>
 static void launch_pair_42(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t tpb = (uint32_t)a.block / 2u;
     const uint32_t nwork = a.ntiles * (kTile / tpb);
@@ -489,37 +482,23 @@ static void launch_pair_42(int mode, const PairLaunch& a, hipStream_t s) {
     const uint32_t grid = (c.persistent > 0) ? max(8u, min(nwork, (uint32_t)c.persistent)) : nwork;
     dim3 g(grid), b(a.block);
     const size_t shm = pair_lds_bytes(a.block, 4, a.list_cap);
-    auto kern = (mode == kModeRhs) ? k_pair42<DIM, real, KERN, kModeRhs + X, ZC>
-                                   : k_pair42<DIM, real, KERN, kModeStep + X, ZC>;
+    auto kern = (mode == kModeRhs) ? k_pair42<DIM, real, KERN, kModeRhs, ZC>
+                                   : k_pair42<DIM, real, KERN, kModeStep, ZC>;
     if (c.ev0)
         hipExtLaunchKernelGGL(kern, g, b, (uint32_t)shm, s, c.ev0, c.ev1, 0u, c, c.plumes, c.tiles, nwork);
     else
         hipLaunchKernelGGL(kern, g, b, shm, s, c, c.plumes, c.tiles, nwork);
 }
 
-template <int DIM, typename real, int KERN, bool ZC, int X>
-static void launch_pair_x(int mode, const PairLaunch& a, hipStream_t s) {
-    if (a.lanes == 1) {
-        launch_pair_2<DIM, real, KERN, ZC, X>(mode, a, s);
-        return;
-    }
-    // two targets a quad: FP32 without coincident particles, else one
-    // target a quad
-    if constexpr (sizeof(real) == 4 && !ZC) launch_pair_42<DIM, real, KERN, ZC, X>(mode, a, s);
-    else launch_pair_l<DIM, real, KERN, 4, ZC>(mode, a, s);
-}
-
 template <int DIM, typename real, int KERN, bool ZC>
 static void launch_pair_z(int mode, const PairLaunch& a, hipStream_t s) {
-    if (a.targets == 2) {
-        if constexpr (DIM == 2 && sizeof(real) == 4) {
-            if (a.exact) {
-                launch_pair_x<DIM, real, KERN, ZC, kModeExact>(mode, a, s);
-                return;
-            }
-        }
-        launch_pair_x<DIM, real, KERN, ZC, 0>(mode, a, s);
-    } else if (a.lanes == 4) launch_pair_l<DIM, real, KERN, 4, ZC>(mode, a, s);
+    if (a.targets == 2 && a.lanes == 4) {
+        // two targets a quad: FP32 without coincident particles, else one
+        // target a quad
+        if constexpr (sizeof(real) == 4 && !ZC) launch_pair_42<DIM, real, KERN, ZC>(mode, a, s);
+        else launch_pair_l<DIM, real, KERN, 4, ZC>(mode, a, s);
+    } else if (a.targets == 2) launch_pair_2<DIM, real, KERN, ZC>(mode, a, s);
+    else if (a.lanes == 4) launch_pair_l<DIM, real, KERN, 4, ZC>(mode, a, s);
     else if (a.lanes == 2) launch_pair_l<DIM, real, KERN, 2, ZC>(mode, a, s);
     else launch_pair_l<DIM, real, KERN, 1, ZC>(mode, a, s);
 }

@@ -1,5 +1,6 @@
-"""Two targets a group of lanes in 2D FP32 contexts of fewer than 2^19 particles: the
-second target's separations are exact integer differences, as for one target."""
+"""Two targets a group of lanes in 2D FP32 contexts of fewer than 2^19 particles: over
+lists the second target's separations are exact integer differences, as for one
+target, and launches over row windows keep one target until a shape is set."""
 import numpy as np
 import pytest
 import torch
@@ -12,9 +13,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n_side,drop,hod,kernel", [(40, 0, 2.0, 4), (45, 3, 1.3, 2), (150, 1, 3.0, 4), (300, 0, 1.5, 4),
                                                     (724, 0, 1.3, 4)])
 def test_two_targets_a_lane_sum_as_one(n_side, drop, hod, kernel):
-    """One lane sums its targets' candidates in the order of their rows, whether it
-    holds one target or two, and those that only the other target has add nothing:
-    the same bits, in right-hand sides (row windows) and steps (lists)."""
+    """One lane sums its targets' entries in the order of their rows, whether it holds one
+    target or two, and those that only the other target has add nothing: the same bits."""
     from paper_2108_09488_amd.context import Context, params_from_spec
     spec = I.config("cfg2_h20_r10", n_side=n_side, h_over_dp=hod, kernel=kernel, jitter=0.1, v=(0.6, 0.8, 0.0))
     x = np.ascontiguousarray(spec.positions()[:, :spec.n - drop])
@@ -25,13 +25,46 @@ def test_two_targets_a_lane_sum_as_one(n_side, drop, hod, kernel):
         print(f"[case] two targets n={x.shape[1]} hod={hod} kernel={kernel} targets={targets}", flush=True)
         c.set_tuning(block=64, lanes=1, targets=targets)
         c.init(torch.from_numpy(x), C).build()
-        r = c.rhs().cpu().numpy()
         c.step(4)
         assert c.lists() == {"built": 1, "read": 1}
-        outs.append((r, c.read_C().cpu().numpy()))
+        c.init(torch.from_numpy(x), C).build()
+        c.adjoint(3, 1, torch.full((2, 1), 0.3, dtype=torch.float64), torch.zeros(1))
+        assert c.lists() == {"built": 1, "read": 1}
+        outs.append(c.read_C().cpu().numpy())
     c.close()
-    assert np.array_equal(outs[0][0], outs[1][0])
-    assert np.array_equal(outs[0][1], outs[1][1])
+    assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("dim,rb,n_side,hod,shape,window", [
+    (2, 4, 361, 3.0, (256, 4, 1), (256, 4, 1)), (2, 4, 363, 3.0, (64, 4, 2), (256, 2, 1)),
+    (2, 4, 513, 3.0, (64, 4, 2), (256, 1, 1)), (2, 4, 513, 2.0, (128, 1, 2), (256, 1, 1)),
+    (2, 4, 723, 2.0, (128, 1, 2), (256, 1, 1)), (2, 4, 726, 2.0, (128, 1, 2), (64, 1, 2)),
+    (2, 4, 726, 1.3, (256, 1, 1), (256, 1, 1)), (2, 4, 1449, 1.3, (256, 1, 1), (64, 1, 2)),
+    (2, 4, 1400, 3.0, (64, 1, 2), (64, 1, 2)), (2, 8, 726, 2.0, (256, 1, 1), (256, 1, 1)),
+    (2, 4, 444, 14.0, (256, 4, 2), (256, 4, 2)), (3, 4, 51, 1.3, (64, 4, 2), (64, 4, 2))])
+def test_shape_of_row_windows(dim, rb, n_side, hod, shape, window):
+    """The right-hand side of a new context is, bit for bit, that of the window shape
+    set by hand, also after an autotuner that keeps the lanes; a shape that is set
+    holds for windows too."""
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    spec = I.config("cfg2_h20_r10" if dim == 2 else "cfg3", n_side=n_side, real_bytes=rb, h_over_dp=hod)
+    x = torch.from_numpy(spec.positions())
+    C = torch.from_numpy(spec.concentration(spec.positions()))
+    c = Context([params_from_spec(spec)], [spec.n])
+    c.init(x, C).build()
+    t = c.get_tuning()
+    print(f"[case] windows dim={dim} rb={rb} n={spec.n} {t}", flush=True)
+    assert (t["block"], t["lanes"], t["targets"]) == shape
+    first = c.rhs().cpu().numpy()
+    if spec.n < 300000:
+        c.autotune(reps=1, keep_lanes=True)
+        assert np.array_equal(c.rhs().cpu().numpy(), first)
+    c.set_tuning(block=window[0], lanes=window[1], targets=window[2])
+    assert np.array_equal(c.rhs().cpu().numpy(), first)
+    c.set_tuning(block=64, lanes=4, targets=1)
+    four = c.rhs().cpu().numpy()
+    assert (window[1:] == (4, 1)) == np.array_equal(four, first)
+    c.close()
 
 
 def test_two_lanes_share_a_list_without_a_side():
