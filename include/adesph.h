@@ -152,12 +152,21 @@ typedef struct {
  * neighbour lists: about 2 bytes (2D) or 4 bytes (3D) per neighbour and
  * particle with a margin, for plumes of at most 2000 expected neighbours per
  * particle; none when a context's lists would pass 16 GiB, or in 2D when 2 bytes
- * for each neighbour of each particle come to more than 384 MiB (768 MiB in FP64). */
+ * for each neighbour of each particle come to more than 384 MiB (768 MiB in FP64).
+ * Lists are most of a 3D context's workspace (128^3 FP32 with 256 neighbours 3.2 GB,
+ * 0.33 without). */
 int ade_workspace_bytes(const ade_params *params, const int64_t *counts, int32_t nplumes,
                         size_t *bytes);
 
+/* The least workspace that ade_create takes: without room for neighbour lists.  A
+ * context made with less than ade_workspace_bytes keeps none, and its steps walk the
+ * cells. */
+int ade_workspace_bytes_min(const ade_params *params, const int64_t *counts, int32_t nplumes,
+                            size_t *bytes);
+
 /* Validates the parameters and lays out the caller's workspace d_ws
- * (ws_bytes >= ade_workspace_bytes, 256-byte aligned); stream is a
+ * (ws_bytes >= ade_workspace_bytes, or, for a context without neighbour lists, >=
+ * ade_workspace_bytes_min; 256-byte aligned); stream is a
  * hipStream_t (NULL: the default stream).  *out receives the context.  A
  * context holds at most 2^28 - 256 particles in total (candidate records are
  * addressed with 32-bit byte offsets); larger ensembles take several
@@ -166,7 +175,7 @@ int ade_workspace_bytes(const ade_params *params, const int64_t *counts, int32_t
  * where the context's cell tables would pass the 160 MiB budget, since the
  * default x cells then widen for the whole context), the same lanes and
  * targets, and neighbour lists read by the same steps (a context whose lists
- * would take too much, ade_workspace_bytes, keeps none; the first two steps of a
+ * would take too much, ade_workspace_bytes, or have no room keeps none; the first two steps of a
  * large one, ade_step): these fix the order of every sum. */
 int ade_create(const ade_params *params, const int64_t *counts, int32_t nplumes, void *d_ws,
                size_t ws_bytes, void *stream, ade_ctx **out);

@@ -22,7 +22,7 @@ ERROR_NAMES = {0: "ADE_OK", -1: "ADE_EINVAL", -2: "ADE_EWORKSPACE", -3: "ADE_EHI
                -4: "ADE_EUNSTABLE", -5: "ADE_ENONFINITE", -6: "ADE_ESTATE"}
 
 # every entry point declared in include/adesph.h
-EXPORTS = ["ade_workspace_bytes", "ade_create", "ade_init_particles", "ade_set_velocities", "ade_build_cells",
+EXPORTS = ["ade_workspace_bytes", "ade_workspace_bytes_min", "ade_create", "ade_init_particles", "ade_set_velocities", "ade_build_cells",
            "ade_coincident", "ade_lists",
            "ade_step", "ade_step_graph", "ade_rhs", "ade_read_C", "ade_read_x", "ade_mass", "ade_conc_range",
            "ade_neighbours", "ade_sensor_interp", "ade_adjoint_workspace_bytes", "ade_adjoint",
@@ -70,6 +70,7 @@ def lib() -> ct.CDLL:
     pi64, pd, psz = ct.POINTER(ct.c_int64), ct.POINTER(ct.c_double), ct.POINTER(ct.c_size_t)
     sigs = {
         "ade_workspace_bytes": [P, p, i32, psz],
+        "ade_workspace_bytes_min": [P, p, i32, psz],
         "ade_create": [P, p, i32, p, sz, p, ct.POINTER(p)],
         "ade_init_particles": [p, p, p],
         "ade_set_velocities": [p, p],

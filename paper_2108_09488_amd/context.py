@@ -36,9 +36,12 @@ class Context:
     params  : sequence of AdeParams (or PlumeSpec), one per plume
     counts  : particles per plume
     stream  : torch.cuda.Stream to enqueue on (default: the current stream)
+    lists   : whether the workspace has room for the neighbour lists of a uniform
+              flow (most of a 3D context's memory); without it, or where the GPU
+              has no memory left for it, steps walk the cells
     """
 
-    def __init__(self, params: Sequence, counts: Sequence[int], device="cuda:0", stream=None):
+    def __init__(self, params: Sequence, counts: Sequence[int], device="cuda:0", stream=None, lists: bool = True):
         L = lib()
         ps = [p if isinstance(p, AdeParams) else params_from_spec(p) for p in params]
         self.nplumes = len(ps)
@@ -49,10 +52,17 @@ class Context:
         self.dtype = torch.float32 if self.real_bytes == 4 else torch.float64
         self.device = torch.device(device)
         self.N = int(sum(int(c) for c in counts))
-        nb = ct.c_size_t(0)
+        nb, least = ct.c_size_t(0), ct.c_size_t(0)
         check(L.ade_workspace_bytes(self._params, self._counts, self.nplumes, ct.byref(nb)))
-        self.ws_bytes = nb.value
-        self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
+        check(L.ade_workspace_bytes_min(self._params, self._counts, self.nplumes, ct.byref(least)))
+        self.ws_bytes = nb.value if lists else least.value
+        try:
+            self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
+        except torch.cuda.OutOfMemoryError:
+            if self.ws_bytes == least.value:
+                raise
+            self.ws_bytes = least.value
+            self.ws = torch.empty(self.ws_bytes, dtype=torch.uint8, device=self.device)
         self.stream = stream if stream is not None else torch.cuda.current_stream(self.device)
         self._inputs_ready(self.ws)  # memory that work on the current stream may still use
         h = ct.c_void_p()
@@ -286,12 +296,13 @@ class Context:
         return J.value, [g[0], g[1], g[2]]
 
 
-def workspace_bytes(params, counts) -> int:
+def workspace_bytes(params, counts, lists: bool = True) -> int:
     ps = [p if isinstance(p, AdeParams) else params_from_spec(p) for p in params]
     arr = (AdeParams * len(ps))(*ps)
     cn = (ct.c_int64 * len(ps))(*[int(c) for c in counts])
     nb = ct.c_size_t(0)
-    check(lib().ade_workspace_bytes(arr, cn, len(ps), ct.byref(nb)))
+    size = lib().ade_workspace_bytes if lists else lib().ade_workspace_bytes_min
+    check(size(arr, cn, len(ps), ct.byref(nb)))
     return nb.value
 
 

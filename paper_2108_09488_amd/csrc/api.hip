@@ -158,6 +158,10 @@ ade_tuning window_tuning(const Plan& pl, const ade_tuning& t) {
 // rows its targets reach hold fewer than 65536 particles).  A list has room for
 // the expected entries (two targets share up to 1.31 times one's) and a margin;
 // a plume whose particles need more walks the row windows.
+// The lists are most of a 3D context's memory (128^3 with 256 neighbours 2.9 GB beside
+// 0.33 GB, 200^3 11.4 beside 0.86), which a caller may decline (ade_workspace_bytes_min);
+// they pay as far as the budget goes (a step with and without: 200^3 with 256 neighbours
+// 1.90 and 3.40 ms, 256^3 with 70 1.58 and 3.12, 128^3 FP64 with 108 0.45 and 1.21).
 constexpr size_t kListBudget = size_t(16) << 30;  // bytes; contexts whose lists would take more keep none
 // In 2D a step's reading of the lists has to stay near the 256 MB of the last-level
 // cache: with one target a group, 2 bytes per neighbour, the 256-plume ensemble reads
@@ -510,7 +514,7 @@ int plan_build(const ade_params* params, const int64_t* counts, int32_t nplumes,
 
 namespace {
 
-void layout(Bump& b, ade_ctx* c, const Plan& pl) {
+void layout(Bump& b, ade_ctx* c, const Plan& pl, bool lists = true) {
     const size_t N = (size_t)pl.N;
     const size_t rb = (size_t)pl.real_bytes;
     c->plumes = b.take<PlumeDev>(pl.P);
@@ -559,7 +563,7 @@ void layout(Bump& b, ade_ctx* c, const Plan& pl) {
     }
     // the lists of any launch shape: all or none of them fit the budget
     c->list_bytes = 0;
-    for (int shape = 0; shape < 5; ++shape) {
+    for (int shape = 0; lists && shape < 5; ++shape) {
         const size_t need = list_plan(pl, shape == 0 || shape == 3 ? 1 : shape == 1 ? 2 : 4, shape < 3 ? 1 : 2).bytes;
         if (need == 0) {
             c->list_bytes = 0;
@@ -1023,6 +1027,18 @@ int ade_workspace_bytes(const ade_params* params, const int64_t* counts, int32_t
     return ADE_OK;
 }
 
+int ade_workspace_bytes_min(const ade_params* params, const int64_t* counts, int32_t nplumes, size_t* bytes) {
+    if (!bytes) return fail(ADE_EINVAL, "null bytes");
+    Plan pl;
+    int rc = plan_build(params, counts, nplumes, pl);
+    if (rc) return rc;
+    Bump b(nullptr);
+    ade_ctx tmp;
+    layout(b, &tmp, pl, false);
+    *bytes = b.off + 256;
+    return ADE_OK;
+}
+
 int ade_create(const ade_params* params, const int64_t* counts, int32_t nplumes, void* d_ws,
                size_t ws_bytes, void* stream, ade_ctx** out) {
     if (!out) return fail(ADE_EINVAL, "null out");
@@ -1052,6 +1068,10 @@ int ade_create(const ade_params* params, const int64_t* counts, int32_t nplumes,
     }
     Bump b(d_ws);
     layout(b, c, c->plan);
+    if (b.off + 256 > ws_bytes && c->list_bytes > 0) {  // no room for lists: a context without them
+        b = Bump(d_ws);
+        layout(b, c, c->plan, false);
+    }
     c->window = window_tuning(c->plan, c->tuning);
     if (c->list_bytes == 0) c->tuning = c->window;
     if (b.off + 256 > ws_bytes) {
