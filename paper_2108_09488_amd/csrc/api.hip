@@ -708,24 +708,32 @@ static void set_shape(const ade_ctx* c, PairLaunch& a, const ade_tuning& t) {
 
 static int shape_of(const ade_tuning& t) { return 4 * t.lanes + targets_of(t); }
 
-// launch a pair kernel; when timing is on, events stamped with the kernel's
-// own start and end times are attached to the launch
-int run_pair(ade_ctx* c, int mode, const PairLaunch& a) {
+// The pair kernels of a step or a right-hand side: launch 0 is a itself, and with lists
+// launch 1 those of the plumes that have none.
+static int pair_launches(const ade_ctx* c, const PairLaunch& a) { return a.list && c->win_ntiles > 0 ? 2 : 1; }
+static hipError_t launch_pair_of(const ade_ctx* c, int mode, const PairLaunch& a, int i, hipEvent_t e0, hipEvent_t e1) {
     const Plan& pl = c->plan;
     PairLaunch b = a;
-    b.ev0 = b.ev1 = nullptr;
-    int rc = take_events(c, b.ev0, b.ev1);
-    if (rc) return rc;
-    HIPCHK(launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->stream));
-    if (a.list && c->win_ntiles > 0) {  // the plumes without lists
+    if (i == 1) {
         b.list = nullptr;
         set_shape(c, b, c->window);
         b.step = nullptr;
         b.tiles = c->win_tiles;
         b.ntiles = c->win_ntiles;
-        b.ev0 = b.ev1 = nullptr;
-        if ((rc = take_events(c, b.ev0, b.ev1))) return rc;
-        HIPCHK(launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->stream));
+    }
+    b.ev0 = e0;
+    b.ev1 = e1;
+    return launch_pair(pl.dim, pl.real_bytes, pl.kernel, mode, b, c->stream);
+}
+
+// launch the pair kernels; when timing is on, events stamped with each kernel's
+// own start and end times are attached to its launch
+int run_pair(ade_ctx* c, int mode, const PairLaunch& a) {
+    for (int i = 0; i < pair_launches(c, a); ++i) {
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        int rc = take_events(c, e0, e1);
+        if (rc) return rc;
+        HIPCHK(launch_pair_of(c, mode, a, i, e0, e1));
     }
     return ADE_OK;
 }
@@ -1349,29 +1357,50 @@ static int clear_counts(ade_ctx* c) {
     return ADE_OK;
 }
 
-// Times the candidate launch shapes of a tuner: `launch(k)` enqueues
-// candidate k's step-mode kernel with the events around it (a velocity
-// field's leaves cell counts, which are cleared).  The clocks of the GPU rise only under sustained
+// Times the candidate launch shapes of a tuner: `launch(k, n)` enqueues
+// candidate k's step-mode kernels, n launches, with the events ev[2 i], ev[2 i + 1]
+// around launch i (a velocity field's leaves cell counts, which are cleared).  The clocks of the GPU rise only under sustained
 // load and fall again within seconds of idling (a context timed back to back
 // ran 10% faster from its second timing on; with 2 s idle between timings it
 // never did), so the GPU is first kept busy for ~50 ms with the first
 // candidate, and every round then times each candidate once (round 0
 // untimed), so that a drift of the clocks weighs on all candidates alike.
-static int time_candidates(ade_ctx* c, int ncand, int32_t reps, hipEvent_t e0, hipEvent_t e1,
-                           const std::function<hipError_t(int)>& launch, int* best) {
+struct TuneEvents {
+    hipEvent_t ev[4] = {};
+    hipError_t create() {
+        for (hipEvent_t& e : ev) {
+            const hipError_t rc = hipEventCreate(&e);
+            if (rc != hipSuccess) return rc;
+        }
+        return hipSuccess;
+    }
+    ~TuneEvents() {
+        for (hipEvent_t e : ev)
+            if (e) hipEventDestroy(e);
+    }
+};
+static int time_candidates(ade_ctx* c, int ncand, int32_t reps, const TuneEvents& e,
+                           const std::function<hipError_t(int, int*)>& launch, int* best) {
+    int n = 0;
     auto timed = [&](int k, float* ms) -> int {
-        if (launch(k) != hipSuccess) return fail(ADE_EHIP, "autotune launch");
+        if (launch(k, &n) != hipSuccess) return fail(ADE_EHIP, "autotune launch");
         int rc = c->plan.general ? clear_counts(c) : ADE_OK;
         if (rc) return rc;
-        if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(ms, e0, e1) != hipSuccess)
-            return fail(ADE_EHIP, "event synchronise");
+        *ms = 0.f;
+        for (int i = 0; i < n; ++i) {
+            float one = 0.f;
+            if (hipEventSynchronize(e.ev[2 * i + 1]) != hipSuccess ||
+                hipEventElapsedTime(&one, e.ev[2 * i], e.ev[2 * i + 1]) != hipSuccess)
+                return fail(ADE_EHIP, "event synchronise");
+            *ms += one;
+        }
         return ADE_OK;
     };
     float one = 0.f;
     int rc = timed(0, &one);
     const int warm = std::min(4000, (int)std::ceil(50.0 / std::max(one, 0.01f)));
     for (int k = 0; !rc && k < warm; ++k) {
-        if (launch(0) != hipSuccess) rc = fail(ADE_EHIP, "autotune launch");
+        if (launch(0, &n) != hipSuccess) rc = fail(ADE_EHIP, "autotune launch");
         else if (c->plan.general) rc = clear_counts(c);
     }
     std::vector<float> tot((size_t)ncand, 0.f);
@@ -1400,23 +1429,21 @@ static int autotune_gen(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* bes
         }
     }
     if (cands.empty()) return fail(ADE_EINVAL, "no launch shape fits");
-    hipEvent_t e0, e1;
-    HIPCHK(hipEventCreate(&e0));
-    HIPCHK(hipEventCreate(&e1));
+    TuneEvents e;
+    HIPCHK(e.create());
     int kbest = 0;
-    int rc = time_candidates(c, (int)cands.size(), reps, e0, e1,
-                             [&](int k) {
+    int rc = time_candidates(c, (int)cands.size(), reps, e,
+                             [&](int k, int* n) {
                                  c->tuning = cands[(size_t)k];
                                  GenLaunch g = gen_args(c, nullptr);
-                                 g.ev0 = e0;
-                                 g.ev1 = e1;
+                                 g.ev0 = e.ev[0];
+                                 g.ev1 = e.ev[1];
+                                 *n = 1;
                                  return launch_pair_gen(pl.dim, pl.real_bytes, pl.kernel, kModeStep, g, c->stream);
                              },
                              &kbest);
     const int rc_clear = clear_counts(c);
     if (!rc) rc = rc_clear;
-    hipEventDestroy(e0);
-    hipEventDestroy(e1);
     c->tuning = rc ? start : cands[(size_t)kbest];
     drop_graph(c);
     if (rc) return rc;
@@ -1447,24 +1474,27 @@ int ade_autotune(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* best) {
                 }
     }
     if (cands.empty()) return fail(ADE_EINVAL, "no launch shape fits");
-    hipEvent_t e0, e1;
-    HIPCHK(hipEventCreate(&e0));
-    HIPCHK(hipEventCreate(&e1));
+    TuneEvents e;
+    HIPCHK(e.create());
     int kbest = 0;
-    // the update-mode kernel, as a step runs it, to the second C buffer
-    int rc = time_candidates(c, (int)cands.size(), reps, e0, e1,
-                             [&](int k) {
+    // the update-mode kernels, as a step runs them, to the second C buffer; a shape
+    // whose lists are not there has them built, and then runs once untimed
+    int rc = time_candidates(c, (int)cands.size(), reps, e,
+                             [&](int k, int* n) {
                                  c->tuning = c->window = cands[(size_t)k];
+                                 const bool there = c->list_shape == shape_of(c->tuning);
                                  if (settle_lists(c) != ADE_OK) return hipErrorUnknown;
-                                 PairLaunch a =
+                                 const PairLaunch a =
                                      pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, c->aux, c->aux_rec);
-                                 a.ev0 = e0;
-                                 a.ev1 = e1;
-                                 return launch_pair(pl.dim, pl.real_bytes, pl.kernel, kModeStep, a, c->stream);
+                                 *n = pair_launches(c, a);
+                                 hipError_t rc = hipSuccess;
+                                 for (int r = there || !c->list_use ? 1 : 0; r < 2; ++r)
+                                     for (int i = 0; i < *n && rc == hipSuccess; ++i)
+                                         rc = launch_pair_of(c, kModeStep, a, i, r ? e.ev[2 * i] : nullptr,
+                                                             r ? e.ev[2 * i + 1] : nullptr);
+                                 return rc;
                              },
                              &kbest);
-    hipEventDestroy(e0);
-    hipEventDestroy(e1);
     c->tuning = rc ? start : cands[(size_t)kbest];
     // (kept lanes are also those of the windows)
     const bool keep = (flags & ADE_TUNE_KEEP_LANES) && shape_of(window0) != shape_of(start);
