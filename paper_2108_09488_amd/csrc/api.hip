@@ -1500,7 +1500,7 @@ int ade_autotune(ade_ctx* c, int32_t reps, int32_t flags, ade_tuning* best) {
     const bool keep = (flags & ADE_TUNE_KEEP_LANES) && shape_of(window0) != shape_of(start);
     c->window = rc || keep ? window0 : c->tuning;
     drop_graph(c);
-    if (rc) return rc;
+    if (rc || (rc = settle_lists(c))) return rc;  // the lists that the next steps read
     if (best) *best = c->tuning;
     return ADE_OK;
 }

@@ -56,3 +56,19 @@ def test_timing_of_more_launches_than_events():
     ms, n = c.timing_stop()
     assert n == 3001 and ms > 0.0
     c.close()
+
+
+def test_a_tuned_context_has_its_lists():
+    """The lists of the shape that the autotuner chose stand when it returns."""
+    from paper_2108_09488_amd.context import Context, params_from_spec
+    a = I.config("cfg2_h20_r10", n_side=200)
+    x = a.positions()
+    c = Context([params_from_spec(a)], [a.n])
+    c.init(torch.from_numpy(x), torch.from_numpy(a.concentration(x))).build()
+    c.autotune(reps=1)
+    assert c.lists()["built"] == 1
+    c.step(1)
+    assert c.lists() == {"built": 1, "read": 0}  # the first two steps of a large context walk the windows
+    c.step(2)
+    assert c.lists() == {"built": 1, "read": 1}
+    c.close()
