@@ -13,7 +13,7 @@ divided by the wall time of the timed region.
 
 Also reported: the roofline of the pair kernel (HIP events on its eager
 launches), the 2D consistency sweep (six 512^2 plumes in one context), the
-batched ensemble (256 plumes of 32^2..256^2 particles, 200 graph-replayed
+batched ensemble (256 plumes of 32^2..256^2 particles, 200
 steps), the inverse problem (forward + adjoint), the velocity-field plume and
 the paper-scale problems, each with the pair kernel's roofline, and the FP64
 CPU oracle on a bounded sample of the headline workload (cpu_baseline).
@@ -158,8 +158,7 @@ def time_sweep(sweep, steps, warmup, graph):
 def batched(device, steps, warmup, n_plumes=256):
     """The ensemble: 256 plumes of 32^2..256^2 particles with their own
     dispersivities, flow directions and time steps, in one context: one
-    launch per kernel per step for all plumes, steps replayed from a HIP
-    graph, launch shape (work-item size, lanes and targets per lane,
+    launch per kernel per step for all plumes, launch shape (work-item size, lanes and targets per lane,
     persistent grid or not, XCD dealing) picked by the autotuner."""
     import numpy as np
     import torch
@@ -210,7 +209,7 @@ def batched(device, steps, warmup, n_plumes=256):
     return {"plumes": n_plumes, "particles": n, "interactions_per_step": inter,
             "steps": steps, "ms_per_step": 1e3 * wall / steps, "tuning": tuned,
             "interactions_per_s": rate,
-            "plain_same_nbar": {"workload": "one 512^2 plume, h/dp 1.5, C4, FP32, graph replay",
+            "plain_same_nbar": {"workload": "one 512^2 plume, h/dp 1.5, C4, FP32",
                                 "neighbours_mean": rinter / ref.n, "interactions_per_s": plain},
             "vs_plain_same_nbar": rate / plain,
             "roofline": roofline_alu(2, inter, pms / pn, list_kernel_name(tuned, coincident=coincident), pn)}
@@ -297,9 +296,10 @@ def parse_shape(text):
 
 def headline_3d(device, steps, warmup, shape=None):
     """The 3D plume (128^3 particles, h = 2 dp, FP32): autotuned launch shape
-    (or the given one), `steps` steps replayed from the captured graph after
-    `warmup` (the timed region), then the same number of eager steps with HIP
-    events around every pair-kernel launch (the roofline)."""
+    (or the given one), `steps` steps of one ade_step_graph call after `warmup`
+    (the timed region; runs of fewer than 512 steps are launched one by one), then
+    the same number of steps with HIP events around every pair-kernel launch (the
+    roofline)."""
     import numpy as np
     import torch
     from paper_2108_09488_amd import inputs as I
@@ -634,11 +634,11 @@ def main():
         torch.cuda.synchronize()
         del src, dst
 
-    # the headline: the 3D plume, graph-replayed steps
+    # the headline: the steps of the 3D plume
     h = headline_3d(device, args.steps, args.warmup, parse_shape(args.shape_3d))
     inter3 = h["interactions_per_step"]
     value = inter3 * args.steps / h["wall"]
-    print(f"[bench] 3D plume: {1e3 * h['wall'] / args.steps:.3f} ms/step (graph), pair kernel "
+    print(f"[bench] 3D plume: {1e3 * h['wall'] / args.steps:.3f} ms/step, pair kernel "
           f"{1e3 * h['roofline']['avg_launch_ms']:.1f} us", file=sys.stderr, flush=True)
     extras = {"eager": h["eager"]}
     want = set() if args.no_extras else set(args.extras.split(","))
@@ -667,11 +667,11 @@ def main():
             "eager_ms_per_step": 1e3 * ewall / args.steps,
             "roofline": roofline_alu(2, inter_step, pair["ms_total"] / pair["launches"], kname,
                                      pair["launches"], profile=TRAFFIC_PROFILE)}
-        print(f"[bench] sweep: {1e3 * wall / args.steps:.3f} ms/step (graph)", file=sys.stderr, flush=True)
+        print(f"[bench] sweep: {1e3 * wall / args.steps:.3f} ms/step", file=sys.stderr, flush=True)
     if "batched" in want:
         b = batched(device, steps=200, warmup=args.warmup)
         b["vs_plain"] = b["interactions_per_s"] / extras["sweep"]["interactions_per_s"] if "sweep" in extras else None
-        b["vs_plain_workload"] = "the six-plume 2D sweep context (graph replay)"
+        b["vs_plain_workload"] = "the six-plume 2D sweep context"
         extras["batched"] = b
         print(f"[bench] batched: {b['ms_per_step']:.3f} ms/step", file=sys.stderr, flush=True)
     if "fwd_adjoint" in want:

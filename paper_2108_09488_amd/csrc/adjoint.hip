@@ -984,9 +984,9 @@ int adjoint_uniform(ade_ctx* c, const AdjLayout& L, int64_t nsteps, int32_t K, c
         for (int k = 0; k < pl.dim; ++k) sp += P.vel[k] * P.vel[k];
         base.speed = std::sqrt(sp);
     }
-    // the lists of the forward run, if the plume has them: workgroups of 256
-    // threads, or of 64 where those would not fill the chip; at most
-    // kAdjMaxSubs of them a tile
+    // the lists of the forward run, if the plume has them; the wavefronts of a tile in
+    // at most kAdjMaxSubs workgroups: of 64 threads with one lane to one or two targets, of
+    // 128 with two lanes to one or four to two, of 256 with four to one
     const PairLaunch fwd = pair_args(c, c->S.C, c->S.rec, c->S.C, 1.0, nullptr, nullptr);
     base.list = fwd.list;
     base.waves = fwd.waves;

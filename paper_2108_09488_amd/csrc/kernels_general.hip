@@ -127,8 +127,8 @@ struct GPart {
 // Read from the particle's record (RECORD), or from the structure-of-arrays
 // state.  The records' loads return 16 bytes a lane: read as 13 separate
 // components, the 3D FP32 kernel was bound by the vector cache's return path
-// (busy 98% of its 528 us at 61^3 particles, 18 cycles a load, the VALU 36%); with
-// the records it takes 310 us.
+// (busy 92% of the cycles at 61^3 particles, the VALU 35% of its slots, 538 us under
+// the tracer); with the records it takes 332 us, at less than half the accesses.
 template <int DIM, typename real, bool RECORD>
 __device__ __forceinline__ GPart<DIM, real> load_part(const StateArrays& S, uint32_t k) {
     GPart<DIM, real> p;

@@ -9,9 +9,9 @@
 // row windows of kernels_pair.hip hold 1.5 (2D) to 2 (3D) candidates per
 // neighbour and cost a window search and a cursor per launch.
 //
-// What bounds it: VALU issue (84% of the slots in 3D, 70% in the 2D sweep), with
-// the L1 lookups of the gathers close behind (short lists of 26 neighbours: 64%
-// and 67%).  The list costs 2 bytes (2D) or 4 (3D) per entry and launch.
+// What bounds it: VALU issue (86% of the slots in 3D, 65% in the 2D sweep), with
+// the L1 lookups of the gathers close behind in 2D.  The list costs 2 bytes (2D) or
+// 4 (3D) per entry and launch.
 // Measured per update launch against the row windows: 128^3 plume (256
 // neighbours) 870 -> 475 us, the six-plume sweep 96 -> 68 us, the 256-plume
 // ensemble 235 -> 201 us, a 512^2 plume (46 neighbours) 24 -> 13.5 us; the build
