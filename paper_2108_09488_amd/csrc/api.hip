@@ -857,7 +857,12 @@ static bool few_launches(const ade_ctx* c, int64_t nsteps) {
 // call under capture walks the row windows instead.
 int settle_lists(ade_ctx* c, int64_t nsteps) {
     c->list_use = false;
-    if (c->plan.general || c->list_bytes == 0 || in_capture(c) || few_launches(c, nsteps)) return ADE_OK;
+    if (c->plan.general || c->list_bytes == 0) return ADE_OK;
+    if (in_capture(c)) {
+        c->since = int64_t(1) << 62;  // the caller's graph may run the steps any number of times
+        return ADE_OK;
+    }
+    if (few_launches(c, nsteps)) return ADE_OK;
     c->list_used = true;
     if (c->list_shape != shape_of(c->tuning)) {
         std::vector<uint32_t> h;

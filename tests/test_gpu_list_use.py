@@ -144,6 +144,28 @@ def test_captured_calls_read_none(dim, n_side):
     c.close()
 
 
+def test_steps_behind_a_captured_call_read_lists():
+    """A captured step may have been replayed often, so the next eager step of a large
+    context is not one of the first two behind the build."""
+    stream = torch.cuda.Stream()
+    spec = I.config("cfg2_h20_r10", n_side=160)
+    c = _context([spec], [spec.positions()], stream)
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        c.step(1)
+    for _ in range(5):
+        with torch.cuda.stream(stream):
+            g.replay()
+    c.step(1)
+    assert c.lists() == {"built": 1, "read": 1} and c.info()["step"] == 6
+    before = c.read_C().cpu().numpy()
+    _init(c, [spec], [spec.positions()]).step(1)  # new particles start from their build
+    assert c.lists() == {"built": 0, "read": 0}
+    assert not np.array_equal(before, c.read_C().cpu().numpy())
+    c.close()
+
+
 def test_velocity_fields_and_dense_plumes_have_none():
     from paper_2108_09488_amd import _lib
     from paper_2108_09488_amd.context import Context, params_from_spec
