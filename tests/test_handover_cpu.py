@@ -29,7 +29,7 @@ class Library:
     def __getattr__(self, name):
         def call(*args):
             if "workspace_bytes" in name:
-                args[-1]._obj.value = 512
+                args[-1]._obj.value = 256 if name.endswith("_min") else 512
             self.log.append((name, [a.value for a in args if isinstance(a, ct.c_void_p)]))
             return 0
         return call
@@ -85,3 +85,26 @@ def test_nothing_to_hand_over_on_one_stream(fake):
     log, cur, _ = fake
     _context(cur)
     assert not any(e[0] in ("wait", "record") for e in log)
+
+
+def test_no_memory_for_lists(fake, monkeypatch):
+    """A context whose full workspace does not fit takes the least one; where that does
+    not fit either, or was asked for, the error is the allocator's."""
+    log, _, own = fake
+    empty = torch.empty
+    limit = [300]
+
+    def scarce(n, **kw):
+        if n > limit[0]:
+            raise torch.cuda.OutOfMemoryError("out of memory")
+        return empty(n, **kw)
+
+    monkeypatch.setattr(torch, "empty", scarce)
+    _, c = _context(own)
+    assert c.ws_bytes == 256 and c.ws.numel() == 256
+    limit[0] = 100
+    with pytest.raises(torch.cuda.OutOfMemoryError):
+        _context(own)
+    limit[0] = 1000
+    _, c = _context(own)
+    assert c.ws_bytes == 512
